@@ -204,7 +204,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 most C/16 when the coupling exceeds 1e-6, at most what the GPU holds.  Concurrent coordinates read each other's stale shared-vector
  *                 entries; strongly coupled problems need a small window to keep the per-epoch
  *                 convergence of the sequential algorithm.
- *   "group"       lanes per coordinate: 0 = by segment length (default), 4, 8, 16, 32, 64, or
+ *   "group"       lanes per coordinate: 0 = by segment length (default; wider, up to 64, while a
+ *                 binding window leaves the GPU short of waves), 4, 8, 16, 32, 64, or
  *                 256 (one workgroup per coordinate).
  *   "fresh_reads" 1 = gather the shared vector with device-scope loads (bypass non-coherent
  *                 caches), 0 = plain loads.
@@ -212,12 +213,15 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 (shared vector below 2 GiB; with skewed segment lengths only when each
  *                 in-flight coordinate can have a workgroup of its own, then with workgroups
  *                 taking positions from a queue), 0 = the plain kernels.
- *   "spread"      1 (default) = when the shared vector has at most 4 M entries and the window
- *                 does not bind (every coordinate may be in flight), the pipelined kernel runs on a
- *                 copy that holds one entry per 64 bytes (scd_epochs copies it out before its
+ *   "spread"      1 (default) = when the shared vector has at most 4 M entries, the pipelined kernel
+ *                 runs on a copy that holds one entry per 64 bytes (scd_epochs copies it out before its
  *                 epochs and back after them, on the same stream), so that the gathers of one
  *                 coordinate do not wait behind other coordinates' atomics on neighbouring
- *                 entries; 0 = it runs on the packed vector.
+ *                 entries.  It does so when the window does not bind (every coordinate may be in
+ *                 flight), and with a binding window when the coordinates in flight hold at least
+ *                 4,096 entries, a segment has at most one entry per 32 of the shared vector on
+ *                 average, and there are at least two stored entries per shared-vector entry;
+ *                 0 = it runs on the packed vector.
  *   "queue_chunk" consecutive permutation positions each workgroup of the queued kernel claims
  *                 at a time: 0 (default) = 1 per 64 coordinates in flight (at least 1), else
  *                 1..64.  Larger chunks lower the claim rate on the queue's counter and let

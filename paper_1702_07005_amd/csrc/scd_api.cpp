@@ -252,6 +252,40 @@ int64_t pipe_groups(const scd_solver* h, int64_t window, int64_t groups) {
     return std::max<int64_t>(1, groups * 4 / 5);
 }
 
+// Whether a pipelined plan should run on the spread copy of the shared vector (one entry per 64 bytes).
+// Packed, the gathers of entries whose 64-byte segment other coordinates' atomics are updating wait
+// behind those atomics (measured: gather-and-atomic pairs on 100,000 packed fp32 entries at 9.5 G/s,
+// spread at 20 G/s, the rate of the atomics alone).  That binds when every coordinate may be in flight
+// (the window does not bind), and with a binding window once the coordinates in flight hold a few
+// thousand entries: columns of 100 entries on 100,000 rows, one wave per column, packed against spread:
+// 32 in flight 2.68 and 2.35 ms an epoch, 300 0.65 and 0.34, 632 0.56 and 0.27, 4,000 0.54 and 0.26;
+// columns of 20 entries on 20,000 rows, 281 in flight: 67 and 46 us; rows of 370 entries on 166,000
+// columns, 6 in flight (2,200 entries): 1.22 and 1.23 ms, bound by latency either way.  Not where a
+// segment holds neighbouring entries (2,000 x 200 dense: 47 and 107 us at 8 in flight): it would touch
+// one 64-byte segment per entry instead of one per 16.  Nor where the copies in and out (64 bytes per
+// entry, 4.4 us each way at 100,000) could take longer than the gathers they save.
+constexpr double kSpreadMinInFlight = 4096.0;  // entries of the coordinates in flight
+bool spread_pays(const scd_solver* h, int64_t window, int64_t groups) {
+    if (window >= h->C) return true;
+    const double mean = (double)h->nnz / (double)h->C;
+    return (double)groups * mean >= kSpreadMinInFlight && mean * 32.0 <= (double)h->L && h->nnz >= 2 * h->L;
+}
+
+// Lanes per coordinate of a pipelined plan whose window binds: wider groups than the segment length
+// asks for (auto_group, the fewest lanes that hold a segment) while the coordinates in flight leave the
+// GPU short of waves.  A wave that holds several coordinates issues their gathers and atomics as one
+// instruction stream of many slices, and all wait for the slowest; with a wave of its own a coordinate
+// takes one or two.  Measured at G = auto and G = 64: 50,000 columns of 100 entries (auto 16), 32 in
+// flight 9.6 and 2.7 ms an epoch, 632 0.74 and 0.56 (on the spread copy 0.55 and 0.27); 500,000 click
+// rows (auto 8) 32 in flight 37.0 and 15.8, 300 5.2 and 2.9, 1,000 2.45 and 2.50, 4,000 1.41 and 2.0.
+// Hence at most three waves per CU.
+constexpr int64_t kWideGroupWavesPerCU = 3;
+int wide_group(const scd_solver* h, int G, int64_t groups) {
+    for (int wide = 64; wide > G; wide /= 2)
+        if (groups * wide <= (int64_t)h->cus * kWideGroupWavesPerCU * 64) return wide;
+    return G;
+}
+
 // The staged variant: option 2, or option 1 with a matrix beyond the Infinity Cache; it needs its ring and
 // enough CUs for the stagers (all on the XCD of the hot-set workgroup).
 bool staged_plan(const scd_solver* h) {
@@ -331,7 +365,7 @@ bool split_fits(const scd_solver* h, uint32_t part) {
 int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
     memset(lp, 0, sizeof *lp);
     lp->fresh = (int)h->fresh;
-    const int G = h->group ? (int)h->group : auto_group(h);
+    int G = h->group ? (int)h->group : auto_group(h);
     const int64_t window = h->window ? h->window : h->auto_window;
     lp->wide = h->wide;
     const int64_t cap_blocks = (int64_t)h->cus * kBlocksPerCU;
@@ -402,7 +436,7 @@ int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
         if (pipe_ok) groups = pipe_groups(h, window, groups);
         lp->kind = pipe_ok ? PLAN_PIPE : PLAN_BLOCK;
         lp->drain = pipe_drain(h, window, groups);
-        lp->unbound = window >= h->C;
+        lp->spread = spread_pays(h, window, groups);
         lp->group = kBlockThreads;
         lp->blocks = (int)groups;
         *n_groups = (uint32_t)groups;
@@ -456,10 +490,11 @@ int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
         groups = pipe_groups(h, window, groups);
         lp->kind = PLAN_PIPE;  // segments beyond the slices take its long path
         lp->drain = pipe_drain(h, window, groups);
-        lp->unbound = window >= h->C;
+        lp->spread = spread_pays(h, window, groups);
+        if (lp->drain && h->group == 0) G = wide_group(h, G, groups);
     }
     lp->group = G;
-    lp->blocks = (int)((groups + per_block - 1) / per_block);
+    lp->blocks = (int)((groups * G + kBlockThreads - 1) / kBlockThreads);
     if (lp->kind == PLAN_MIXED) {
         // Each workgroup takes ceil(groups / blocks) positions per batch.
         const int64_t ng = (groups + lp->blocks - 1) / lp->blocks;
@@ -1067,14 +1102,9 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
     a.n_groups = n_groups;
     a.u_bytes = shared_bytes(h) <= kPipeMaxBytes ? (uint32_t)shared_bytes(h) : 0u;
     a.u_shift = h->wide ? 3u : 2u;
-    // With every coordinate in flight (the window does not bind) the pipelined kernel runs on the
-    // spread copy when there is one: packed, the gathers of entries whose 64-byte segment other
-    // coordinates' atomics are updating wait behind those atomics (measured: gather-and-atomic
-    // pairs on 100,000 packed fp32 entries at 9.5 G/s, spread one per 64 bytes at 20 G/s, the rate
-    // of the atomics alone).  With a binding window the epoch is bound by the latency of the
-    // coordinates in flight instead, and a coordinate that gathers many neighbouring entries (a
-    // dense column) would touch one segment per entry instead of one per 16.
-    const bool spread = h->us && h->spread && lp.kind == PLAN_PIPE && lp.unbound && n_epochs > 0;
+    // The pipelined kernel runs on the spread copy where that pays (spread_pays, when the plan was
+    // made) and there is one.
+    const bool spread = h->us && h->spread && lp.kind == PLAN_PIPE && lp.spread && n_epochs > 0;
     if (spread) {
         a.u = h->us;
         a.u_bytes = (uint32_t)(h->L << kSpreadShift);

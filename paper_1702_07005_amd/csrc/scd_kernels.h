@@ -84,7 +84,7 @@ struct LaunchPlan {
     int chunk;          // PLAN_QUEUE, PLAN_SPLIT: consecutive positions (units) per claim
     uint32_t part;      // PLAN_SPLIT: entries per part of a long segment (multiple of 64, <= kSplitMaxPart)
     int wide;           // shared vector stored as double
-    int unbound;        // PLAN_PIPE: the window does not bind (every coordinate may be in flight)
+    int spread;         // PLAN_PIPE: run on the spread copy of the shared vector (when there is one)
     int team;           // PLAN_TEAM: workgroups per in-flight coordinate (K)
     size_t lds_bytes;
 };
