@@ -113,6 +113,7 @@ struct scd_solver {
     void* u = nullptr;  // shared vector: float, or double when `wide`
     int wide = 0;
     uint32_t max_hits = 0;  // most stored entries sharing one shared-vector index
+    unsigned* hits = nullptr;  // [L] stored entries per shared-vector index; during scd_create only
     float* norms = nullptr;
     float* cy = nullptr;  // ridge primal: <y, a_c> per coordinate
     double* cyd = nullptr;  // the same in fp64 (objective evaluation)
@@ -504,17 +505,102 @@ int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
     return SCD_OK;
 }
 
-// Number of entries with at least T hits, and the sum of their hits (synchronises).
-int hot_count(scd_solver* h, const unsigned* hits, unsigned T, unsigned long long* dev2, hipStream_t s,
-              unsigned long long* count, unsigned long long* sum) {
+// Stored entries per shared-vector index: those that scd_create counted, or (after it) counted again
+// into a buffer that the caller frees.
+int need_hits(scd_solver* h, unsigned** hits, bool* owned, hipStream_t s) {
+    *hits = h->hits;
+    *owned = !h->hits;
+    if (h->hits) return SCD_OK;
+    HIP_TRY(hipMalloc(hits, sizeof(unsigned) * (size_t)h->L));
+    hipError_t e = hipMemsetAsync(*hits, 0, sizeof(unsigned) * (size_t)h->L, s);
+    if (e == hipSuccess) e = launch_count_hits(h->idx, h->nnz, *hits, s);
+    if (e == hipSuccess) return SCD_OK;
+    (void)hipFree(*hits);
+    *hits = nullptr;
+    *owned = false;
+    return fail(SCD_ERR_HIP, "count hits: %s", hipGetErrorString(e));
+}
+
+// The smallest T in [1, max_hits + 1] with at most `cap` entries of at least T hits (synchronises).  Each
+// histogram pass narrows T's interval kHitBins times, so two or three passes over hits find it; bins
+// live in h->partials.
+int hits_threshold(scd_solver* h, const unsigned* hits, unsigned cap, unsigned* T, hipStream_t s) {
+    static_assert(sizeof(unsigned) * kHitBins <= sizeof(double) * kObjBlocksMax * 5, "bins fit the partials");
+    unsigned* bins = reinterpret_cast<unsigned*>(h->partials);
+    std::vector<unsigned> n(kHitBins);
+    uint64_t lo = 1, hi = (uint64_t)h->max_hits + 1;  // T in [lo, hi]; `above` entries have at least hi hits
+    uint64_t above = 0;
+    while (lo < hi) {
+        const uint64_t width = (hi - lo + kHitBins - 1) / kHitBins;
+        HIP_TRY(hipMemsetAsync(bins, 0, sizeof(unsigned) * kHitBins, s));
+        HIP_TRY(launch_hits_histogram(hits, h->L, (unsigned)lo, (unsigned)hi, (unsigned)width, bins, s));
+        HIP_TRY(hipMemcpyAsync(n.data(), bins, sizeof(unsigned) * kHitBins, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        int b = (int)((hi - 1 - lo) / width);  // the bin that holds hi - 1
+        while (b >= 0 && above + n[(size_t)b] <= cap) above += n[(size_t)b--];
+        if (b < 0) {
+            hi = lo;  // even all entries of at least lo hits are few enough
+            break;
+        }
+        const uint64_t top = std::min<uint64_t>(hi, lo + (uint64_t)(b + 1) * width);
+        if (width == 1) {
+            lo = hi = top;
+            break;
+        }
+        lo += (uint64_t)b * width;
+        hi = top;
+    }
+    *T = (unsigned)hi;
+    return SCD_OK;
+}
+
+// Entries with at least T hits, and the sum of their hits (synchronises; the two counts in h->sums).
+int hot_count(scd_solver* h, const unsigned* hits, unsigned T, hipStream_t s, unsigned long long* count,
+              unsigned long long* sum) {
     unsigned long long host2[2] = {0, 0};
-    HIP_TRY(hipMemsetAsync(dev2, 0, 2 * sizeof(unsigned long long), s));
+    unsigned long long* dev2 = reinterpret_cast<unsigned long long*>(h->sums);
+    HIP_TRY(hipMemsetAsync(dev2, 0, sizeof host2, s));
     HIP_TRY(launch_hot_count_ge(hits, h->L, T, dev2, s));
     HIP_TRY(hipMemcpyAsync(host2, dev2, sizeof host2, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     *count = host2[0];
     *sum = host2[1];
     return SCD_OK;
+}
+
+// Slots, in index order, of the `count` entries with at least T hits: slot_of[L] (kHotCold for the
+// others) and hot_ids[count], allocated here (synchronises).  On an error neither is left allocated.
+int assign_slots(const scd_solver* h, const unsigned* hits, unsigned T, unsigned long long count, uint16_t** slot_of,
+                 int32_t** hot_ids, hipStream_t s) {
+    const size_t nblk = (size_t)((h->L + kHotAssignBlock - 1) / kHotAssignBlock);
+    unsigned* blocks = nullptr;
+    std::vector<unsigned> base(nblk);
+    *slot_of = nullptr;
+    *hot_ids = nullptr;
+    hipError_t e = hipMalloc(&blocks, sizeof(unsigned) * nblk);
+    if (e == hipSuccess) e = hipMalloc(slot_of, sizeof(uint16_t) * (size_t)h->L);
+    if (e == hipSuccess) e = hipMalloc(hot_ids, sizeof(int32_t) * (size_t)count);
+    if (e == hipSuccess) e = launch_hot_block_count(hits, h->L, T, blocks, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(base.data(), blocks, sizeof(unsigned) * nblk, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) {
+        unsigned run = 0;
+        for (auto& b : base) {
+            const unsigned c = b;
+            b = run;
+            run += c;
+        }
+        e = hipMemcpyAsync(blocks, base.data(), sizeof(unsigned) * nblk, hipMemcpyHostToDevice, s);
+    }
+    if (e == hipSuccess) e = launch_hot_assign(hits, h->L, T, blocks, *slot_of, *hot_ids, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    (void)hipFree(blocks);
+    if (e == hipSuccess) return SCD_OK;
+    (void)hipFree(*slot_of);
+    (void)hipFree(*hot_ids);
+    *slot_of = nullptr;
+    *hot_ids = nullptr;
+    return fail(e == hipErrorOutOfMemory ? SCD_ERR_OOM : SCD_ERR_HIP, "hot slots: %s", hipGetErrorString(e));
 }
 
 // Hot set of the hot-set kernel: the entries with at least T stored entries pointing at them (T
@@ -526,50 +612,21 @@ int build_hot_tables(scd_solver* h, hipStream_t s) {
     const uint32_t cap = hot_capacity(h);
     if (cap == 0 || h->nnz == 0 || h->max_seg > kHotMaxSegment || h->max_hits == 0) return SCD_OK;
     unsigned* hits = nullptr;
-    unsigned long long* dev2 = nullptr;
-    unsigned* blocks = nullptr;
+    bool own_hits = false;
     uint16_t* slot_of = nullptr;  // [L]: slot of each shared-vector entry, kHotCold when not hot
     bool skip = false;
-    const int64_t nblk = (h->L + kHotAssignBlock - 1) / kHotAssignBlock;
-    int rc = SCD_OK;
+    int rc = need_hits(h, &hits, &own_hits, s);
     auto hip = [&](hipError_t e, const char* what) {
         if (rc == SCD_OK && e != hipSuccess)
             rc = fail(e == hipErrorOutOfMemory ? SCD_ERR_OOM : SCD_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
         return rc == SCD_OK;
     };
-    hip(hipMalloc(&hits, sizeof(unsigned) * (size_t)h->L), "hipMalloc(hits)");
-    hip(hipMalloc(&dev2, 2 * sizeof(unsigned long long)), "hipMalloc(counts)");
-    hip(hipMalloc(&blocks, sizeof(unsigned) * (size_t)nblk), "hipMalloc(block counts)");
-    if (rc == SCD_OK) {
-        hip(hipMemsetAsync(hits, 0, sizeof(unsigned) * (size_t)h->L, s), "zero hits");
-        hip(launch_count_hits(h->idx, h->nnz, hits, s), "count hits");
-    }
     // Smallest T in [1, max_hits + 1] with count(hits >= T) <= cap (count at max_hits + 1 is 0).
-    unsigned lo = 1, hi = h->max_hits + 1;
+    unsigned T = 1;
     unsigned long long cnt = 0, sum = 0;
-    while (rc == SCD_OK && lo < hi) {
-        const unsigned mid = lo + (hi - lo) / 2;
-        if (int r = hot_count(h, hits, mid, dev2, s, &cnt, &sum)) rc = r;
-        else if (cnt <= cap) hi = mid;
-        else lo = mid + 1;
-    }
-    if (rc == SCD_OK && (rc = hot_count(h, hits, lo, dev2, s, &cnt, &sum)) == SCD_OK && cnt > 0) {
-        std::vector<unsigned> base((size_t)nblk);
-        hip(launch_hot_block_count(hits, h->L, lo, blocks, s), "hot block counts");
-        hip(hipMemcpyAsync(base.data(), blocks, sizeof(unsigned) * (size_t)nblk, hipMemcpyDeviceToHost, s),
-            "copy block counts");
-        hip(hipStreamSynchronize(s), "synchronize");
-        unsigned run = 0;
-        for (auto& b : base) {
-            const unsigned c = b;
-            b = run;
-            run += c;
-        }
-        hip(hipMemcpyAsync(blocks, base.data(), sizeof(unsigned) * (size_t)nblk, hipMemcpyHostToDevice, s),
-            "copy block bases");
-        hip(hipMalloc(&slot_of, sizeof(uint16_t) * (size_t)h->L), "hipMalloc(slot_of)");
-        hip(hipMalloc(&h->hot_ids, sizeof(int32_t) * (size_t)cnt), "hipMalloc(hot_ids)");
-        hip(launch_hot_assign(hits, h->L, lo, blocks, slot_of, h->hot_ids, s), "hot slots");
+    if (rc == SCD_OK) rc = hits_threshold(h, hits, cap, &T, s);
+    if (rc == SCD_OK) rc = hot_count(h, hits, T, s, &cnt, &sum);
+    if (rc == SCD_OK && cnt > 0 && (rc = assign_slots(h, hits, T, cnt, &slot_of, &h->hot_ids, s)) == SCD_OK) {
         // Each stored entry's key (-1 - hot slot, or its index), which the producers read in place of
         // idx (4 bytes per entry).  Without the memory for it the hot-set kernel is not used.
         if (rc == SCD_OK) {
@@ -609,9 +666,7 @@ int build_hot_tables(scd_solver* h, hipStream_t s) {
             }
         }
     }
-    (void)hipFree(hits);
-    (void)hipFree(dev2);
-    (void)hipFree(blocks);
+    if (own_hits) (void)hipFree(hits);
     (void)hipFree(slot_of);
     if (rc != SCD_OK || skip) {
         (void)hipFree(h->entry_key);
@@ -659,17 +714,17 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
         HIP_TRY(hipMalloc(&h->team_slots, sb));
         HIP_TRY(hipMemsetAsync(h->team_slots, 0, sb, s));
     }
-    unsigned* hits = nullptr;
+    unsigned* hits = h->hits;
     // Without memory for the tables the other kernels run instead: an allocation that fails here
     // (after the check above, e.g. by fragmentation) is not an error of the calling function.
-    const bool got = hipMalloc(&hits, sizeof(unsigned) * (size_t)h->L) == hipSuccess &&
+    const bool got = (hits || hipMalloc(&hits, sizeof(unsigned) * (size_t)h->L) == hipSuccess) &&
                      hipMalloc(&h->team_idx, sizeof(int32_t) * nnz1) == hipSuccess &&
                      hipMalloc(&h->team_val, sizeof(float) * nnz1) == hipSuccess &&
                      hipMalloc(&h->team_off, sizeof(uint32_t) * (size_t)h->C * (K + 1)) == hipSuccess &&
                      hipMalloc(&h->team_bound, sizeof(uint32_t) * (K + 1)) == hipSuccess;
     if (!got) {
         (void)hipGetLastError();  // clear the allocation failure
-        (void)hipFree(hits);
+        if (hits != h->hits) (void)hipFree(hits);
         free_team_tables(h);
         return SCD_OK;
     }
@@ -679,8 +734,10 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
     };
     std::vector<unsigned> hh;
     if (rc == SCD_OK) {
-        hip(hipMemsetAsync(hits, 0, sizeof(unsigned) * (size_t)h->L, s), "zero team hits");
-        if (h->nnz > 0) hip(launch_count_hits(h->idx, h->nnz, hits, s), "count hits");
+        if (hits != h->hits) {
+            hip(hipMemsetAsync(hits, 0, sizeof(unsigned) * (size_t)h->L, s), "zero team hits");
+            hip(launch_count_hits(h->idx, h->nnz, hits, s), "count hits");
+        }
         hh.resize((size_t)h->L);
         hip(hipMemcpyAsync(hh.data(), hits, sizeof(unsigned) * (size_t)h->L, hipMemcpyDeviceToHost, s), "copy hits");
         hip(hipStreamSynchronize(s), "synchronize");
@@ -703,7 +760,7 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
             "team partition");
         hip(hipStreamSynchronize(s), "synchronize");
     }
-    (void)hipFree(hits);
+    if (hits != h->hits) (void)hipFree(hits);
     if (rc != SCD_OK) {
         free_team_tables(h);
         return rc;
@@ -785,6 +842,98 @@ int obj_group(const scd_solver* h) {
 
 int obj_blocks(const scd_solver* h, int G) { return objective_blocks(h->C, G); }
 
+// The coupling probe: |A~ 1|^2, the sum of G's diagonal, the non-empty coordinates, and the largest
+// coordinate's kappa estimate (kProbes Rademacher probes).  All probes share one pass over the matrix
+// where memory for a row of kProbeRow values per shared-vector entry is free; otherwise each has its
+// own, with h->u as the probe vector.  Synchronises; h->u and h->model are scratch here.
+int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* diag1, double* cn, float* kmax) {
+    static_assert(kProbes % kProbeRow == 0, "whole passes");
+    ProbeArgs a{};
+    a.ptr = h->ptr;
+    a.idx = h->idx;
+    a.val = h->val;
+    a.norms = h->norms;
+    a.sign = h->form == FORM_SVM_DUAL ? h->y : nullptr;
+    a.C = (uint32_t)h->C;
+    a.mu = h->form == FORM_SVM_DUAL ? 0.0f : (float)(h->lambda * (double)h->n_rows);
+    a.inv_probes = 1.0f / (float)kProbes;
+    // The most used entries, summed in LDS.
+    uint16_t* slot_of = nullptr;
+    int32_t* hot_ids = nullptr;
+    const unsigned fit = (unsigned)std::min<size_t>(kProbeSlots, h->max_lds / (sizeof(float) * (kProbeRow + 1)));
+    if (h->hits && h->max_hits >= kProbeMinHits && fit > 0) {
+        unsigned T = 0;
+        unsigned long long cnt = 0, sum = 0;
+        if (int r = hits_threshold(h, h->hits, fit, &T, s)) return r;
+        T = std::max(T, kProbeMinHits);
+        if (int r = hot_count(h, h->hits, T, s, &cnt, &sum)) return r;
+        if (cnt > 0) {
+            if (int r = assign_slots(h, h->hits, T, cnt, &slot_of, &hot_ids, s)) {
+                if (r != SCD_ERR_OOM) return r;
+                (void)hipGetLastError();  // without the memory every add goes to the vector
+            } else {
+                a.slot_of = slot_of;
+                a.hot_ids = hot_ids;
+                a.n_hot = (uint32_t)cnt;
+            }
+        }
+    }
+    float* rows = nullptr;
+    if (hipMalloc(&rows, sizeof(float) * kProbeRow * (size_t)h->L) != hipSuccess) {
+        (void)hipGetLastError();
+        rows = nullptr;
+    }
+    int rc = SCD_OK;
+    auto hip = [&](hipError_t e, const char* what) {
+        if (rc == SCD_OK && e != hipSuccess)
+            rc = fail(e == hipErrorOutOfMemory ? SCD_ERR_OOM : SCD_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+    };
+    const int blocks = obj_blocks(h, G);
+    const size_t vec = sizeof(float) * (size_t)h->L;
+    unsigned bits = 0;
+    unsigned* dev_bits = reinterpret_cast<unsigned*>(h->flags);
+    hip(hipMemsetAsync(dev_bits, 0, sizeof(unsigned), s), "zero kappa");
+    hip(hipMemsetAsync(h->u, 0, vec, s), "zero probe vector");
+    if (rows) {
+        a.first = 1;
+        a.T0 = static_cast<float*>(h->u);
+        a.T = rows;
+        a.max_bits = dev_bits;
+        hip(hipMemsetAsync(rows, 0, vec * kProbeRow, s), "zero probe rows");
+        if (rc == SCD_OK) hip(launch_probe_scatter(a, kProbeRow, G, h->cus, s), "probe scatter");
+        if (rc == SCD_OK) hip(launch_probe_gather(a, kProbeRow, G, blocks, s), "probe gather");
+    } else {
+        a.T = static_cast<float*>(h->u);
+        a.first = 0;
+        hip(hipMemsetAsync(h->model, 0, sizeof(float) * (size_t)h->C, s), "zero probe sums");
+        if (rc == SCD_OK) hip(launch_probe_scatter(a, 1, G, h->cus, s), "probe scatter");
+    }
+    if (rc == SCD_OK)
+        hip(launch_probe_totals(static_cast<const float*>(h->u), h->L, h->norms, (uint32_t)h->C, a.mu, blocks,
+                                h->partials, h->sums, s),
+            "probe totals");
+    hip(hipMemcpyAsync(h->host_sums, h->sums, 3 * sizeof(double), hipMemcpyDeviceToHost, s), "copy probe");
+    for (int p = 1; !rows && p <= kProbes && rc == SCD_OK; ++p) {
+        a.first = (uint32_t)p;
+        a.K = h->model;
+        a.max_bits = p == kProbes ? dev_bits : nullptr;
+        hip(hipMemsetAsync(h->u, 0, vec, s), "zero probe vector");
+        if (rc == SCD_OK) hip(launch_probe_scatter(a, 1, G, h->cus, s), "probe scatter");
+        if (rc == SCD_OK) hip(launch_probe_gather(a, 1, G, blocks, s), "probe gather");
+    }
+    hip(hipMemcpyAsync(&bits, dev_bits, sizeof bits, hipMemcpyDeviceToHost, s), "copy kappa");
+    hip(hipStreamSynchronize(s), "synchronize");
+    (void)hipFree(rows);
+    (void)hipFree(slot_of);
+    (void)hipFree(hot_ids);
+    if (rc != SCD_OK) return rc;
+    *coh2 = h->host_sums[0];
+    *diag1 = h->host_sums[1];
+    *cn = h->host_sums[2];
+    memcpy(kmax, &bits, sizeof bits);
+    return SCD_OK;
+}
+
 int check_handle(scd_handle_t h) {
     if (!h) return fail(SCD_ERR_INVALID, "null handle");
     return SCD_OK;
@@ -799,6 +948,7 @@ int set_device(const scd_solver* h) {
 
 void release(scd_solver* h) {
     if (!h) return;
+    (void)hipFree(h->hits);
     (void)hipFree(h->model);
     (void)hipFree(h->u);
     (void)hipFree(h->norms);
@@ -980,11 +1130,18 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         else step(fail(SCD_ERR_NUMERIC, "non-finite matrix value or label"));
     }
     if (rc == SCD_OK) {
-        // Largest number of updates one shared-vector entry receives per epoch (h->u as counters).
-        unsigned* hits = static_cast<unsigned*>(h->u);
+        // Updates of each shared-vector entry per epoch, and their largest.  They are kept until the end
+        // of this call for the tables that need them; without the memory (h->u as counters) they are
+        // counted again there.
+        if (hipMalloc(&h->hits, sizeof(unsigned) * (size_t)h->L) != hipSuccess) {
+            (void)hipGetLastError();
+            h->hits = nullptr;
+        }
+        unsigned* hits = h->hits ? h->hits : static_cast<unsigned*>(h->u);
         hip(hipMemsetAsync(hits, 0, sizeof(unsigned) * (size_t)h->L, s), "zero hits");
         hip(hipMemsetAsync(h->flags, 0, sizeof(unsigned), s), "zero max hits");
-        hip(launch_max_hits(h->idx, h->nnz, h->L, hits, reinterpret_cast<unsigned*>(h->flags), s), "count hits");
+        hip(launch_count_hits(h->idx, h->nnz, hits, s), "count hits");
+        hip(launch_max_hits(hits, h->L, reinterpret_cast<unsigned*>(h->flags), s), "largest hits");
         hip(hipMemcpyAsync(&h->max_hits, h->flags, sizeof(unsigned), hipMemcpyDeviceToHost, s), "copy hits");
         hip(hipStreamSynchronize(s), "synchronize");
         if (rc == SCD_OK && h->max_hits > kWideHits) {
@@ -999,36 +1156,11 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         hip(launch_norms(h->ptr, h->idx, h->val, formulation == SCD_RIDGE_PRIMAL ? h->y : nullptr, (uint32_t)h->C,
                          G, obj_blocks(h, G), h->norms, h->cy, h->cyd, s),
             "norms");
-        // Coupling of the coordinates (sets the default window), using h->u as the probe vector.
-        const float mu = formulation == SCD_SVM_DUAL ? 0.0f : (float)(lambda * (double)h->n_rows);
-        const float* sign = formulation == SCD_SVM_DUAL ? h->y : nullptr;
-        // Probe 0 (all-ones): sum of G's entries, sum of its diagonal, non-empty coordinates.
-        // Probes 1..kProbes (Rademacher): per-coordinate squared off-diagonal row mass into K = h->model.
+        // Coupling of the coordinates: sets the default window.
         double coh2 = 0.0, diag1 = 0.0, cn = 0.0;
-        hip(hipMemsetAsync(h->model, 0, sizeof(float) * (size_t)h->C, s), "zero probe sums");  // K[c]
-        for (uint32_t probe = 0; probe <= (uint32_t)kProbes && rc == SCD_OK; ++probe) {
-            hip(launch_probe(h->ptr, h->idx, h->val, h->norms, sign, (uint32_t)h->C, h->L, mu, probe, G,
-                             obj_blocks(h, G), static_cast<float*>(h->u), h->model, h->partials, h->sums, s),
-                "coupling probe");
-            hip(hipMemcpyAsync(h->host_sums, h->sums, 4 * sizeof(double), hipMemcpyDeviceToHost, s), "copy probe");
-            hip(hipStreamSynchronize(s), "synchronize");
-            if (rc != SCD_OK) break;
-            if (probe == 0) {
-                coh2 = h->host_sums[0];
-                diag1 = h->host_sums[2];
-                cn = h->host_sums[3];
-            }
-        }
-        unsigned kmax_bits = 0;
-        hip(hipMemsetAsync(h->flags, 0, sizeof(unsigned), s), "zero kappa");
-        hip(launch_kappa_max(h->model, h->norms, (uint32_t)h->C, kProbes, obj_blocks(h, G),
-                             reinterpret_cast<unsigned*>(h->flags), s),
-            "kappa max");
-        hip(hipMemcpyAsync(&kmax_bits, h->flags, sizeof(unsigned), hipMemcpyDeviceToHost, s), "copy kappa");
-        hip(hipStreamSynchronize(s), "synchronize");
+        float kmax = 0.0f;
+        if (rc == SCD_OK) step(probe_coupling(h, G, s, &coh2, &diag1, &cn, &kmax));
         if (rc == SCD_OK) {
-            float kmax = 0.0f;
-            memcpy(&kmax, &kmax_bits, sizeof kmax);
             const double pairs = cn * (cn - 1.0);
             h->coherence = pairs > 0.0 ? (coh2 - diag1) / pairs : 0.0;
             // Worst coordinate's mean squared coupling to one other coordinate.
@@ -1042,6 +1174,8 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         if (rc == SCD_OK) step(hot_if_needed(h, s));
         if (rc == SCD_OK) step(team_if_needed(h, s));
         if (rc == SCD_OK) step(split_if_needed(h, s));
+        (void)hipFree(h->hits);
+        h->hits = nullptr;
         hip(hipMemsetAsync(h->model, 0, sizeof(float) * (size_t)h->C, s), "zero model");
         hip(hipMemsetAsync(h->u, 0, (h->wide ? sizeof(double) : sizeof(float)) * (size_t)h->L, s), "zero shared");
         hip(hipStreamSynchronize(s), "synchronize");

@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(256) void k_hot_assign(const unsigned* __restrict__
 }
 
 hipError_t launch_hot_count_ge(const unsigned* hits, int64_t L, unsigned T, unsigned long long* out2, hipStream_t s) {
-    hipLaunchKernelGGL(k_hot_count_ge, dim3(grid_for(L)), dim3(256), 0, s, hits, L, T, out2);
+    hipLaunchKernelGGL(k_hot_count_ge, dim3(std::min(grid_for(L), 512u)), dim3(256), 0, s, hits, L, T, out2);
     return hipGetLastError();
 }
 

@@ -350,8 +350,14 @@ hipError_t launch_epoch(int form, const EpochArgs& a, const LaunchPlan& lp, hipS
 hipError_t ordered_lds_prepare(int form, bool wide, size_t lds_bytes);
 hipError_t launch_convert_f32_to_f64(const float* in, int64_t n, double* out, hipStream_t s);
 hipError_t launch_convert_f64_to_f32(const double* in, int64_t n, float* out, hipStream_t s);
-hipError_t launch_max_hits(const int32_t* idx, int64_t nnz, int64_t L, unsigned* hits, unsigned* out, hipStream_t s);
+// Set-up statistics.  hits[i] += stored entries with index i; their largest into out[0]; the histogram
+// adds to bins[b] the entries with hits in [lo + b width, lo + (b + 1) width) and below hi, where
+// kHitBins bins of that width reach hi.
+constexpr int kHitBins = 2048;
 hipError_t launch_count_hits(const int32_t* idx, int64_t nnz, unsigned* hits, hipStream_t s);
+hipError_t launch_max_hits(const unsigned* hits, int64_t L, unsigned* out, hipStream_t s);
+hipError_t launch_hits_histogram(const unsigned* hits, int64_t L, unsigned lo, unsigned hi, unsigned width,
+                                 unsigned* bins, hipStream_t s);
 hipError_t launch_hot_entry_keys(const int32_t* idx, int64_t nnz, const uint16_t* slot_of, int32_t* entry_key,
                                   hipStream_t s);
 hipError_t launch_perm_fill(const PermKeys& p, int32_t* out, hipStream_t s);
@@ -363,11 +369,35 @@ hipError_t launch_norms(const int64_t* ptr, const int32_t* idx, const float* val
                         int blocks, float* out, float* cy, double* cyd, hipStream_t s);
 hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, const float* val, int64_t nnz,
                            int64_t bound, const float* y, int64_t ny, int pm1, int* flags, hipStream_t s);
-hipError_t launch_probe(const int64_t* ptr, const int32_t* idx, const float* val, const float* norms,
-                        const float* sign, uint32_t C, int64_t L, float mu, uint32_t probe, int G, int blocks,
-                        float* T, float* K, double* partials, double* out, hipStream_t s);
-hipError_t launch_kappa_max(const float* K, const float* norms, uint32_t C, int probes, int blocks, unsigned* out,
-                            hipStream_t s);
+// Coupling probe: kProbeRow probes in one pass, or one (np).  At most kProbeSlots of the most used
+// shared-vector entries, of at least kProbeMinHits, are summed in LDS (kProbeRow + 1 sums each).
+constexpr int kProbeRow = 8;
+constexpr unsigned kProbeSlots = 4000;
+constexpr unsigned kProbeMinHits = 2048;
+struct ProbeArgs {
+    const int64_t* ptr;
+    const int32_t* idx;
+    const float* val;
+    const float* norms;
+    const float* sign;        // labels (SVM) or null
+    uint32_t C;
+    float mu;
+    uint32_t first;           // first probe of the pass
+    const uint16_t* slot_of;  // [L]: LDS slot or kHotCold (when n_hot > 0)
+    const int32_t* hot_ids;   // [n_hot]
+    uint32_t n_hot;
+    float* T0;                // np = kProbeRow: probe 0's vector [L]
+    float* T;                 // [L][np]
+    float* K;                 // np = 1: per-coordinate sums over the probes so far
+    float inv_probes;
+    unsigned* max_bits;       // gather: largest mean (float bits), null before the last pass
+};
+hipError_t launch_probe_scatter(const ProbeArgs& a, int np, int G, int cus, hipStream_t s);
+hipError_t launch_probe_gather(const ProbeArgs& a, int np, int G, int blocks, hipStream_t s);
+// out[0..2] = |T0|^2, sum of G_cc, non-empty coordinates.
+hipError_t launch_probe_totals(const float* T0, int64_t L, const float* norms, uint32_t C, float mu, int blocks,
+                               double* partials, double* out, hipStream_t s);
+hipError_t launch_sum_partials(const double* partials, int nparts, int width, double* out, hipStream_t s);
 // One objective evaluation: k_objective (partials[blocks][5]) and k_sum_partials (sums[0..4]).  With
 // o.cyd null the ridge primal gathers y beside the shared vector.
 hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, double* partials, double* sums,

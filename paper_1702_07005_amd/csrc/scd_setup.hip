@@ -1,6 +1,8 @@
 // scd_setup.hip -- set-up and evaluation kernels for gfx950: the permutation array, the frozen
 // gather-dot, squared norms (and <y, a_c>), input validation, the objective / duality-gap
-// reductions, the coupling probe, precision conversions and per-entry hit counts.
+// reductions and precision conversions.
+#include <algorithm>
+
 #include "scd_device.h"
 
 namespace scd {
@@ -61,13 +63,22 @@ __global__ __launch_bounds__(256) void k_norms(const int64_t* __restrict__ ptr, 
 // flags bits: 1 ptr not monotone / wrong ends, 2 index out of range, 4 non-finite value,
 // 8 non-finite label, 16 label not +-1.
 // flags[1] (as unsigned long long) receives the longest segment.
-__global__ void k_validate_ptr(const int64_t* __restrict__ ptr, uint32_t S, int64_t nnz, int* flags) {
-    uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c == 0 && (ptr[0] != 0 || ptr[S] != nnz)) atomicOr(flags, 1);
-    if (c < S) {
+__global__ __launch_bounds__(256) void k_validate_ptr(const int64_t* __restrict__ ptr, uint32_t S, int64_t nnz, int* flags) {
+    __shared__ unsigned long long red[4];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (ptr[0] != 0 || ptr[S] != nnz)) atomicOr(flags, 1);
+    unsigned long long longest = 0;
+    for (uint64_t c = (uint64_t)blockIdx.x * 256u + threadIdx.x; c < S; c += (uint64_t)gridDim.x * 256u) {
         const int64_t len = ptr[c + 1] - ptr[c];
         if (len < 0) atomicOr(flags, 1);
-        else atomicMax(reinterpret_cast<unsigned long long*>(flags) + 1, (unsigned long long)len);
+        else longest = max(longest, (unsigned long long)len);
+    }
+    // One atomic per workgroup: one per segment, all on one address, took 0.9 ms for 5 M segments.
+    for (int o = 32; o > 0; o >>= 1) longest = max(longest, (unsigned long long)__shfl_xor(longest, o, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = longest;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        longest = max(max(red[0], red[1]), max(red[2], red[3]));
+        if (longest) atomicMax(reinterpret_cast<unsigned long long*>(flags) + 1, longest);
     }
 }
 
@@ -194,89 +205,6 @@ __global__ __launch_bounds__(256) void k_objective(ObjArgs o, double* __restrict
     block_reduce_store<NS>(t, partials + (size_t)blockIdx.x * NS);
 }
 
-// ----------------------------------------------------------------------------------------
-// Coupling probe (set-up only).  With a~_c = sigma_c a_c / sqrt(|a_c|^2 + mu) (sigma_c = the
-// label for the SVM, 1 otherwise; mu = lambda N for the ridge steps, 0 for the SVM step),
-// G = A~^T A~ holds the step-normalised couplings between coordinates.  A probe with
-// Rademacher signs z_c scatters T = A~ z; the gather pass forms (A~^T T)_c - G_cc z_c, the
-// off-diagonal part of (G z)_c, whose square has expectation kappa_c = sum_{j != c} G_cj^2
-// (Hutchinson), accumulated per coordinate in K.  z = 1 (probe 0) gives the coherent sum
-// |A~ 1|^2 instead (vector pass).
-// ----------------------------------------------------------------------------------------
-__device__ __forceinline__ float probe_sign(uint32_t c, uint32_t probe) {
-    if (probe == 0) return 1.0f;
-    return (murmur_fmix32(c ^ (probe * 0x9E3779B9u)) & 1u) ? 1.0f : -1.0f;
-}
-
-template <int G>
-__global__ __launch_bounds__(256) void k_probe_scatter(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
-                                                       const float* __restrict__ val, const float* __restrict__ norms,
-                                                       const float* __restrict__ sign, uint32_t C, float mu,
-                                                       uint32_t probe, float* __restrict__ T) {
-    const int lane = threadIdx.x & (G - 1);
-    const uint32_t ngroups = gridDim.x * (256u / G);
-    for (uint32_t c = (blockIdx.x * 256u + threadIdx.x) / G; c < C; c += ngroups) {
-        const float sc = norms[c];
-        if (!(sc > 0.0f)) continue;
-        const float coef = probe_sign(c, probe) * (sign ? sign[c] : 1.0f) * rsqrtf(sc + mu);
-        for (int64_t k = ptr[c] + lane; k < ptr[c + 1]; k += G) atomic_add_u(T + idx[k], coef * val[k]);
-    }
-}
-
-template <int G>
-__global__ __launch_bounds__(256) void k_probe_gather(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
-                                                      const float* __restrict__ val, const float* __restrict__ norms,
-                                                      const float* __restrict__ sign, const float* __restrict__ T,
-                                                      uint32_t C, float mu, uint32_t probe, float* __restrict__ K,
-                                                      double* __restrict__ partials) {
-    const int lane = threadIdx.x & (G - 1);
-    const uint32_t ngroups = gridDim.x * (256u / G);
-    double t[4] = {0.0, 0.0, 0.0, 0.0};  // |G z|^2, sum G_cc^2, sum G_cc, non-empty coordinates
-    for (uint32_t c = (blockIdx.x * 256u + threadIdx.x) / G; c < C; c += ngroups) {
-        const float sc = norms[c];
-        if (!(sc > 0.0f)) continue;
-        double d = 0.0;
-        for (int64_t k = ptr[c] + lane; k < ptr[c + 1]; k += G) d += (double)val[k] * (double)T[idx[k]];
-        d = group_sum_f64<G>(d);
-        if (lane == 0) {
-            const double scale = (sign ? (double)sign[c] : 1.0) / sqrt((double)sc + (double)mu);
-            const double diag = (double)sc / ((double)sc + (double)mu);
-            // Off-diagonal part of (G z)_c: its square has expectation sum_{j != c} G_cj^2.
-            const double g = d * scale - diag * (double)probe_sign(c, probe);
-            t[0] += g * g;
-            t[1] += diag * diag;
-            t[2] += diag;
-            t[3] += 1.0;
-            if (K) K[c] += (float)(g * g);  // summed over probes
-        }
-    }
-    block_reduce_store<4>(t, partials + (size_t)blockIdx.x * 4);
-}
-
-// Largest per-coordinate off-diagonal row mass kappa_c = sum_{j != c} G_cj^2, from the probe
-// sums K[c] over `probes` Rademacher probes.  Non-negative floats order like their bit patterns.
-__global__ __launch_bounds__(256) void k_kappa_max(const float* __restrict__ K, const float* __restrict__ norms,
-                                                   uint32_t C, float inv_probes, unsigned* __restrict__ out) {
-    float best = 0.0f;
-    for (uint32_t c = blockIdx.x * 256u + threadIdx.x; c < C; c += gridDim.x * 256u) {
-        const float sc = norms[c];
-        if (!(sc > 0.0f)) continue;
-        best = fmaxf(best, K[c] * inv_probes);
-    }
-    for (int o = 32; o > 0; o >>= 1) best = fmaxf(best, __shfl_xor(best, o, 64));
-    if ((threadIdx.x & 63) == 0 && best > 0.0f) atomicMax(out, __float_as_uint(best));
-}
-
-__global__ __launch_bounds__(256) void k_sumsq(const float* __restrict__ T, int64_t L, double* __restrict__ partials) {
-    double t[1] = {0.0};
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
-        const double x = T[i];
-        t[0] += x * x;
-    }
-    block_reduce_store<1>(t, partials + blockIdx.x);
-}
-
-// Sum `nparts` rows of `width` doubles in index order (one workgroup; deterministic).
 // Sums `width` (at most kSumWidthMax) columns of `partials` [nparts][width] in one workgroup, in an
 // order fixed by nparts alone (so the result does not depend on timing): thread t adds rows t,
 // t + 256, ... in turn, each wave combines its lanes by an xor butterfly, and thread 0 adds the
@@ -321,6 +249,12 @@ __global__ __launch_bounds__(256) void k_spread(U* __restrict__ packed, U* __res
     }
 }
 
+hipError_t launch_sum_partials(const double* partials, int nparts, int width, double* out, hipStream_t s) {
+    if (width > kSumWidthMax) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, partials, nparts, width, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_spread(void* packed, void* spread, int64_t L, bool wide, bool to_spread, hipStream_t s) {
     if (wide)
         hipLaunchKernelGGL(k_spread<double>, dim3(grid_for(L)), dim3(256), 0, s, static_cast<double*>(packed),
@@ -363,7 +297,7 @@ hipError_t launch_norms(const int64_t* ptr, const int32_t* idx, const float* val
 
 hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, const float* val, int64_t nnz,
                            int64_t bound, const float* y, int64_t ny, int pm1, int* flags, hipStream_t s) {
-    hipLaunchKernelGGL(k_validate_ptr, dim3((S + 256) / 256), dim3(256), 0, s, ptr, S, nnz, flags);
+    hipLaunchKernelGGL(k_validate_ptr, dim3(std::min<uint32_t>(1024, (S + 255u) / 256u)), dim3(256), 0, s, ptr, S, nnz, flags);
     if (nnz > 0) {
         int64_t b = (nnz + 255) / 256;
         if (b > 8192) b = 8192;
@@ -434,60 +368,12 @@ hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, doubl
     return hipGetLastError();
 }
 
-// out[0] = |G z|^2 (probe > 0) or |A~ 1|^2 (probe 0), out[1] = sum G_cc^2, out[2] = sum G_cc,
-// out[3] = non-empty coordinates.
-hipError_t launch_probe(const int64_t* ptr, const int32_t* idx, const float* val, const float* norms,
-                        const float* sign, uint32_t C, int64_t L, float mu, uint32_t probe, int G, int blocks,
-                        float* T, float* K, double* partials, double* out, hipStream_t s) {
-    hipError_t e = hipMemsetAsync(T, 0, sizeof(float) * (size_t)L, s);
-    if (e != hipSuccess) return e;
-#define SCD_PROBE(GW)                                                                                          \
-    hipLaunchKernelGGL(k_probe_scatter<GW>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, norms, sign, C, mu, \
-                       probe, T);                                                                              \
-    hipLaunchKernelGGL(k_probe_gather<GW>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, norms, sign, T, C,   \
-                       mu, probe, probe ? K : nullptr, partials)
-    switch (G) {
-        case 4: SCD_PROBE(4); break;
-        case 8: SCD_PROBE(8); break;
-        case 16: SCD_PROBE(16); break;
-        case 32: SCD_PROBE(32); break;
-        default: SCD_PROBE(64); break;
-    }
-#undef SCD_PROBE
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, partials, blocks, 4, out);
-    if (probe == 0) {
-        hipLaunchKernelGGL(k_sumsq, dim3(blocks), dim3(256), 0, s, T, L, partials);
-        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, partials, blocks, 1, out);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_kappa_max(const float* K, const float* norms, uint32_t C, int probes, int blocks, unsigned* out,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_kappa_max, dim3(blocks), dim3(256), 0, s, K, norms, C, 1.0f / (float)probes, out);
-    return hipGetLastError();
-}
-
 // ----------------------------------------------------------------------------------------
-// Storage-width conversions of the shared vector and the per-entry update count.
+// Storage-width conversions of the shared vector.
 // ----------------------------------------------------------------------------------------
 template <typename A, typename B>
 __global__ __launch_bounds__(256) void k_convert(const A* __restrict__ in, int64_t n, B* __restrict__ out) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = (B)in[i];
-}
-
-// hits[i] = number of stored entries with index i (one atomic per entry); max into out[0].
-__global__ __launch_bounds__(256) void k_count_hits(const int32_t* __restrict__ idx, int64_t nnz,
-                                                    unsigned* __restrict__ hits) {
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < nnz; k += (int64_t)gridDim.x * 256)
-        atomicAdd(hits + idx[k], 1u);
-}
-
-__global__ __launch_bounds__(256) void k_max_u32(const unsigned* __restrict__ v, int64_t n, unsigned* __restrict__ out) {
-    unsigned best = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) best = max(best, v[i]);
-    for (int o = 32; o > 0; o >>= 1) best = max(best, (unsigned)__shfl_xor((int)best, o, 64));
-    if ((threadIdx.x & 63) == 0 && best) atomicMax(out, best);
 }
 
 hipError_t launch_convert_f32_to_f64(const float* in, int64_t n, double* out, hipStream_t s) {
@@ -497,18 +383,6 @@ hipError_t launch_convert_f32_to_f64(const float* in, int64_t n, double* out, hi
 
 hipError_t launch_convert_f64_to_f32(const double* in, int64_t n, float* out, hipStream_t s) {
     hipLaunchKernelGGL((k_convert<double, float>), dim3(grid_for(n)), dim3(256), 0, s, in, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_max_hits(const int32_t* idx, int64_t nnz, int64_t L, unsigned* hits, unsigned* out, hipStream_t s) {
-    if (nnz > 0) hipLaunchKernelGGL(k_count_hits, dim3(grid_for(nnz)), dim3(256), 0, s, idx, nnz, hits);
-    hipLaunchKernelGGL(k_max_u32, dim3(grid_for(L)), dim3(256), 0, s, hits, L, out);
-    return hipGetLastError();
-}
-
-
-hipError_t launch_count_hits(const int32_t* idx, int64_t nnz, unsigned* hits, hipStream_t s) {
-    if (nnz > 0) hipLaunchKernelGGL(k_count_hits, dim3(grid_for(nnz)), dim3(256), 0, s, idx, nnz, hits);
     return hipGetLastError();
 }
 

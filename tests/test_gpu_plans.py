@@ -87,3 +87,87 @@ def test_wide_groups_with_segments_of_every_length():
     gm = f64(s.get_state()[0])
     assert gm[0] == 0.0 and gm[9] == 0.0 and np.all(gm[1:9] != 0.0)
     s.close()
+
+
+# ------------------------------------------------------------- set-up statistics
+
+def probe_signs(c, probe):
+    """Rademacher sign of coordinate c in a probe (MurmurHash3 finaliser of c xor probe * golden ratio)."""
+    x = (c ^ ((probe * 0x9E3779B9) & 0xFFFFFFFF)) & 0xFFFFFFFF
+    x = x.astype(np.uint64)
+    for shift, mul in ((16, 0x85EBCA6B), (13, 0xC2B2AE35), (16, None)):
+        x ^= x >> np.uint64(shift)
+        if mul is not None:
+            x = (x * np.uint64(mul)) & np.uint64(0xFFFFFFFF)
+    return np.where(x & np.uint64(1), 1.0, -1.0)
+
+
+def reference_coupling(p):
+    """(coupling, coherence) of scd_info_t in fp64 from their definition, with the library's probes."""
+    seg = np.repeat(np.arange(p.C), np.diff(p.ptr))
+    val = p.val.astype(np.float64)
+    norms = np.bincount(seg, val * val, p.C)
+    mu = 0.0 if p.form == "svm_dual" else p.lam * p.n_rows
+    full = norms > 0
+    scale = np.where(full, (p.y if p.form == "svm_dual" else 1.0) / np.sqrt(np.where(full, norms + mu, 1.0)), 0.0)
+    diag = np.where(full, norms / np.where(full, norms + mu, 1.0), 0.0)
+    a = val * scale[seg]
+    ones = np.bincount(p.idx, a, p.L)
+    n = full.sum()
+    K = np.zeros(p.C)
+    for probe in range(1, 9):
+        z = probe_signs(np.arange(p.C, dtype=np.int64), probe)
+        T = np.bincount(p.idx, a * z[seg], p.L)
+        K += np.where(full, (np.bincount(seg, a * T[p.idx], p.C) - diag * z) ** 2, 0.0)
+    return K.max() / 8 / (n - 1), (ones @ ones - diag.sum()) / (n * (n - 1))
+
+
+@pytest.mark.parametrize("case", ["dense", "sparse", "dual", "text", "terms", "click", "click_hot"])
+def test_coupling_estimate(case):
+    # click_hot: entries beyond the 2,048 hits from which the probe sums them in LDS.
+    p = {"dense": lambda: synth.make("dense_ridge"),
+         "sparse": lambda: synth.make("sparse_ridge", n_rows=3_000, n_cols=2_001, density=3e-3),
+         "dual": lambda: synth.as_ridge_dual(synth.make("sparse_ridge", n_rows=3_000, n_cols=2_001, density=3e-3)),
+         "text": lambda: synth.make("text_svm", n_rows=700, n_cols=30_011, row_nnz=211),
+         "terms": lambda: synth.make("text_ridge_csc", n_rows=5_003, n_cols=30_011, row_nnz=97),
+         "click": lambda: synth.make("click_svm", n_rows=9_001, n_cols=20_011),
+         "click_hot": lambda: synth.make("click_svm", n_rows=60_001, n_cols=70_001)}[case]()
+    s = scd.solver_for(p)
+    info = s.info()
+    hits = np.bincount(p.idx, minlength=p.L)
+    print(f"{case}: coupling {info['coupling']:.6e} max hits {info['max_hits']}", flush=True)
+    assert info["max_hits"] == hits.max()
+    assert (hits.max() >= 2048) or case != "click_hot"
+    coupling, coherence = reference_coupling(p)
+    # fp32 sums of up to `hits` terms, then a sum over the segment: a few 1e-6 of either
+    assert abs(info["coupling"] - coupling) <= 2e-5 * coupling
+    assert abs(info["coherence"] - coherence) <= 2e-5 * max(abs(coherence), coupling)
+    if info["hot_entries"]:
+        # the most used entries, cut where the count of hits changes
+        order = np.sort(hits)[::-1]
+        n = info["hot_entries"]
+        assert order[n - 1] >= 1 and (n == p.L or order[n] < order[n - 1])
+    s.close()
+
+
+def test_coupling_estimate_without_memory_for_the_rows():
+    # L so large that the probe's rows (32 bytes per shared-vector entry) do not fit what is left of
+    # the GPU's memory: one probe at a time, with the same result.
+    rng = np.random.default_rng(6)
+    n, L, per = 2_000, 150_000_000, 20
+    idx = np.sort(rng.integers(0, 300, (n, per)) * (L // 300) + np.arange(per), axis=1).astype(np.int32)
+    p = synth.Problem("wide", "ridge_dual", "csr", n, L, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
+                      rng.standard_normal(n * per).astype(np.float32), np.ones(n, dtype=np.float32), 1e-3, 0)
+    coupling, coherence = reference_coupling(p)
+    got = []
+    for leave in (None, 4 << 30):  # 4.8 GB of rows, 1.2 GB for everything else
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        hold = torch.empty(free - leave, dtype=torch.uint8, device="cuda") if leave else None
+        s = scd.solver_for(p)
+        got.append((s.info()["coupling"], s.info()["coherence"]))
+        s.close()
+        del hold
+    torch.cuda.empty_cache()
+    for c, h in got:
+        assert abs(c - coupling) <= 2e-5 * coupling and abs(h - coherence) <= 2e-5 * max(abs(coherence), coupling)
