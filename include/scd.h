@@ -245,7 +245,9 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *   "hot"         1 (default) = with at most 16 coordinates in flight, segments of at most 64
  *                 entries and "group" 0, run the epoch in one workgroup that keeps the most-updated
  *                 shared-vector entries in LDS (their gathers and adds never leave the CU) and
- *                 reads the others ahead of their coordinates; 0 = never.  The hot set is chosen
+ *                 reads the others ahead of their coordinates; 0 = never.  An automatic window of 17 to
+ *                 64 is cut to 16 for this where the epoch would be staged (below) and the hot set
+ *                 covers at least half of the stored entries.  The hot set is chosen
  *                 (a pass over the matrix, synchronising) when this first applies: at create, or
  *                 when "window" or "hot" is set.
  *   "team"        1 (default) = with a binding window, segments of at least 1,024 entries on
@@ -262,7 +264,7 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 flight) x K is at most the number of CUs.  With the automatic window, teams take
  *                 7/8 of the window's share that the other draining kernels take.
  *   "staged"      1 (default) = when the hot-set kernel runs the epoch and the matrix's entries take more
- *                 than 256 MB (beyond the GPU's Infinity Cache), the batches it runs are assembled by
+ *                 than 16 MB, the batches it runs are assembled by
  *                 stager workgroups on the hot-set workgroup's XCD (coordinate metadata, entry keys and
  *                 values, and the cold entries' shared-vector values) and passed through a ring of 32
  *                 records in device memory, so that the one workgroup only copies records and runs
@@ -273,7 +275,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *   "adapt"       1 (default) = when the window is automatic and the hot-set kernel runs the epoch,
  *                 each epoch's window follows the fraction f of coordinates whose step was nonzero
  *                 in the previous epoch: W = 1 + (auto_window - 1) / f, at most 16, run by
- *                 min(4, W / 2) consumer waves whose shares differ by at most one.  A coordinate
+ *                 min(4, W / 2) consumer waves (two at most where the epoch is not staged) whose shares
+ *                 differ by at most one.  A coordinate
  *                 whose step is zero (in the hinge SVM dual, one whose alpha stays at a bound of
  *                 the box) changes nothing that others read, so the coupling rule's budget holds
  *                 for the coordinates in flight that move.  The window is kept in device memory,

@@ -93,9 +93,19 @@ constexpr double kTeamMinMean = 1024.0;
 // permutation (the queued kernel's case).
 constexpr double kTeamMaxSkew = 4.0;  // longest segment at most this many times the mean
 constexpr int64_t kTeamMinSharedBytes = int64_t(4) << 20;
-// Staged hot-set epochs, automatic choice: matrices whose entries (8 bytes each) exceed the
-// 256 MB Infinity Cache, so that the producers' loads go to HBM, and a GPU with CUs for the stagers.
-constexpr int64_t kStagedMinBytes = int64_t(256) << 20;
+// Staged hot-set epochs, automatic choice: matrices whose entries take more than this (8 bytes each), and
+// a GPU with CUs for the stagers.  Click rows, settled, single workgroup against staged, ms an epoch:
+// 50,000 rows (15.6 MB) 1.39 and 0.59, 100,000 3.27 and 1.15, 500,000 15.9 and 5.7, 1 M 36 and 11.3.  The
+// smallest matrices, of which a program may run many at once on its streams, keep to the one workgroup:
+// a staged epoch wants 17 of one XCD's CUs.
+constexpr int64_t kStagedMinBytes = int64_t(16) << 20;
+// An automatic window above what the hot-set kernel holds is cut to that for a staged epoch, up to this
+// window and where the hot set covers at least this share of the entries: the pipelined kernel's atomics
+// then queue on the hot entries.  Click rows, pipelined (a wave per row) against staged at 16 in flight, ms an
+// epoch: 500,000 rows at window 17 29.2 and 5.7, at 32 15.8, at 100 5.5; 200,000 rows (ridge dual) at 40
+// 7.9 and 3.6; 2 M rows at 136 38 and 36.
+constexpr int64_t kHotWidenWindow = 64;
+constexpr double kHotWidenCover = 0.5;
 
 }  // namespace
 
@@ -209,28 +219,33 @@ struct HotGeom {
 // automatic (the coupling rule assumes that every coordinate in flight moves).
 bool hot_adaptive(const scd_solver* h) { return h->window == 0 && h->adapt != 0; }
 
+// Enough entries and CUs for the staged variant, or option 2.
+bool staged_wanted(const scd_solver* h) {
+    if (h->staged == 0 || h->cus < 1 + kHotXcds * kHotStagers) return false;
+    return h->staged == 2 || h->nnz * 8 > kStagedMinBytes;
+}
+
 bool hot_geometry(const scd_solver* h, int64_t W, HotGeom* g) {
+    if (W > kHotMaxWindow && h->window == 0 && W <= kHotWidenWindow && staged_wanted(h)) W = kHotMaxWindow;
     if (W < 2 || W > kHotMaxWindow || h->max_seg > kHotMaxSegment || h->C < 1) return false;
     g->W = (uint32_t)W;
     g->adaptive = hot_adaptive(h);
-    // A second consumer wave when the window may exceed what one consumer holds.
+    // The staged kernel's fixed windows: a second consumer wave when one cannot hold it.
     g->NC = (g->adaptive || W > kHotMaxGroups) ? 2u : 1u;
     g->Smax = (uint32_t)std::max<int64_t>(8, (h->max_seg + 7) / 8 * 8);
     g->cap = hot_batch_cap(g->Smax, kHotEntriesPerLane);  // the staged plan's is larger (staged_cap)
     if (g->cap < (uint32_t)kHotMaxGroups) return false;
-    g->hot_bytes = (uint32_t)(((size_t)(h->n_hot + kHotZeroCells) * (h->wide ? sizeof(double) : sizeof(float)) + 15) /
-                              16 * 16);
+    g->hot_bytes = (uint32_t)(((size_t)(h->n_hot + kHotZeroCells) * sizeof(HotCell) + 15) / 16 * 16);
     g->lds = hot_lds_bytes(g->hot_bytes, g->cap, g->Smax);
     return true;
 }
 
 // Largest hot set that fits LDS next to the largest batch buffers (64 x kStagedEntriesPerLane slots, the
-// staged plan's, which exceed the single-workgroup plan's) as
-// fp64 entries, so that it stays valid at both widths of the shared vector.
+// staged plan's, which exceed the single-workgroup plan's).
 uint32_t hot_capacity(const scd_solver* h) {
     const size_t worst = hot_lds_bytes(0, 64, kStagedEntriesPerLane);
     if (h->max_lds <= worst + 16) return 0;
-    const size_t cells = (h->max_lds - worst - 16) / sizeof(double);
+    const size_t cells = (h->max_lds - worst - 16) / sizeof(HotCell);
     if (cells <= (size_t)kHotZeroCells) return 0;
     return (uint32_t)std::min<size_t>(cells - kHotZeroCells, kHotCold - 1);
 }
@@ -287,12 +302,8 @@ int wide_group(const scd_solver* h, int G, int64_t groups) {
     return G;
 }
 
-// The staged variant: option 2, or option 1 with a matrix beyond the Infinity Cache; it needs its ring and
-// enough CUs for the stagers (all on the XCD of the hot-set workgroup).
-bool staged_plan(const scd_solver* h) {
-    if (h->staged == 0 || !h->ring || h->cus < 1 + kHotXcds * kHotStagers) return false;
-    return h->staged == 2 || h->nnz * 8 > kStagedMinBytes;
-}
+// The staged variant, once its ring is there (its stagers run on the XCD of the hot-set workgroup).
+bool staged_plan(const scd_solver* h) { return h->ring && staged_wanted(h); }
 
 // The staged plan's batches: kStagedEntriesPerLane slots per stager lane.  False if its LDS (the hot
 // workgroup's buffers, or the stagers' images) would not fit; the hot set is sized so that it does.
@@ -306,6 +317,7 @@ bool staged_geometry(const scd_solver* h, HotGeom* g) {
 
 bool hot_plan(const scd_solver* h, int64_t window, HotGeom* g) {
     // Its producers read cold values through a raw buffer over the shared vector (below 2 GiB).
+    if (window > kHotMaxWindow && (h->hot_cover < kHotWidenCover || !staged_plan(h))) return false;
     return h->hot && h->group == 0 && h->hot_built && h->n_hot > 0 && h->hot_cover >= kHotMinCover &&
            shared_bytes(h) <= kPipeMaxBytes && hot_geometry(h, window, g) && g->lds <= h->max_lds;
 }
@@ -605,8 +617,9 @@ int assign_slots(const scd_solver* h, const unsigned* hits, unsigned T, unsigned
 
 // Hot set of the hot-set kernel: the entries with at least T stored entries pointing at them (T
 // the smallest threshold that keeps the set within LDS capacity), slots in index order, so the
-// set is a deterministic function of the matrix.  Built once, on first need; synchronises.
-int build_hot_tables(scd_solver* h, hipStream_t s) {
+// set is a deterministic function of the matrix.  Built once, on first need, and not when it covers less
+// than min_cover of the stored entries; synchronises.
+int build_hot_tables(scd_solver* h, double min_cover, hipStream_t s) {
     if (h->hot_built) return SCD_OK;
     h->hot_built = 1;  // a set that cannot help (n_hot = 0) is not retried
     const uint32_t cap = hot_capacity(h);
@@ -626,6 +639,10 @@ int build_hot_tables(scd_solver* h, hipStream_t s) {
     unsigned long long cnt = 0, sum = 0;
     if (rc == SCD_OK) rc = hits_threshold(h, hits, cap, &T, s);
     if (rc == SCD_OK) rc = hot_count(h, hits, T, s, &cnt, &sum);
+    if (rc == SCD_OK && (double)sum < min_cover * (double)h->nnz) {
+        h->hot_built = 0;  // a narrower window may still want it
+        cnt = 0;
+    }
     if (rc == SCD_OK && cnt > 0 && (rc = assign_slots(h, hits, T, cnt, &slot_of, &h->hot_ids, s)) == SCD_OK) {
         // Each stored entry's key (-1 - hot slot, or its index), which the producers read in place of
         // idx (4 bytes per entry).  Without the memory for it the hot-set kernel is not used.
@@ -683,7 +700,7 @@ int hot_if_needed(scd_solver* h, hipStream_t s) {
     const int64_t window = h->window ? h->window : h->auto_window;
     HotGeom g;
     if (!h->hot || h->group != 0 || h->hot_built || !hot_geometry(h, window, &g)) return SCD_OK;
-    return build_hot_tables(h, s);
+    return build_hot_tables(h, window > kHotMaxWindow ? kHotWidenCover : 0.0, s);
 }
 
 void free_team_tables(scd_solver* h) {

@@ -151,11 +151,11 @@ __device__ __forceinline__ void hot_load_step(HotStep<SL>& t, const HotBuf& hb, 
 // behind one branch per step, taken by the groups whose step is nonzero (in the SVM dual, once their
 // alpha sits at a bound, most coordinates do not move).  A cold or padding slot reads its lane's
 // zero cell and adds coef * 0 to it, so no slot needs a select.
-template <int FORM, typename U, int SL>
-__device__ __forceinline__ void hot_step(const StepConsts& k, U* hot, const HotBuf& hb, float* scr, uint32_t Smax,
+template <int FORM, int SL>
+__device__ __forceinline__ void hot_step(const StepConsts& k, HotCell* hot, const HotBuf& hb, float* scr, uint32_t Smax,
                                          uint32_t cn, bool act, uint32_t sub, int lane, const HotStep<SL>& cur,
                                          uint32_t c, HotStep<SL>& nxt) {
-    U hv[SL];
+    HotCell hv[SL];
 #pragma unroll
     for (int r = 0; r < SL; ++r) hv[r] = hot[cur.kk[r]];
     __builtin_amdgcn_sched_barrier(0);
@@ -172,7 +172,7 @@ __device__ __forceinline__ void hot_step(const StepConsts& k, U* hot, const HotB
     *reinterpret_cast<float2*>(act ? &hb.rec[c].z : scr + 2 * lane) = make_float2(m_new, coef);
     if (coef != 0.0f) {
 #pragma unroll
-        for (int r = 0; r < SL; ++r) atomicAdd(hot + cur.kk[r], (U)(coef * cur.vv[r]));
+        for (int r = 0; r < SL; ++r) atomicAdd(hot + cur.kk[r], (HotCell)(coef * cur.vv[r]));
     }
 }
 
@@ -181,8 +181,8 @@ __device__ __forceinline__ void hot_step(const StepConsts& k, U* hot, const HotB
 // prefetch).  Hot entries are updated in LDS; the new model value and the coefficient go back into
 // the batch buffer, and the producer that owns it issues the global stores and atomics before
 // refilling it, so this wave never waits on global memory.
-template <int FORM, typename U, int SL>
-__device__ __forceinline__ void hot_consumer(const HotArgs& h, const HotSched& sc, uint32_t ci, U* hot,
+template <int FORM, int SL>
+__device__ __forceinline__ void hot_consumer(const HotArgs& h, const HotSched& sc, uint32_t ci, HotCell* hot,
                                              uint32_t* ready, uint32_t* freed, uint32_t* abort_flag, uint32_t* bufs,
                                              float* scr, int lane) {
     const StepConsts k = h.e.k;
@@ -208,12 +208,12 @@ __device__ __forceinline__ void hot_consumer(const HotArgs& h, const HotSched& s
         for (; st + 1 < S; st += 2) {
             const uint32_t c0 = st * W + g0, c1 = c0 + W;
             const uint32_t c2 = st + 2 < S ? c1 + W : c1;
-            hot_step<FORM, U, SL>(k, hot, hb, my_scr, Smax, c1, act, sub, lane, sa, c0, sb);
-            hot_step<FORM, U, SL>(k, hot, hb, my_scr, Smax, c2, act, sub, lane, sb, c1, sa);
+            hot_step<FORM, SL>(k, hot, hb, my_scr, Smax, c1, act, sub, lane, sa, c0, sb);
+            hot_step<FORM, SL>(k, hot, hb, my_scr, Smax, c2, act, sub, lane, sb, c1, sa);
         }
         if (st < S) {
             const uint32_t c0 = st * W + g0;
-            hot_step<FORM, U, SL>(k, hot, hb, my_scr, Smax, c0, act, sub, lane, sa, c0, sb);
+            hot_step<FORM, SL>(k, hot, hb, my_scr, Smax, c0, act, sub, lane, sa, c0, sb);
         }
         __hip_atomic_store(freed + p, n + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
@@ -239,11 +239,11 @@ __device__ __forceinline__ void hot_load_step16(HotStep<SL2>& t, const HotBuf& h
     }
 }
 
-template <int FORM, typename U, int SL2>
-__device__ __forceinline__ void hot_step16(const StepConsts& k, U* hot, const HotBuf& hb, float* scr, uint32_t Smax,
+template <int FORM, int SL2>
+__device__ __forceinline__ void hot_step16(const StepConsts& k, HotCell* hot, const HotBuf& hb, float* scr, uint32_t Smax,
                                            uint32_t cn, bool act, uint32_t sub, int lane, int32_t zkey,
                                            const HotStep<SL2>& cur, uint32_t c, HotStep<SL2>& nxt) {
-    U hv[SL2];
+    HotCell hv[SL2];
 #pragma unroll
     for (int r = 0; r < SL2; ++r) hv[r] = hot[cur.kk[r]];
     __builtin_amdgcn_sched_barrier(0);
@@ -259,12 +259,12 @@ __device__ __forceinline__ void hot_step16(const StepConsts& k, U* hot, const Ho
     *reinterpret_cast<float2*>(act && sub == 0 ? &hb.rec[c].z : scr + 2 * lane) = make_float2(m_new, coef);
     if (coef != 0.0f) {
 #pragma unroll
-        for (int r = 0; r < SL2; ++r) atomicAdd(hot + cur.kk[r], (U)(coef * cur.vv[r]));
+        for (int r = 0; r < SL2; ++r) atomicAdd(hot + cur.kk[r], (HotCell)(coef * cur.vv[r]));
     }
 }
 
-template <int FORM, typename U, int SL2, int SL>
-__device__ __forceinline__ void hot_consumer16(const HotArgs& h, const HotSched& sc, uint32_t ci, U* hot,
+template <int FORM, int SL2, int SL>
+__device__ __forceinline__ void hot_consumer16(const HotArgs& h, const HotSched& sc, uint32_t ci, HotCell* hot,
                                                uint32_t* ready, uint32_t* freed, uint32_t* abort_flag, uint32_t* bufs,
                                                float* scr, int lane) {
     const StepConsts k = h.e.k;
@@ -287,12 +287,12 @@ __device__ __forceinline__ void hot_consumer16(const HotArgs& h, const HotSched&
         for (; st + 1 < S; st += 2) {
             const uint32_t c0 = st * W + g0, c1 = c0 + W;
             const uint32_t c2 = st + 2 < S ? c1 + W : c1;
-            hot_step16<FORM, U, SL2>(k, hot, hb, my_scr, Smax, c1, act, sub, lane, zkey, sa, c0, sb);
-            hot_step16<FORM, U, SL2>(k, hot, hb, my_scr, Smax, c2, act, sub, lane, zkey, sb, c1, sa);
+            hot_step16<FORM, SL2>(k, hot, hb, my_scr, Smax, c1, act, sub, lane, zkey, sa, c0, sb);
+            hot_step16<FORM, SL2>(k, hot, hb, my_scr, Smax, c2, act, sub, lane, zkey, sb, c1, sa);
         }
         if (st < S) {
             const uint32_t c0 = st * W + g0;
-            hot_step16<FORM, U, SL2>(k, hot, hb, my_scr, Smax, c0, act, sub, lane, zkey, sa, c0, sb);
+            hot_step16<FORM, SL2>(k, hot, hb, my_scr, Smax, c0, act, sub, lane, zkey, sa, c0, sb);
         }
         __hip_atomic_store(freed + p, n + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
@@ -493,7 +493,7 @@ template <int FORM, typename U, int SL>
 __global__ __launch_bounds__(64 * kHotWaves) void k_epoch_hot(HotArgs h) {
     extern __shared__ __align__(16) unsigned char hot_lds[];
     const EpochArgs& a = h.e;
-    U* const hot = reinterpret_cast<U*>(hot_lds);
+    HotCell* const hot = reinterpret_cast<HotCell*>(hot_lds);
     uint32_t* const ready = reinterpret_cast<uint32_t*>(hot_lds + h.hot_bytes);
     uint32_t* const freed = ready + kHotMaxProducers;
     uint32_t* const abort_flag = freed + kHotMaxProducers;
@@ -514,21 +514,21 @@ __global__ __launch_bounds__(64 * kHotWaves) void k_epoch_hot(HotArgs h) {
         const uint32_t v = __hip_atomic_load(h.adapt_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (v >= 2 && v <= (uint32_t)kHotMaxWindow) W = v;
     }
-    if (h.adapt_out) NC = hot_adaptive_consumers(W);
+    NC = hot_unstaged_consumers(W);
     const HotSched sc = hot_sched(W, NC, h.cap, h.pos_n);
-    for (uint32_t i = tid; i < h.n_hot + kHotZeroCells; i += blockDim.x) hot[i] = i < h.n_hot ? uu[h.hot_ids[i]] : U(0);
+    for (uint32_t i = tid; i < h.n_hot + kHotZeroCells; i += blockDim.x) hot[i] = i < h.n_hot ? (HotCell)uu[h.hot_ids[i]] : HotCell(0);
     if (tid < 2 * kHotMaxProducers + 2) ready[tid] = 0u;  // ready, freed, abort and moved are contiguous
     __syncthreads();
     if ((uint32_t)wave < sc.NC) {
         if (sc.w_hi <= 4)
-            hot_consumer16<FORM, U, (SL + 1) / 2, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
+            hot_consumer16<FORM, (SL + 1) / 2, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
         else
-            hot_consumer<FORM, U, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
+            hot_consumer<FORM, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
     } else {
         hot_producer<FORM, U>(h, sc, ready, freed, abort_flag, bufs, moved, wave - (int)sc.NC, lane);
     }
     __syncthreads();
-    for (uint32_t i = tid; i < h.n_hot; i += blockDim.x) uu[h.hot_ids[i]] = hot[i];
+    for (uint32_t i = tid; i < h.n_hot; i += blockDim.x) uu[h.hot_ids[i]] = (U)hot[i];
     // Next launch's window: (W - 1) f kappa <= budget with a fraction f of this launch's coordinates
     // moving, i.e. W = 1 + (w_rule - 1) / f, at most what the consumers hold.  A launch that gave up
     // keeps the window.
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(64 * kHotWaves) void k_epoch_staged(HotArgs h) {
             staged_stager<FORM, U>(h, sc, reinterpret_cast<uint32_t*>(hot_lds));
         return;
     }
-    U* const hot = reinterpret_cast<U*>(hot_lds);
+    HotCell* const hot = reinterpret_cast<HotCell*>(hot_lds);
     uint32_t* const ready = reinterpret_cast<uint32_t*>(hot_lds + h.hot_bytes);
     uint32_t* const freed = ready + kHotMaxProducers;
     uint32_t* const abort_flag = freed + kHotMaxProducers;
@@ -945,18 +945,18 @@ __global__ __launch_bounds__(64 * kHotWaves) void k_epoch_staged(HotArgs h) {
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __hip_atomic_store(h.prog, h.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    for (uint32_t i = tid; i < h.n_hot + kHotZeroCells; i += blockDim.x) hot[i] = i < h.n_hot ? uu[h.hot_ids[i]] : U(0);
+    for (uint32_t i = tid; i < h.n_hot + kHotZeroCells; i += blockDim.x) hot[i] = i < h.n_hot ? (HotCell)uu[h.hot_ids[i]] : HotCell(0);
     if (tid < 2 * kHotMaxProducers + 2) ready[tid] = 0u;
     __syncthreads();
     if ((uint32_t)wave < sc.NC) {
         if (sc.w_hi <= 4)
-            hot_consumer16<FORM, U, (SL + 1) / 2, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
+            hot_consumer16<FORM, (SL + 1) / 2, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
         else
-            hot_consumer<FORM, U, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
+            hot_consumer<FORM, SL>(h, sc, (uint32_t)wave, hot, ready, freed, abort_flag, bufs, scr, lane);
     } else
         staged_loader<FORM, U>(h, sc, ready, freed, abort_flag, bufs, moved, wave - (int)sc.NC, lane);
     __syncthreads();
-    for (uint32_t i = tid; i < h.n_hot; i += blockDim.x) uu[h.hot_ids[i]] = hot[i];
+    for (uint32_t i = tid; i < h.n_hot; i += blockDim.x) uu[h.hot_ids[i]] = (U)hot[i];
     if (h.adapt_out && tid == 0 && *abort_flag == 0u) {
         const uint64_t mv = *moved, wmax = kHotMaxWindow;
         uint64_t w = mv ? 1 + (uint64_t)(h.w_rule - 1) * h.pos_n / mv : wmax;

@@ -127,6 +127,11 @@ constexpr int kHotMaxWindow = 2 * kHotMaxGroups;  // coordinates in flight at mo
 constexpr uint32_t kHotOpening = 16;
 constexpr int kHotMaxSegment = 64;
 
+// The hot set in LDS is fp64 whatever the shared vector's type: an LDS fp32 atomic add takes 1.2 ns a
+// lane (80 ns a wave, the same for conflict-free and random addresses), an fp64 one 3.4 ns a wave without
+// conflicts and 9.4 on random addresses.  50,000 click rows on an fp32 shared vector, first four epochs
+// and settled: 2.29 and 1.96 ms an epoch with fp32 cells, 1.84 and 1.77 with fp64.
+using HotCell = double;
 constexpr uint16_t kHotCold = 0xFFFF;    // slot_of value of an entry that is not hot
 
 // 32-bit words of one batch buffer (B coordinates, Smax entry slots each): a 4-word record per
@@ -248,6 +253,11 @@ __host__ __device__ inline uint32_t hot_adaptive_consumers(uint32_t W) {
     const uint32_t n = W / 2;
     return n < 1 ? 1u : n > (uint32_t)kHotMaxConsumers ? (uint32_t)kHotMaxConsumers : n;
 }
+
+// Consumers of the single-workgroup kernel, fixed or adaptive: its other waves assemble the batches and
+// set the pace at wide windows, so it keeps ten of them (50,000 click rows, ms an epoch: 16 in flight on
+// two consumers 1.46, on four 1.76; 8 in flight on two 1.51, on one 1.80; 4 on two 2.13, on one 2.59).
+__host__ __device__ inline uint32_t hot_unstaged_consumers(uint32_t W) { return W >= 4 ? 2u : 1u; }
 
 size_t hot_lds_bytes(uint32_t hot_bytes, uint32_t B, uint32_t Smax);
 // Dynamic LDS of a staged launch: every workgroup gets the same size, and a stager keeps one batch

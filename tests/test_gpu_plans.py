@@ -171,3 +171,41 @@ def test_coupling_estimate_without_memory_for_the_rows():
     torch.cuda.empty_cache()
     for c, h in got:
         assert abs(c - coupling) <= 2e-5 * coupling and abs(h - coherence) <= 2e-5 * max(abs(coherence), coupling)
+
+
+# ------------------------------------------------------------- hot-set plans
+
+def test_staged_from_16_mb_of_entries():
+    # 39 entries of 8 bytes a row: the first matrix above 16 MiB has 53,774 rows.
+    for rows, kernel in ((53_773, "hot_lds"), (53_774, "hot_staged")):
+        p = synth.make("click_svm", n_rows=rows, n_cols=70_003)
+        s = scd.solver_for(p)
+        info = s.info()
+        print(f"{rows} rows: {info['kernel']} auto window {info['auto_window']}", flush=True)
+        assert info["kernel"] == kernel
+        follow_oracle(p, s, 4)
+        s.close()
+
+
+@pytest.mark.parametrize("wide", [0, 1])
+def test_wide_automatic_window_cut_for_the_hot_set(wide):
+    # The ridge dual on click rows couples weakly enough for a window between 17 and 64 at this
+    # lambda; cut to 16 for the staged kernel, it follows the oracle; an explicit window, the option
+    # staged = 0 and a smaller matrix keep the pipelined kernel.
+    p = synth.as_ridge_dual(synth.make("click_svm", n_rows=60_000, n_cols=90_000, lam=6 / 60_000))
+    s = scd.solver_for(p)
+    s.set_option("shared_fp64", wide)
+    auto = s.info()["auto_window"]
+    print(f"auto window {auto} {s.info()['kernel']} hot {s.info()['hot_entries']}", flush=True)
+    assert 16 < auto <= 64 and s.info()["kernel"] == "hot_staged" and s.info()["window"] == 16
+    follow_oracle(p, s, 4)
+    for key, value in (("window", auto), ("staged", 0), ("hot", 0), ("group", 8), ("pipeline", 0)):
+        s.set_option(key, value)
+        assert (s.info()["kernel"] == "hot_staged") == (key == "pipeline"), key
+        s.set_option(key, {"staged": 1, "hot": 1, "pipeline": 1}.get(key, 0))
+        assert s.info()["kernel"] == "hot_staged", key
+    s.close()
+    small = synth.as_ridge_dual(synth.make("click_svm", n_rows=40_000, n_cols=60_000, lam=6 / 40_000))
+    s = scd.solver_for(small)
+    assert s.info()["auto_window"] > 16 and s.info()["kernel"] == "pipelined"
+    s.close()
