@@ -1000,6 +1000,16 @@ void release(scd_solver* h) {
     delete h;
 }
 
+// The hot set for the passes over all coordinates, where its tables exist: worth its copies into LDS (up
+// to 62 KB for each of two workgroups per CU) once the matrix has kHotPassMinEntries entries.
+constexpr int64_t kHotPassMinEntries = int64_t(8) << 20;
+HotCells hot_cells(const scd_solver* h) {
+    if (!h->n_hot || h->nnz < kHotPassMinEntries || h->L * (int64_t)sizeof(double) > kPipeMaxBytes ||
+        2 * h->n_hot * sizeof(double) > h->max_lds)
+        return HotCells{nullptr, nullptr, 0};
+    return HotCells{h->entry_key, h->hot_ids, h->n_hot};
+}
+
 // Enqueue the five reduction sums of the current state and their copy into host[0..4].
 int enqueue_sums(scd_solver* h, hipStream_t s, double* host) {
     ObjArgs o{};
@@ -1017,7 +1027,8 @@ int enqueue_sums(scd_solver* h, hipStream_t s, double* host) {
     o.lam = h->lambda;
     const int G = obj_group(h);
     const int blocks = obj_blocks(h, G);
-    HIP_TRY(launch_objective(h->form, o, G, blocks, h->partials, h->sums, s));
+    o.hot = hot_cells(h);
+    HIP_TRY(launch_objective(h->form, o, G, blocks, h->cus, h->partials, h->sums, s));
     HIP_TRY(hipMemcpyAsync(host, h->sums, 5 * sizeof(double), hipMemcpyDeviceToHost, s));
     return SCD_OK;
 }
@@ -1611,8 +1622,8 @@ int scd_gather_dots(scd_handle_t h, const float* u, float* out, void* stream) {
     if (!u || !out) return fail(SCD_ERR_INVALID, "null device pointer");
     if (int r = set_device(h)) return r;
     const int G = obj_group(h);
-    HIP_TRY(launch_gather_dots(h->ptr, h->idx, h->val, u, (uint32_t)h->C, G, obj_blocks(h, G), out,
-                               (hipStream_t)stream));
+    HIP_TRY(launch_gather_dots(h->ptr, h->idx, h->val, u, (uint32_t)h->C, h->L, hot_cells(h), G, obj_blocks(h, G), h->cus,
+                               out, (hipStream_t)stream));
     return SCD_OK;
 }
 

@@ -89,6 +89,13 @@ struct LaunchPlan {
     size_t lds_bytes;
 };
 
+// The hot set for passes over all coordinates against a frozen vector: n = 0 for none.
+struct HotCells {
+    const int32_t* key;  // [nnz]: -1 - slot, or the index
+    const int32_t* ids;  // [n]
+    uint32_t n;
+};
+
 struct ObjArgs {
     const int64_t* ptr;
     const int32_t* idx;
@@ -102,6 +109,7 @@ struct ObjArgs {
     uint32_t C;
     int64_t L;
     double lam;
+    HotCells hot;
 };
 
 // Hot-set epoch (one workgroup of kHotWaves waves): the n_hot most-updated shared-vector entries live
@@ -374,7 +382,7 @@ hipError_t launch_perm_fill(const PermKeys& p, int32_t* out, hipStream_t s);
 // Copies the packed shared vector into its spread copy (entry i at byte i << kSpreadShift), or back.
 hipError_t launch_spread(void* packed, void* spread, int64_t L, bool wide, bool to_spread, hipStream_t s);
 hipError_t launch_gather_dots(const int64_t* ptr, const int32_t* idx, const float* val, const float* u, uint32_t C,
-                              int G, int blocks, float* out, hipStream_t s);
+                              int64_t L, const HotCells& hc, int G, int blocks, int cus, float* out, hipStream_t s);
 hipError_t launch_norms(const int64_t* ptr, const int32_t* idx, const float* val, const float* y, uint32_t C, int G,
                         int blocks, float* out, float* cy, double* cyd, hipStream_t s);
 hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, const float* val, int64_t nnz,
@@ -408,9 +416,9 @@ hipError_t launch_probe_gather(const ProbeArgs& a, int np, int G, int blocks, hi
 hipError_t launch_probe_totals(const float* T0, int64_t L, const float* norms, uint32_t C, float mu, int blocks,
                                double* partials, double* out, hipStream_t s);
 hipError_t launch_sum_partials(const double* partials, int nparts, int width, double* out, hipStream_t s);
-// One objective evaluation: k_objective (partials[blocks][5]) and k_sum_partials (sums[0..4]).  With
-// o.cyd null the ridge primal gathers y beside the shared vector.
-hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, double* partials, double* sums,
+// One objective evaluation: k_objective (partials[blocks][5]; at most two workgroups per CU with o.hot)
+// and k_sum_partials (sums[0..4]).  With o.cyd null the ridge primal gathers y beside the shared vector.
+hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, int cus, double* partials, double* sums,
                             hipStream_t s);
 hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s);
 // Sets the calling thread's message returned by scd_last_error.

@@ -13,19 +13,74 @@ __global__ void k_perm_fill(PermKeys p, int32_t* __restrict__ out) {
 }
 
 // ----------------------------------------------------------------------------------------
-// Frozen gather-dot: out[c] = <a_c, u> with the epoch kernel's arithmetic (fp32 FMA per
-// lane, group butterfly), for every coordinate in index order.
+// Gathers of the frozen passes (gather-dot, objectives).  Scattered loads bound them: 130-140 G/s on
+// click rows, whose stored values would stream in a third of that time.  With HOT, the solver's hot set
+// (the most used entries, most of them in every wave's rows) is copied into LDS by each workgroup and
+// read there; `key` stands in for idx (-1 - slot, or the index), and only the cold entries' loads
+// leave the CU (hot lanes use an out-of-range offset of the raw buffer: no access).
 // ----------------------------------------------------------------------------------------
-template <int G>
-__global__ __launch_bounds__(256) void k_gather_dots(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
-                                                     const float* __restrict__ val, const float* __restrict__ u,
-                                                     uint32_t C, float* __restrict__ out) {
+constexpr int kHotPassThreads = 1024;  // two workgroups of 16 waves a CU share the copies
+
+template <typename U>
+__device__ __forceinline__ void hot_fill(U* cells, const HotCells& hc, const U* u) {
+    for (uint32_t i = threadIdx.x; i < hc.n; i += blockDim.x) cells[i] = u[hc.ids[i]];
+    __syncthreads();
+}
+
+template <typename U>
+__device__ __forceinline__ U hot_or_load(const __amdgpu_buffer_rsrc_t& r, const U* cells, int key) {
+    const U h = cells[key < 0 ? -1 - key : 0];
+    const int off = key < 0 ? (int)0x7FFFFFF8 : (int)((uint32_t)key * (uint32_t)sizeof(U));
+    if constexpr (sizeof(U) == 4) {
+        const float g = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+        return key < 0 ? h : g;
+    } else {
+        const double g = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+        return key < 0 ? h : g;
+    }
+}
+
+// ----------------------------------------------------------------------------------------
+// Frozen gather-dot: out[c] = <a_c, u> with the epoch kernel's arithmetic (fp32 FMA per
+// lane, group butterfly), for every coordinate in index order.  Blocks of G * R entries: all index
+// and value loads, then all gathers; a lane past the end re-reads entry s0 with weight 0.
+// 5 M click rows (195 M entries): 1.40 ms one entry at a time, 0.75 in blocks with the hot set in LDS (the
+// objectives 1.34 and 0.86); 16.6 M columns of 1 to 350,000 entries, no hot set: 18.1 and 8.6 ms.
+// ----------------------------------------------------------------------------------------
+template <int G, int R, bool HOT>
+__global__ __launch_bounds__(HOT ? kHotPassThreads : 256) void k_gather_dots(
+    const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, const float* __restrict__ val,
+    const float* __restrict__ u, uint32_t C, HotCells hc, uint32_t u_bytes, float* __restrict__ out) {
+    extern __shared__ __align__(16) unsigned char pass_lds[];
+    float* const cells = reinterpret_cast<float*>(pass_lds);
+    if constexpr (HOT) hot_fill(cells, hc, u);
+    const __amdgpu_buffer_rsrc_t ur = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(u), (short)0, (int)u_bytes, 0x00020000);
     const int lane = threadIdx.x & (G - 1);
-    const uint32_t ngroups = gridDim.x * (256u / G);
-    for (uint32_t c = (blockIdx.x * 256u + threadIdx.x) / G; c < C; c += ngroups) {
+    const uint32_t ngroups = gridDim.x * (blockDim.x / G);
+    for (uint32_t c = (blockIdx.x * blockDim.x + threadIdx.x) / G; c < C; c += ngroups) {
         const int64_t s0 = ptr[c], s1 = ptr[c + 1];
         float acc = 0.0f;
-        for (int64_t k = s0 + lane; k < s1; k += G) acc = fmaf(val[k], u[idx[k]], acc);
+        for (int64_t b = s0; b < s1; b += (int64_t)G * R) {
+            int ix[R];
+            float vx[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int64_t k = b + lane + (int64_t)r * G;
+                const bool in = k < s1;
+                const int64_t kk = in ? k : s0;
+                ix[r] = HOT ? hc.key[kk] : idx[kk];
+                const float v = val[kk];
+                vx[r] = in ? v : 0.0f;
+            }
+            float g[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if constexpr (HOT) g[r] = hot_or_load<float>(ur, cells, ix[r]);
+                else g[r] = u[ix[r]];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc = fmaf(vx[r], g[r], acc);
+        }
         acc = group_sum<G>(acc);
         if (lane == 0) out[c] = acc;
     }
@@ -115,7 +170,7 @@ __global__ void k_validate_labels(const float* __restrict__ y, int64_t n, int pm
 // ----------------------------------------------------------------------------------------
 template <int NS>
 __device__ __forceinline__ void block_reduce_store(double (&v)[NS], double* out) {
-    __shared__ double red[NS][256 / 64];
+    __shared__ double red[NS][kHotPassThreads / 64];
     const int tid = threadIdx.x;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -126,22 +181,34 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NS], double* out)
     __syncthreads();
     if (tid == 0) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) out[s] = red[s][0] + red[s][1] + red[s][2] + red[s][3];
+        for (int s = 0; s < NS; ++s) {
+            double x = 0.0;
+            for (uint32_t w = 0; w < blockDim.x / 64; ++w) x += red[s][w];
+            out[s] = x;
+        }
     }
 }
 
-constexpr int kObjSlices = 8;  // entries per lane per block of the objective's gather-dot
+// Entries per lane per block of the objective's gather-dot.  Narrow groups take one block per segment
+// of the lengths that choose them, so that few lanes re-read entry s0.
+constexpr int obj_slices(int G) { return G <= 8 ? slice_depth(G) : 8; }
 
 // DIRECT (ridge primal only): <a_c, y - w> is gathered from y and w in fp64 instead of taken as
 // <y, a_c> (o.cyd, computed at set-up) minus <a_c, w>; for callers that hold no set-up data.
-template <int FORM, int G, typename U, bool DIRECT>
-__global__ __launch_bounds__(256) void k_objective(ObjArgs o, double* __restrict__ partials) {
-    constexpr int NS = 5;
+template <int FORM, int G, typename U, bool DIRECT, bool HOT>
+__global__ __launch_bounds__(HOT ? kHotPassThreads : 256) void k_objective(ObjArgs o, double* __restrict__ partials) {
+    static_assert(!(DIRECT && HOT), "callers without set-up data hold no hot set");
+    constexpr int NS = 5, kObjSlices = obj_slices(G);
+    extern __shared__ __align__(16) unsigned char pass_lds[];
     const U* __restrict__ u = static_cast<const U*>(o.u);
+    U* const cells = reinterpret_cast<U*>(pass_lds);
+    if constexpr (HOT) hot_fill(cells, o.hot, u);
+    const __amdgpu_buffer_rsrc_t ur =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(o.u), (short)0, HOT ? (int)(o.L * (int64_t)sizeof(U)) : 0, 0x00020000);
     const int lane = threadIdx.x & (G - 1);
-    const uint32_t ngroups = gridDim.x * (256u / G);
+    const uint32_t ngroups = gridDim.x * (blockDim.x / G);
     double t[NS] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (uint32_t c = (blockIdx.x * 256u + threadIdx.x) / G; c < o.C; c += ngroups) {
+    for (uint32_t c = (blockIdx.x * blockDim.x + threadIdx.x) / G; c < o.C; c += ngroups) {
         // Blocks of G * kObjSlices entries: all index and value loads of a block, then all its
         // gathers, so that a block costs two memory round trips instead of two per entry.  Lanes
         // past the end re-read entry s0 with weight 0.
@@ -155,13 +222,16 @@ __global__ __launch_bounds__(256) void k_objective(ObjArgs o, double* __restrict
                 const int64_t k = b + lane + (int64_t)r * G;
                 const bool in = k < s1;
                 const int64_t kk = in ? k : s0;
-                ix[r] = o.idx[kk];
+                ix[r] = HOT ? o.hot.key[kk] : o.idx[kk];
                 const float v = o.val[kk];
                 vx[r] = in ? v : 0.0f;
             }
             U g[kObjSlices];
 #pragma unroll
-            for (int r = 0; r < kObjSlices; ++r) g[r] = u[ix[r]];
+            for (int r = 0; r < kObjSlices; ++r) {
+                if constexpr (HOT) g[r] = hot_or_load<U>(ur, cells, ix[r]);
+                else g[r] = u[ix[r]];
+            }
             if constexpr (DIRECT) {
                 float yy[kObjSlices];
 #pragma unroll
@@ -192,7 +262,7 @@ __global__ __launch_bounds__(256) void k_objective(ObjArgs o, double* __restrict
             }
         }
     }
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < o.L; i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < o.L; i += (int64_t)gridDim.x * blockDim.x) {
         if constexpr (FORM == FORM_RIDGE_PRIMAL) {
             const double r = (double)o.yv[i] - (double)u[i];
             t[3] += r * r;
@@ -271,16 +341,40 @@ hipError_t launch_perm_fill(const PermKeys& p, int32_t* out, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_gather_dots(const int64_t* ptr, const int32_t* idx, const float* val, const float* u, uint32_t C,
-                              int G, int blocks, float* out, hipStream_t s) {
-    switch (G) {
-        case 4: hipLaunchKernelGGL(k_gather_dots<4>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, out); break;
-        case 8: hipLaunchKernelGGL(k_gather_dots<8>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, out); break;
-        case 16: hipLaunchKernelGGL(k_gather_dots<16>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, out); break;
-        case 32: hipLaunchKernelGGL(k_gather_dots<32>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, out); break;
-        default: hipLaunchKernelGGL(k_gather_dots<64>, dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, out); break;
+// The hot passes' launch: dynamic LDS for the cells, and two workgroups per CU at most.
+static hipError_t hot_pass_lds(const void* f, size_t lds) {
+    return lds > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipSuccess;
+}
+
+static unsigned hot_pass_blocks(int64_t C, int G, int cus) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(2 * (int64_t)cus, (C * G + kHotPassThreads - 1) / kHotPassThreads));
+}
+
+template <int G>
+static hipError_t gather_typed(const int64_t* ptr, const int32_t* idx, const float* val, const float* u, uint32_t C,
+                               int64_t L, const HotCells& hc, int blocks, int cus, float* out, hipStream_t s) {
+    constexpr int R = slice_depth(G);
+    if (hc.n) {
+        const size_t lds = sizeof(float) * hc.n;
+        const hipError_t e = hot_pass_lds(reinterpret_cast<const void*>(&k_gather_dots<G, R, true>), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_gather_dots<G, R, true>), dim3(hot_pass_blocks(C, G, cus)), dim3(kHotPassThreads), lds, s, ptr,
+                           idx, val, u, C, hc, (uint32_t)(L * 4), out);
+    } else {
+        hipLaunchKernelGGL((k_gather_dots<G, R, false>), dim3(blocks), dim3(256), 0, s, ptr, idx, val, u, C, hc, 0u, out);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_gather_dots(const int64_t* ptr, const int32_t* idx, const float* val, const float* u, uint32_t C,
+                              int64_t L, const HotCells& hc, int G, int blocks, int cus, float* out, hipStream_t s) {
+    switch (G) {
+        case 4: return gather_typed<4>(ptr, idx, val, u, C, L, hc, blocks, cus, out, s);
+        case 8: return gather_typed<8>(ptr, idx, val, u, C, L, hc, blocks, cus, out, s);
+        case 16: return gather_typed<16>(ptr, idx, val, u, C, L, hc, blocks, cus, out, s);
+        case 32: return gather_typed<32>(ptr, idx, val, u, C, L, hc, blocks, cus, out, s);
+        default: return gather_typed<64>(ptr, idx, val, u, C, L, hc, blocks, cus, out, s);
+    }
 }
 
 hipError_t launch_norms(const int64_t* ptr, const int32_t* idx, const float* val, const float* y, uint32_t C, int G,
@@ -310,38 +404,43 @@ hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, c
     return hipGetLastError();
 }
 
+template <int FORM, int G, typename U, bool DIRECT>
+static hipError_t objective_launch(const ObjArgs& o, int* blocks, int cus, double* partials, hipStream_t s) {
+    if constexpr (!DIRECT) {
+        if (o.hot.n) {
+            const size_t lds = sizeof(U) * o.hot.n;
+            const hipError_t e = hot_pass_lds(reinterpret_cast<const void*>(&k_objective<FORM, G, U, false, true>), lds);
+            if (e != hipSuccess) return e;
+            *blocks = (int)hot_pass_blocks(o.C, G, cus);
+            hipLaunchKernelGGL((k_objective<FORM, G, U, false, true>), dim3(*blocks), dim3(kHotPassThreads), lds, s, o, partials);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_objective<FORM, G, U, DIRECT, false>), dim3(*blocks), dim3(256), 0, s, o, partials);
+    return hipGetLastError();
+}
+
 template <int FORM, typename U, bool DIRECT>
-static void objective_typed(const ObjArgs& o, int G, int blocks, double* partials, hipStream_t s) {
+static hipError_t objective_typed(const ObjArgs& o, int G, int* blocks, int cus, double* partials, hipStream_t s) {
     switch (G) {
-#define SCD_OBJ(GW)                                                                                         \
-    case GW:                                                                                                \
-        hipLaunchKernelGGL((k_objective<FORM, GW, U, DIRECT>), dim3(blocks), dim3(256), 0, s, o, partials); \
-        break;
-        SCD_OBJ(4)
-        SCD_OBJ(8)
-        SCD_OBJ(16)
-        SCD_OBJ(32)
-        default: SCD_OBJ(64)
-#undef SCD_OBJ
+        case 4: return objective_launch<FORM, 4, U, DIRECT>(o, blocks, cus, partials, s);
+        case 8: return objective_launch<FORM, 8, U, DIRECT>(o, blocks, cus, partials, s);
+        case 16: return objective_launch<FORM, 16, U, DIRECT>(o, blocks, cus, partials, s);
+        case 32: return objective_launch<FORM, 32, U, DIRECT>(o, blocks, cus, partials, s);
+        default: return objective_launch<FORM, 64, U, DIRECT>(o, blocks, cus, partials, s);
     }
 }
 
 template <int FORM>
-static void objective_form(const ObjArgs& o, int G, int blocks, double* partials, hipStream_t s) {
+static hipError_t objective_form(const ObjArgs& o, int G, int* blocks, int cus, double* partials, hipStream_t s) {
     // The ridge primal without <y, a_c> from set-up gathers y beside w.
     if constexpr (FORM == FORM_RIDGE_PRIMAL) {
-        if (!o.cyd) {
-            if (o.wide)
-                objective_typed<FORM, double, true>(o, G, blocks, partials, s);
-            else
-                objective_typed<FORM, float, true>(o, G, blocks, partials, s);
-            return;
-        }
+        if (!o.cyd)
+            return o.wide ? objective_typed<FORM, double, true>(o, G, blocks, cus, partials, s)
+                          : objective_typed<FORM, float, true>(o, G, blocks, cus, partials, s);
     }
-    if (o.wide)
-        objective_typed<FORM, double, false>(o, G, blocks, partials, s);
-    else
-        objective_typed<FORM, float, false>(o, G, blocks, partials, s);
+    return o.wide ? objective_typed<FORM, double, false>(o, G, blocks, cus, partials, s)
+                  : objective_typed<FORM, float, false>(o, G, blocks, cus, partials, s);
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(uint64_t* __restrict__ p, uint32_t n) {
@@ -356,16 +455,17 @@ hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s) {
 }
 
 // sums[0..2] = coordinate sums, sums[3..4] = vector sums.
-hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, double* partials, double* sums,
+hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, int cus, double* partials, double* sums,
                             hipStream_t s) {
+    hipError_t e = hipErrorInvalidValue;
     switch (form) {
-        case FORM_RIDGE_PRIMAL: objective_form<FORM_RIDGE_PRIMAL>(o, G, blocks, partials, s); break;
-        case FORM_SVM_DUAL: objective_form<FORM_SVM_DUAL>(o, G, blocks, partials, s); break;
-        case FORM_RIDGE_DUAL: objective_form<FORM_RIDGE_DUAL>(o, G, blocks, partials, s); break;
-        default: return hipErrorInvalidValue;
+        case FORM_RIDGE_PRIMAL: e = objective_form<FORM_RIDGE_PRIMAL>(o, G, &blocks, cus, partials, s); break;
+        case FORM_SVM_DUAL: e = objective_form<FORM_SVM_DUAL>(o, G, &blocks, cus, partials, s); break;
+        case FORM_RIDGE_DUAL: e = objective_form<FORM_RIDGE_DUAL>(o, G, &blocks, cus, partials, s); break;
+        default: break;
     }
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, partials, blocks, 5, sums);
-    return hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_sum_partials(partials, blocks, 5, sums, s);
 }
 
 // ----------------------------------------------------------------------------------------

@@ -119,7 +119,7 @@ extern "C" int scd_objective_static(const scd_matrix_t* A, const float* y, doubl
     const int G = objective_group(C > 0 ? (double)A->nnz / (double)C : 0.0);
     const int blocks = objective_blocks(C, G);
     double t[5] = {0, 0, 0, 0, 0};
-    e = launch_objective(formulation, o, G, blocks, partials, sums, s);
+    e = launch_objective(formulation, o, G, blocks, 1, partials, sums, s);
     if (e == hipSuccess) e = hipMemcpyAsync(t, sums, sizeof t, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_static(SCD_ERR_HIP, "objective pass", e);

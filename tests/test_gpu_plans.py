@@ -209,3 +209,56 @@ def test_wide_automatic_window_cut_for_the_hot_set(wide):
     s = scd.solver_for(small)
     assert s.info()["auto_window"] > 16 and s.info()["kernel"] == "pipelined"
     s.close()
+
+
+# ------------------------------------------------------------- passes over a frozen vector
+
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("form,rows", [("svm_dual", 215_093), ("svm_dual", 215_093 - 5), ("ridge_dual", 217_001)])
+def test_frozen_passes_with_the_hot_set_in_lds(form, rows, wide):
+    # 39 entries a row: the passes read the hot set from LDS from 8 Mi entries (215,093 rows) on.
+    # Tolerances: a 39-term fp32 sum, 39 x 2^-24 of sum |a u|; fp64 objectives 1e-9.
+    p = synth.make("click_svm", n_rows=rows, n_cols=300_007)
+    p = synth.as_ridge_dual(p) if form == "ridge_dual" else p
+    s = scd.solver_for(p)
+    s.set_option("window", 8)  # builds the hot set whatever the automatic window is
+    s.set_option("shared_fp64", wide)
+    assert s.info()["hot_entries"] > 0 and (p.nnz >= 8 << 20) == (rows >= 215_093)
+    rng = np.random.default_rng(8)
+    u = rng.standard_normal(p.L).astype(np.float32)
+    got = f64(s.gather_dots(torch.from_numpy(u).cuda()))
+    ref, cond = orc.gather_dots(p.ptr, p.idx, p.val, u)
+    assert np.all(np.abs(got - ref) <= 39 * 2.0 ** -24 * cond)
+    model = rng.random(p.C).astype(np.float32)
+    shared = (0.1 * rng.standard_normal(p.L)).astype(np.float32)
+    s.set_state(torch.from_numpy(model).cuda(), torch.from_numpy(shared).cuda(), 0)
+    P, D = s.objective()
+    Pr, Dr, _ = orc.objectives(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, model.astype(np.float64),
+                               shared.astype(np.float64))
+    scale = max(abs(Pr), abs(Dr))
+    assert abs(P - Pr) <= 1e-9 * scale and abs(D - Dr) <= 1e-9 * scale
+    s.close()
+
+
+@pytest.mark.parametrize("per", [3, 17, 49, 161, 300])
+def test_gather_dots_over_segment_lengths(per):
+    # the group widths 4 to 64, segments from empty to beyond one block of each
+    rng = np.random.default_rng(per)
+    n, L = 1_003, 4_099
+    lens = np.concatenate([[0, 1, 2, 3, 600, 0], rng.integers(max(1, per - 2), per + 3, n - 6)])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    idx = np.concatenate([np.sort(rng.choice(L, k, replace=False)) for k in lens]).astype(np.int32)
+    val = rng.standard_normal(int(ptr[-1])).astype(np.float32)
+    p = synth.Problem("lengths", "ridge_dual", "csr", n, L, ptr, idx, val, rng.standard_normal(n).astype(np.float32), 1e-2, 0)
+    s = scd.solver_for(p)
+    u = rng.standard_normal(L).astype(np.float32)
+    got = f64(s.gather_dots(torch.from_numpy(u).cuda()))
+    ref, cond = orc.gather_dots(ptr, idx, val, u)
+    assert np.all(np.abs(got - ref) <= 600 * 2.0 ** -24 * cond) and got[0] == 0.0
+    model = rng.standard_normal(n).astype(np.float32)
+    s.set_state(torch.from_numpy(model).cuda(), torch.from_numpy(u).cuda(), 0)
+    P, D = s.objective()
+    Pr, Dr, _ = orc.objectives(p.form, n, L, ptr, idx, val, p.y, p.lam, model.astype(np.float64), u.astype(np.float64))
+    scale = max(abs(Pr), abs(Dr))
+    assert abs(P - Pr) <= 1e-9 * scale and abs(D - Dr) <= 1e-9 * scale
+    s.close()
