@@ -229,7 +229,7 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 coordinate do not wait behind other coordinates' atomics on neighbouring
  *                 entries.  It does so when the window does not bind (every coordinate may be in
  *                 flight), and with a binding window when the coordinates in flight hold at least
- *                 4,096 entries (16,384 with a workgroup per coordinate), a segment has at most one entry per 32 of the shared vector on
+ *                 4,096 entries (65,536 with a workgroup per coordinate), a segment has at most one entry per 32 of the shared vector on
  *                 average, and there are at least two stored entries per shared-vector entry;
  *                 0 = it runs on the packed vector.
  *   "queue_chunk" consecutive permutation positions each workgroup of the queued kernel claims

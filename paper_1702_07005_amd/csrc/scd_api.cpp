@@ -283,13 +283,13 @@ int64_t pipe_groups(const scd_solver* h, int64_t window, int64_t groups) {
 // 32 in flight 2.68 and 2.35 ms an epoch, 300 0.65 and 0.34, 632 0.56 and 0.27, 4,000 0.54 and 0.26;
 // columns of 20 entries on 20,000 rows, 281 in flight: 67 and 46 us.  Segments that take a workgroup
 // each are bound by latency until more are in flight: text rows of 370 entries on 166,000 columns, 6 in
-// flight 1.22 and 1.23 ms, 100 in flight 0.256 and 0.248, of 809 entries at about 6 1.09 and 1.13; columns
-// of 1,000 entries on 100,000 rows, 32 in flight 8.8 and 7.6.  Not where a
+// flight 1.22 and 1.23 ms, 100 in flight 0.256 and 0.248, of 809 entries at about 6 1.09 and 1.13, of 2,038
+// at about 10 7.35 and 7.51; columns of 1,000 entries on 100,000 rows, 100 in flight 5.6 and 3.0.  Not where a
 // segment holds neighbouring entries (2,000 x 200 dense: 47 and 107 us at 8 in flight): it would touch
 // one 64-byte segment per entry instead of one per 16.  Nor where the copies in and out (64 bytes per
 // entry, 4.4 us each way at 100,000) could take longer than the gathers they save.
 constexpr double kSpreadMinInFlight = 4096.0;  // entries of the coordinates in flight,
-constexpr double kSpreadMinInFlightBlock = 16384.0;  // with a workgroup per coordinate
+constexpr double kSpreadMinInFlightBlock = 65536.0;  // with a workgroup per coordinate
 bool spread_pays(const scd_solver* h, int64_t window, int64_t groups, int G) {
     if (window >= h->C) return true;
     const double mean = (double)h->nnz / (double)h->C;
