@@ -216,7 +216,9 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *   "lockstep"    1 (default) = where the pipelined kernel would give each coordinate a workgroup, with an
  *                 automatic window of 2 to 16, "group", "fresh_reads" 0, "team" 1, and a shared vector
  *                 whose used entries (those some stored entry points at; at most 1 M entries in all) fit
- *                 the LDS of eight workgroups as fp64 (about 160,000), run the epoch in lockstep rounds of
+ *                 the LDS of eight workgroups as fp64 (about 160,000), and auto_window segments of at most
+ *                 12,288 entries together on average (24,576 up to 416,666 stored entries), run the epoch in
+ *                 lockstep rounds of
  *                 auto_window coordinates: the eight workgroups each hold an index range of the shared
  *                 vector, every coordinate of a round is a wave of each, and the waves exchange partial
  *                 inner products.  scd_info_t still names kernel 4, with window = auto_window.  It needs a

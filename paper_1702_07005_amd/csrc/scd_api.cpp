@@ -377,11 +377,24 @@ int team_members(const scd_solver* h, int64_t* teams) {
 // The lockstep kernel applies: an automatic window of 2 to 16 coordinates on segments long enough for a
 // workgroup each (the pipelined kernel would give them one), and a shared vector small enough that its used
 // entries may fit.  Options that ask for another schedule turn it off.
+//
+// Its eight CUs take all the entries of a round, so it pays while those are few, or while the grouped copy
+// stays in one XCD's 4 MB of L2.  Pipelined against lockstep, entries in flight (W x mean length), ms an epoch:
+// text rows of 300 to 900, 1,800 to 10,800 in flight, 8 to 27 MB of copy: 0.57-2.64 and 0.37-1.75 (1.4 to 2.3
+// times faster, all of 14); dense 2,000 x 200, 18,000 to 22,000 in flight, 2.4 MB: 0.055 and 0.046; 2,000 x 300,
+// 22,000 in flight, 3.6 MB: 0.079 and 0.083; 2,500 x 375, 35,000 in flight, 5.6 MB: 0.072 and 0.092;
+// 4,000 x 600, 64,000 in flight: 0.106 and 0.171.
 constexpr int64_t kLockMaxShared = int64_t(1) << 20;
+constexpr double kLockMaxInFlight = 12288.0;
+constexpr double kLockMaxInFlightL2 = 24576.0;  // with a copy of at most kLockMaxL2Bytes
+constexpr int64_t kLockMaxL2Bytes = 2500000;
 bool lock_wanted(const scd_solver* h) {
-    return h->lockstep && h->window == 0 && h->group == 0 && !h->fresh && h->pipeline && h->team == 1 &&
-           h->auto_window >= 2 && h->auto_window <= kLockMaxWindow && h->auto_window < h->C && h->L <= kLockMaxShared &&
-           auto_group(h) == kBlockThreads && h->cus >= (int)kTeamXcds * kLockMaxMembers;
+    if (!h->lockstep || h->window != 0 || h->group != 0 || h->fresh || !h->pipeline || h->team != 1 || h->auto_window < 2 ||
+        h->auto_window > kLockMaxWindow || h->auto_window >= h->C || h->L > kLockMaxShared ||
+        auto_group(h) != kBlockThreads || h->cus < (int)kTeamXcds * kLockMaxMembers)
+        return false;
+    const double in_flight = (double)h->auto_window * ((double)h->nnz / (double)h->C);
+    return in_flight <= (h->nnz * 6 <= kLockMaxL2Bytes ? kLockMaxInFlightL2 : kLockMaxInFlight);
 }
 
 uint32_t split_part_len(const scd_solver* h) { return h->split_part ? (uint32_t)h->split_part : kSplitMaxPart; }

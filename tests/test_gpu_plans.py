@@ -289,7 +289,7 @@ def _lockstep(s):
 LOCKSTEP = {
     # (lengths, L, form): a member's part is about an eighth of a segment; 256 entries stay in registers
     "dense": lambda: synth.make("dense_ridge", n_rows=1_999, n_cols=203),
-    "dense_long": lambda: synth.make("dense_ridge", n_rows=4_001, n_cols=151),  # parts of 500
+    "dense_long": lambda: synth.make("dense_ridge", n_rows=3_001, n_cols=101),  # parts of 376
     "text": lambda: synth.make("text_svm", n_rows=3_500, n_cols=166_000, row_nnz=370),
     "svm_ragged": lambda: _rows(np.concatenate([[0, 1, 2, 63, 64, 65, 0], np.full(200, 511), [2_048, 2_056, 3_000]]), 6_007,
                                 "svm_dual", 1 / 210, 1),
@@ -379,6 +379,20 @@ def test_lockstep_selection():
         if i["auto_window"] >= 5:  # below, four fifths of the window is the window less one at most
             assert _lockstep(s) == (used < 163_000)
         s.epochs(0, 2)
+        s.close()
+
+
+def test_lockstep_limits_on_the_entries_in_flight():
+    # 24,576 entries in flight while the copy takes at most 2.5 MB (6 bytes an entry), else 12,288
+    for rows, cols in ((2_000, 208), (2_000, 209), (2_500, 375), (6_000, 100)):
+        p = synth.make("dense_ridge", n_rows=rows, n_cols=cols)
+        s = scd.solver_for(p)
+        i = s.info()
+        in_flight = i["auto_window"] * rows
+        want = 2 <= i["auto_window"] <= 16 and in_flight <= (24_576 if p.nnz * 6 <= 2_500_000 else 12_288)
+        print(f"{rows} x {cols}: auto {i['auto_window']} in flight {in_flight} window {i['window']}", flush=True)
+        assert i["kernel"] == "pipelined" and i["window"] == (i["auto_window"] if want else i["auto_window"] * 4 // 5)
+        follow_oracle(p, s, 3)
         s.close()
 
 
