@@ -910,6 +910,8 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
             }
     }
     const size_t nnz = (size_t)h->nnz;
+    std::vector<uint64_t> slots(kLockSlotWords + 1, 0);
+    slots[kLockSlotWords] = 1;  // the first launch's first tag
     int32_t *grouped = nullptr, *d_ids = nullptr;
     uint16_t *d_cell = nullptr, *d_idx = nullptr;
     uint32_t *d_bound = nullptr, *d_off = nullptr;
@@ -920,8 +922,8 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
         (e = hipMalloc(&d_ids, sizeof(int32_t) * ids.size())) == hipSuccess &&
         (e = hipMalloc(&d_cell, sizeof(uint16_t) * (size_t)h->L)) == hipSuccess &&
         (e = hipMalloc(&d_bound, sizeof bound)) == hipSuccess &&
-        (e = hipMalloc(&t.slots, sizeof(uint64_t) * kLockSlotWords)) == hipSuccess &&
-        (e = hipMemsetAsync(t.slots, 0, sizeof(uint64_t) * kLockSlotWords, s)) == hipSuccess &&
+        (e = hipMalloc(&t.slots, sizeof(uint64_t) * (kLockSlotWords + 1))) == hipSuccess &&
+        (e = hipMemcpyAsync(t.slots, slots.data(), sizeof(uint64_t) * slots.size(), hipMemcpyHostToDevice, s)) == hipSuccess &&
         (e = hipMemcpyAsync(d_bound, bound, sizeof bound, hipMemcpyHostToDevice, s)) == hipSuccess &&
         (e = hipMemcpyAsync(d_ids, ids.data(), sizeof(int32_t) * ids.size(), hipMemcpyHostToDevice, s)) == hipSuccess &&
         (e = hipMemcpyAsync(d_cell, cell_of.data(), sizeof(uint16_t) * (size_t)h->L, hipMemcpyHostToDevice, s)) == hipSuccess &&
@@ -935,7 +937,6 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     t.val = d_val;
     t.off = d_off;
     t.ids = d_ids;
-    t.tag0 = 1;
     h->lock_args = t;
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -1451,13 +1452,7 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
             la.xcd = h->lock_xcd;
             la.spin_limit = h->hot_wait_limit > 0 ? (uint32_t)h->hot_wait_limit : kHotSpinLimit;
             la.err = h->hot_err;
-            const uint32_t rounds = (uint32_t)((h->C + n_groups - 1) / n_groups);
-            if (la.tag0 > 0xFFFFFFFFu - rounds - 1u) {  // tags start over
-                HIP_TRY(launch_fill_zero(la.slots, kLockSlotWords, s));
-                la.tag0 = h->lock_args.tag0 = 1;
-            }
             HIP_TRY(launch_epoch_lock(h->form, h->wide != 0, la, s));
-            h->lock_args.tag0 += rounds + 1;
         } else if (lp.kind == PLAN_TEAM) {
             TeamArgs ta{};
             ta.e = a;

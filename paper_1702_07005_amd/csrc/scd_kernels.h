@@ -334,9 +334,9 @@ struct LockArgs {
     const int32_t* ids;    // [cell0[K]]: shared-vector index of each cell (indices no entry uses have none)
     uint32_t cell0[kLockMaxMembers + 1];  // first cell of each member
     uint32_t max_cells;    // most cells of a member
-    uint64_t* slots;       // [kLockSlotWords]
+    uint64_t* slots;       // [kLockSlotWords + 1]: zero at first; the last word is the next launch's first tag,
+                           // 1 at first
     uint32_t K, W, xcd;
-    uint32_t tag0;         // tag of the launch's first round (tags grow by one per round)
     uint32_t spin_limit;   // bounded waits: polls before a wave gives up and sets *err
     int* err;
 };

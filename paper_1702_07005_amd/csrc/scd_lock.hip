@@ -26,6 +26,10 @@
 // sets *err and its round's flag in LDS (one of two, so that no wave of the round reads it early), and its
 // workgroup leaves in the next round, as do the others in turn.
 //
+// Tags grow by one per round and on from launch to launch: the first one is kept in device memory behind the
+// slots, read by every member when it starts and advanced by member 0 when it ends.  By then round 0 has been
+// exchanged, so every member has read it; and a launch replayed from a captured graph gets new tags too.
+//
 // Placement: workgroup b runs on XCD b mod 8; the members are those of one XCD (correct on any, slower
 // across).  K is at most 8, so that the four kernels a process runs at once by default all fit one XCD's 32
 // CUs, one member each, and none waits for members that cannot start; handles use the XCDs in turn.
@@ -108,8 +112,11 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
     uint32_t ci[kLockSlices];
     float cv[kLockSlices];
     lock_load(t, cur, lane, ci, cv);
+    uint64_t* const base_tag = t.slots + kLockSlotWords;
+    const uint32_t tag0 = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)__hip_atomic_load(base_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the loop's waits need not allow for these loads
-    uint32_t tag = t.tag0;
+    uint32_t tag = tag0;
     for (uint32_t r = 0; r < rounds; ++r, ++tag) {
         const uint32_t j = r * W + wave;
         // Of the last round: the same for every wave.
@@ -177,6 +184,8 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     }
     __syncthreads();
+    if (k == 0 && threadIdx.x == 0)
+        __hip_atomic_store(base_tag, (uint64_t)(uint32_t)(tag0 + rounds + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (uint32_t i = threadIdx.x; i < n_cells; i += blockDim.x) u[t.ids[cell0 + i]] = (U)cells[i];
 }
 

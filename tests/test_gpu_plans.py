@@ -414,6 +414,38 @@ def test_lockstep_handles_side_by_side():
         s.close()
 
 
+def test_lockstep_replayed_from_a_graph():
+    # A captured call of two epochs repeats their visiting orders at every replay.  Replays between eager
+    # epochs and state reads follow a solver that runs the same orders eagerly: the steps are the same, and
+    # only the order of fp64 adds within a round differs.
+    p = LOCKSTEP["text"]()
+    s, t = scd.solver_for(p), scd.solver_for(p)
+    assert _lockstep(s)
+    zeros = torch.zeros(p.C, device="cuda"), torch.zeros(p.L, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    s.set_state(*zeros, 0)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        s.epochs(0, 2)
+    for replay in range(4):
+        graph.replay()
+        t.set_state(*(zeros if replay == 0 else t.get_state()[:2]), epoch=0)
+        t.epochs(0, 2)
+        if replay == 1:  # an eager epoch between the replays
+            for x in (s, t):
+                x.set_state(epoch=7)
+                x.epochs(0, 1)
+        torch.cuda.synchronize()
+        a, b = s.get_state(), t.get_state()
+        assert s.duality_gap() > 0.0
+        for x, y in zip(a[:2], b[:2]):
+            assert float((x - y).abs().max()) <= 1e-4 * float(y.abs().max()), replay
+    for x in (s, t):
+        x.close()
+
+
 def test_lockstep_wait_limit():
     # bounded waits with a limit of one poll: either every exchange completes in time (valid state) or
     # the timeout is reported at the next synchronising call and a written state replaces the invalid one
