@@ -836,13 +836,8 @@ int team_if_needed(scd_solver* h, hipStream_t s) {
 }
 
 void free_lock_tables(scd_solver* h) {
-    LockArgs& t = h->lock_args;
-    (void)hipFree(const_cast<uint16_t*>(t.idx));
-    (void)hipFree(const_cast<float*>(t.val));
-    (void)hipFree(const_cast<uint32_t*>(t.off));
-    (void)hipFree(const_cast<int32_t*>(t.ids));
-    (void)hipFree(t.slots);
-    t = LockArgs{};
+    (void)hipFree(h->lock_args.slots);  // the tables' one allocation
+    h->lock_args = LockArgs{};
 }
 
 // Members' index ranges from the hits: the used indices cut into K runs of about equal entry count, or,
@@ -912,37 +907,53 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     const size_t nnz = (size_t)h->nnz;
     std::vector<uint64_t> slots(kLockSlotWords + 1, 0);
     slots[kLockSlotWords] = 1;  // the first launch's first tag
-    int32_t *grouped = nullptr, *d_ids = nullptr;
-    uint16_t *d_cell = nullptr, *d_idx = nullptr;
-    uint32_t *d_bound = nullptr, *d_off = nullptr;
-    float* d_val = nullptr;
-    if ((e = hipMalloc(&grouped, sizeof(int32_t) * nnz)) == hipSuccess && (e = hipMalloc(&d_val, sizeof(float) * nnz)) == hipSuccess &&
-        (e = hipMalloc(&d_idx, sizeof(uint16_t) * nnz)) == hipSuccess &&
-        (e = hipMalloc(&d_off, sizeof(uint32_t) * (size_t)h->C * (t.K + 1))) == hipSuccess &&
-        (e = hipMalloc(&d_ids, sizeof(int32_t) * ids.size())) == hipSuccess &&
-        (e = hipMalloc(&d_cell, sizeof(uint16_t) * (size_t)h->L)) == hipSuccess &&
-        (e = hipMalloc(&d_bound, sizeof bound)) == hipSuccess &&
-        (e = hipMalloc(&t.slots, sizeof(uint64_t) * (kLockSlotWords + 1))) == hipSuccess &&
-        (e = hipMemcpyAsync(t.slots, slots.data(), sizeof(uint64_t) * slots.size(), hipMemcpyHostToDevice, s)) == hipSuccess &&
-        (e = hipMemcpyAsync(d_bound, bound, sizeof bound, hipMemcpyHostToDevice, s)) == hipSuccess &&
-        (e = hipMemcpyAsync(d_ids, ids.data(), sizeof(int32_t) * ids.size(), hipMemcpyHostToDevice, s)) == hipSuccess &&
-        (e = hipMemcpyAsync(d_cell, cell_of.data(), sizeof(uint16_t) * (size_t)h->L, hipMemcpyHostToDevice, s)) == hipSuccess &&
-        (e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, d_bound, (int)t.K, grouped, d_val, d_off, s)) == hipSuccess &&
-        (e = launch_lock_cells(grouped, h->nnz, d_cell, d_idx, s)) == hipSuccess)
-        e = hipStreamSynchronize(s);
-    (void)hipFree(grouped);
-    (void)hipFree(d_cell);
-    (void)hipFree(d_bound);
-    t.idx = d_idx;
-    t.val = d_val;
-    t.off = d_off;
-    t.ids = d_ids;
-    h->lock_args = t;
+    // One allocation for the tables (t.slots, at its start, owns it) and one for the scratch.
+    auto place = [](size_t& at, size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) / 256 * 256;
+        return here;
+    };
+    size_t size = 0, scratch_size = 0;
+    const size_t o_slots = place(size, sizeof(uint64_t) * slots.size()), o_ids = place(size, sizeof(int32_t) * ids.size()),
+                 o_off = place(size, sizeof(uint32_t) * (size_t)h->C * (t.K + 1)), o_val = place(size, sizeof(float) * nnz),
+                 o_idx = place(size, sizeof(uint16_t) * nnz);
+    const size_t o_grouped = place(scratch_size, sizeof(int32_t) * nnz),
+                 o_cell = place(scratch_size, sizeof(uint16_t) * (size_t)h->L), o_bound = place(scratch_size, sizeof bound);
+    char *base = nullptr, *scratch = nullptr;
+    e = hipMalloc(&base, size);
+    if (e == hipSuccess) e = hipMalloc(&scratch, scratch_size);
+    if (e == hipSuccess) {
+        t.slots = reinterpret_cast<uint64_t*>(base + o_slots);
+        int32_t* const d_ids = reinterpret_cast<int32_t*>(base + o_ids);
+        uint32_t* const d_off = reinterpret_cast<uint32_t*>(base + o_off);
+        float* const d_val = reinterpret_cast<float*>(base + o_val);
+        uint16_t* const d_idx = reinterpret_cast<uint16_t*>(base + o_idx);
+        int32_t* const grouped = reinterpret_cast<int32_t*>(scratch + o_grouped);
+        uint16_t* const d_cell = reinterpret_cast<uint16_t*>(scratch + o_cell);
+        uint32_t* const d_bound = reinterpret_cast<uint32_t*>(scratch + o_bound);
+        t.ids = d_ids;
+        t.off = d_off;
+        t.val = d_val;
+        t.idx = d_idx;
+        auto up = [&](void* to, const void* from, size_t bytes) {
+            if (e == hipSuccess) e = hipMemcpyAsync(to, from, bytes, hipMemcpyHostToDevice, s);
+        };
+        up(t.slots, slots.data(), sizeof(uint64_t) * slots.size());
+        up(d_bound, bound, sizeof bound);
+        up(d_ids, ids.data(), sizeof(int32_t) * ids.size());
+        up(d_cell, cell_of.data(), sizeof(uint16_t) * (size_t)h->L);
+        if (e == hipSuccess)
+            e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, d_bound, (int)t.K, grouped, d_val, d_off, s);
+        if (e == hipSuccess) e = launch_lock_cells(grouped, h->nnz, d_cell, d_idx, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+    (void)hipFree(scratch);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_lock_tables(h);
+        (void)hipFree(base);
         return e == hipErrorOutOfMemory ? SCD_OK : fail(SCD_ERR_HIP, "lockstep tables: %s", hipGetErrorString(e));
     }
+    h->lock_args = t;
     static std::atomic<uint32_t> made{0};
     h->lock_xcd = made.fetch_add(1, std::memory_order_relaxed) % kTeamXcds;
     h->lock_state = 1;
@@ -1041,7 +1052,7 @@ int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* di
     uint16_t* slot_of = nullptr;
     int32_t* hot_ids = nullptr;
     const unsigned fit = (unsigned)std::min<size_t>(kProbeSlots, h->max_lds / (sizeof(float) * (kProbeRow + 1)));
-    if (h->hits && h->max_hits >= kProbeMinHits && fit > 0) {
+    if (h->hits && h->max_hits >= kProbeMinHits && h->nnz >= kProbeMinEntries && fit > 0) {
         unsigned T = 0;
         unsigned long long cnt = 0, sum = 0;
         if (int r = hits_threshold(h, h->hits, fit, &T, s)) return r;

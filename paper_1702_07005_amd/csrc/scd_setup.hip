@@ -60,6 +60,11 @@ __global__ __launch_bounds__(HOT ? kHotPassThreads : 256) void k_gather_dots(
     for (uint32_t c = (blockIdx.x * blockDim.x + threadIdx.x) / G; c < C; c += ngroups) {
         const int64_t s0 = ptr[c], s1 = ptr[c + 1];
         float acc = 0.0f;
+        if constexpr (!HOT && (G <= 8 || G == 64)) {
+            // One entry at a time where blocks do not pay: short segments (3.3 M click entries, all in cache:
+            // 13.8 us, 14.6 in blocks) and whole waves (9,000 text rows of 1,000: 38.5 us, 41.8 in blocks).
+            for (int64_t k = s0 + lane; k < s1; k += G) acc = fmaf(val[k], u[idx[k]], acc);
+        } else
         for (int64_t b = s0; b < s1; b += (int64_t)G * R) {
             int ix[R];
             float vx[R];
