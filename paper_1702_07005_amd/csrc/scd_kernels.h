@@ -416,7 +416,7 @@ hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, c
 constexpr int kProbeRow = 8;
 constexpr unsigned kProbeSlots = 4000;
 constexpr unsigned kProbeMinHits = 2048;
-constexpr int64_t kProbeMinEntries = 3 << 19;  // choosing the slots costs 0.4 ms: not for fewer stored entries
+constexpr int64_t kProbeMinEntries = 3 << 19;  // choosing slots costs small creates more than it saves
 struct ProbeArgs {
     const int64_t* ptr;
     const int32_t* idx;
