@@ -1609,7 +1609,8 @@ int scd_set_state(scd_handle_t h, const float* model, const float* shared, int64
     if (epoch < 0) return fail(SCD_ERR_INVALID, "epoch must be >= 0");
     if (int r = set_device(h)) return r;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(hipMemsetAsync(h->hot_err, 0, sizeof(int), s));  // a written state replaces an invalid one
+    // A written state replaces an invalid one, whose epoch may have left partials under the tags of the next.
+    HIP_TRY(launch_reset_waits(h->hot_err, h->lock_args.slots, s));
     h->adapt_fresh = 1;  // the moving fraction of the previous epochs says nothing about this state
     if (model) HIP_TRY(hipMemcpyAsync(h->model, model, sizeof(float) * (size_t)h->C, hipMemcpyDeviceToDevice, s));
     if (shared) {

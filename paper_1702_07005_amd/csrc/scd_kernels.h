@@ -446,6 +446,8 @@ hipError_t launch_sum_partials(const double* partials, int nparts, int width, do
 hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, int cus, double* partials, double* sums,
                             hipStream_t s);
 hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s);
+// *err = 0 and, with slots, the lockstep exchange as it is at first (LockArgs::slots).
+hipError_t launch_reset_waits(int* err, uint64_t* slots, hipStream_t s);
 // Sets the calling thread's message returned by scd_last_error.
 void set_last_error(const char* msg);
 

@@ -27,8 +27,12 @@
 // workgroup leaves in the next round, as do the others in turn.
 //
 // Tags grow by one per round and on from launch to launch: the first one is kept in device memory behind the
-// slots, read by every member when it starts and advanced by member 0 when it ends.  By then round 0 has been
-// exchanged, so every member has read it; and a launch replayed from a captured graph gets new tags too.
+// slots, read by every member when it starts and advanced by member 0 when it ends, so a launch replayed from a
+// captured graph gets new tags too.  In a launch whose waits all end, round 0 has been exchanged by then and every
+// member has read it.  Member 0 may also give up in round 0 and advance it before another member starts, which
+// then reads the next launch's first tag and publishes under it.  Such a launch has set *err, and the state is
+// invalid until scd_set_state, which clears the slots and starts the tags again (launch_reset_waits, on the same
+// stream, so after that launch): no later launch sees those partials.
 //
 // Placement: workgroup b runs on XCD b mod 8; the members are those of one XCD (correct on any, slower
 // across).  K is at most 8, so that the four kernels a process runs at once by default all fit one XCD's 32

@@ -459,6 +459,17 @@ hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s) {
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_reset_waits(int* __restrict__ err, uint64_t* __restrict__ slots) {
+    if (threadIdx.x == 0) *err = 0;
+    if (slots)
+        for (int i = threadIdx.x; i <= kLockSlotWords; i += 256) slots[i] = i == kLockSlotWords ? 1ull : 0ull;
+}
+
+hipError_t launch_reset_waits(int* err, uint64_t* slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_reset_waits, dim3(1), dim3(256), 0, s, err, slots);
+    return hipGetLastError();
+}
+
 // sums[0..2] = coordinate sums, sums[3..4] = vector sums.
 hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, int cus, double* partials, double* sums,
                             hipStream_t s) {

@@ -1,4 +1,4 @@
-"""CPU models of the two cross-workgroup protocols of the epoch kernels, run under random
+"""CPU models of the cross-workgroup protocols of the epoch kernels, run under random
 interleavings of their waves (host only; no GPU).
 
 * The staged hot-set epoch: stager waves (other CUs) stage batches into a ring of R records and
@@ -12,6 +12,10 @@ interleavings of their waves (host only; no GPU).
   unit waits for the GATHER slots of its coordinate.  Checked: no deadlock for any number of
   workgroups and chunk sizes, and every part of a coordinate takes the same step (the sum of all its
   GATHER partials).
+* The lockstep epoch: members exchange tagged partials through two sets of slots, and the first tag of
+  a launch comes from a word that member 0 advances.  Checked: a launch without time-outs takes only its
+  own partials of the same round, whatever order its members start in, also after a launch that timed out
+  and whose state was then written again.
 """
 import random
 
@@ -294,3 +298,95 @@ def test_split_model_detects_out_of_order_units():
     # itself: the model must report that deadlock.
     lens = [300] * 8
     assert not run_split(lens, 64, 1, 16, 0, in_order=False)
+
+
+# ---------------------------------------------------------------------------------------- lockstep
+
+class Lockstep:
+    """The exchange of K members.  A slot holds (tag, launch, round): who may read it is checked, not
+    what is in it."""
+
+    def __init__(self, K, seed):
+        self.K, self.rng = K, random.Random(seed)
+        self.launches = 0
+        self.reset()
+
+    def reset(self):  # as made, and by every scd_set_state
+        self.slots = [[(0, None, None)] * self.K for _ in range(2)]
+        self.base = 1
+
+    def launch(self, rounds, late=(), patience=None):
+        """Runs one launch; members in `late` start when nobody else can go on.  With `patience`, a
+        member gives up after so many polls.  Returns (timed out, a partial of another round taken)."""
+        self.launches += 1
+        err = stale = False
+        M = [dict(ph="start", tag0=None, tag=None, r=0, spins=0, left=False) for _ in range(self.K)]
+
+        def step(k):
+            nonlocal err, stale
+            m = M[k]
+            if m["ph"] == "start":
+                m["tag0"] = m["tag"] = self.base
+                m["ph"] = "round"
+                return True
+            if m["ph"] == "round":
+                if m["r"] == rounds or m["left"]:
+                    m["ph"] = "done"
+                    if k == 0:
+                        self.base = m["tag0"] + rounds + 1
+                    return True
+                self.slots[m["tag"] & 1][k] = (m["tag"], self.launches, m["r"])
+                m["ph"], m["spins"] = "poll", 0
+                return True
+            if m["ph"] == "poll":
+                seen = self.slots[m["tag"] & 1]
+                if all(v[0] == m["tag"] for v in seen):
+                    stale |= any(v[1:] != (self.launches, m["r"]) for v in seen)
+                elif patience is not None and m["spins"] >= patience:
+                    err = m["left"] = True
+                else:
+                    m["spins"] += 1
+                    return patience is not None
+                m["r"] += 1
+                m["tag"] += 1
+                m["ph"] = "round"
+                return True
+            return False
+
+        while True:
+            early = [k for k in range(self.K) if k not in late]
+            self.rng.shuffle(early)
+            some = early[:self.rng.randint(1, len(early))]  # uneven speeds
+            if any([step(k) for k in some]) or any([step(k) for k in early]):
+                continue
+            if not any([step(k) for k in late]):
+                break
+        assert all(m["ph"] == "done" for m in M), "deadlock"
+        return err, stale
+
+
+def lockstep_after_a_time_out(reset, K, seed):
+    m = Lockstep(K, seed)
+    assert m.launch(5) == (False, False)
+    err, _ = m.launch(4, late=(K - 1,), patience=3)
+    assert err  # the late member was missed
+    if reset:
+        m.reset()
+    out = [m.launch(n) for n in (3, 1, 4)]
+    assert not any(e for e, _ in out)
+    return any(s for _, s in out)
+
+
+@pytest.mark.parametrize("K", [2, 3, 8])
+def test_lockstep_takes_no_partial_of_a_timed_out_launch(K):
+    for seed in range(30):
+        m = Lockstep(K, seed)
+        for n in (1, 2, 5, 1, 1):
+            assert m.launch(n) == (False, False)
+            assert m.launch(n, late=(seed % K,)) == (False, False)
+        assert not lockstep_after_a_time_out(True, K, seed)
+
+
+def test_lockstep_model_detects_slots_kept_after_a_time_out():
+    # Without the reset the late member's partial carries the first tag of the next launch.
+    assert any(lockstep_after_a_time_out(False, 8, seed) for seed in range(30))
