@@ -574,12 +574,26 @@ int need_hits(scd_solver* h, unsigned** hits, bool* owned, hipStream_t s) {
     return fail(SCD_ERR_HIP, "count hits: %s", hipGetErrorString(e));
 }
 
+// Device scratch of the two passes over hits below.  scd_create lends them the reduction buffers of the
+// objectives; a later call has no stream of the caller's, and a gap evaluation may still be running there in
+// those buffers, so it allocates its own.
+struct HitScratch {
+    unsigned* bins = nullptr;             // [kHitBins]
+    unsigned long long* two = nullptr;    // [2]
+};
+constexpr size_t kHitScratchBytes = sizeof(unsigned) * kHitBins + 2 * sizeof(unsigned long long);
+
+HitScratch hit_scratch(void* buf) {
+    HitScratch w;
+    w.two = static_cast<unsigned long long*>(buf);
+    w.bins = reinterpret_cast<unsigned*>(w.two + 2);
+    return w;
+}
+
 // The smallest T in [1, max_hits + 1] with at most `cap` entries of at least T hits (synchronises).  Each
-// histogram pass narrows T's interval kHitBins times, so two or three passes over hits find it; bins
-// live in h->partials.
-int hits_threshold(scd_solver* h, const unsigned* hits, unsigned cap, unsigned* T, hipStream_t s) {
-    static_assert(sizeof(unsigned) * kHitBins <= sizeof(double) * kObjBlocksMax * 5, "bins fit the partials");
-    unsigned* bins = reinterpret_cast<unsigned*>(h->partials);
+// histogram pass narrows T's interval kHitBins times, so two or three passes over hits find it.
+int hits_threshold(const scd_solver* h, const unsigned* hits, unsigned cap, const HitScratch& w, unsigned* T, hipStream_t s) {
+    unsigned* bins = w.bins;
     std::vector<unsigned> n(kHitBins);
     uint64_t lo = 1, hi = (uint64_t)h->max_hits + 1;  // T in [lo, hi]; `above` entries have at least hi hits
     uint64_t above = 0;
@@ -607,11 +621,11 @@ int hits_threshold(scd_solver* h, const unsigned* hits, unsigned cap, unsigned* 
     return SCD_OK;
 }
 
-// Entries with at least T hits, and the sum of their hits (synchronises; the two counts in h->sums).
-int hot_count(scd_solver* h, const unsigned* hits, unsigned T, hipStream_t s, unsigned long long* count,
-              unsigned long long* sum) {
+// Entries with at least T hits, and the sum of their hits (synchronises).
+int hot_count(const scd_solver* h, const unsigned* hits, unsigned T, const HitScratch& w, hipStream_t s,
+              unsigned long long* count, unsigned long long* sum) {
     unsigned long long host2[2] = {0, 0};
-    unsigned long long* dev2 = reinterpret_cast<unsigned long long*>(h->sums);
+    unsigned long long* dev2 = w.two;
     HIP_TRY(hipMemsetAsync(dev2, 0, sizeof host2, s));
     HIP_TRY(launch_hot_count_ge(hits, h->L, T, dev2, s));
     HIP_TRY(hipMemcpyAsync(host2, dev2, sizeof host2, hipMemcpyDeviceToHost, s));
@@ -678,8 +692,12 @@ int build_hot_tables(scd_solver* h, double min_cover, hipStream_t s) {
     // Smallest T in [1, max_hits + 1] with count(hits >= T) <= cap (count at max_hits + 1 is 0).
     unsigned T = 1;
     unsigned long long cnt = 0, sum = 0;
-    if (rc == SCD_OK) rc = hits_threshold(h, hits, cap, &T, s);
-    if (rc == SCD_OK) rc = hot_count(h, hits, T, s, &cnt, &sum);
+    void* scratch = nullptr;
+    if (rc == SCD_OK && own_hits) hip(hipMalloc(&scratch, kHitScratchBytes), "hipMalloc(hit scratch)");
+    const HitScratch w = hit_scratch(own_hits ? scratch : h->partials);
+    if (rc == SCD_OK) rc = hits_threshold(h, hits, cap, w, &T, s);
+    if (rc == SCD_OK) rc = hot_count(h, hits, T, w, s, &cnt, &sum);
+    (void)hipFree(scratch);
     if (rc == SCD_OK && (double)sum < min_cover * (double)h->nnz) {
         h->hot_built = 0;  // a narrower window may still want it
         cnt = 0;
@@ -1055,9 +1073,11 @@ int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* di
     if (h->hits && h->max_hits >= kProbeMinHits && h->nnz >= kProbeMinEntries && fit > 0) {
         unsigned T = 0;
         unsigned long long cnt = 0, sum = 0;
-        if (int r = hits_threshold(h, h->hits, fit, &T, s)) return r;
+        static_assert(kHitScratchBytes <= sizeof(double) * kObjBlocksMax * 5, "the scratch fits the partials");
+        const HitScratch w = hit_scratch(h->partials);
+        if (int r = hits_threshold(h, h->hits, fit, w, &T, s)) return r;
         T = std::max(T, kProbeMinHits);
-        if (int r = hot_count(h, h->hits, T, s, &cnt, &sum)) return r;
+        if (int r = hot_count(h, h->hits, T, w, s, &cnt, &sum)) return r;
         if (cnt > 0) {
             if (int r = assign_slots(h, h->hits, T, cnt, &slot_of, &hot_ids, s)) {
                 if (r != SCD_ERR_OOM) return r;

@@ -211,6 +211,33 @@ def test_wide_automatic_window_cut_for_the_hot_set(wide):
     s.close()
 
 
+def test_hot_set_built_beside_a_running_gap_evaluation():
+    # set_option("window", 8) counts hits on a stream of its own while a gap evaluation is still queued
+    # behind epochs on the caller's: neither may touch the other's scratch.
+    p = synth.make("sparse_ridge", n_rows=60_000, n_cols=30_000, density=5e-4, lam=1e-2)
+    s, t = scd.solver_for(p), scd.solver_for(p)
+    assert s.info()["hot_entries"] == 0 and s.info()["kernel"] == "pipelined"
+    t.set_option("window", 8)
+    want = t.info()["hot_entries"]
+    assert want > 0
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    s.epochs(0, 400, stream=stream)
+    for slot in range(4):
+        s.duality_gap_async(slot, stream=stream)
+        s.epochs(0, 1, stream=stream)
+    s.set_option("window", 8)
+    got = [s.duality_gap_wait(slot) for slot in range(4)]
+    torch.cuda.synchronize()
+    # at the minimiser: the four evaluations differ by fp32 rounding of the state only
+    P, D = s.objective()
+    assert s.info()["hot_entries"] == want and s.info()["kernel"] == "hot_lds"
+    for gap, Ps, Ds in got:
+        assert abs(Ps - P) <= 1e-5 * abs(P) and abs(Ds - D) <= 1e-5 * abs(D) and abs(gap) <= 1e-5 * abs(P)
+    s.close()
+    t.close()
+
+
 # ------------------------------------------------------------- passes over a frozen vector
 
 @pytest.mark.parametrize("wide", [0, 1])
