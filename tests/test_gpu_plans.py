@@ -267,6 +267,41 @@ def test_frozen_passes_with_the_hot_set_in_lds(form, rows, wide):
     s.close()
 
 
+@pytest.mark.parametrize("kind", ["hot", 3, 17, 49, 161, 300])
+def test_gather_dots_of_infinities(kind):
+    # u with infinities and NaN: a segment sees those of its own entries and no others, also where lanes
+    # past its end stand in with its first entry.  Each reference sum is the one of IEEE arithmetic.
+    rng = np.random.default_rng(12)
+    if kind == "hot":
+        p = synth.make("click_svm", n_rows=215_093, n_cols=300_007)
+        s = scd.solver_for(p)
+        s.set_option("window", 8)
+        assert s.info()["hot_entries"] > 0
+    else:
+        n, L = 1_003, 4_099
+        lens = np.concatenate([[0, 1, 2], rng.integers(max(1, kind - 2), kind + 3, n - 3)])
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        idx = np.concatenate([np.sort(rng.choice(L, k, replace=False)) for k in lens]).astype(np.int32)
+        val = rng.standard_normal(int(ptr[-1])).astype(np.float32)
+        p = synth.Problem("lengths", "ridge_dual", "csr", n, L, ptr, idx, val, np.ones(n, dtype=np.float32), 1e-2, 0)
+        s = scd.solver_for(p)
+    u = rng.standard_normal(p.L).astype(np.float32)
+    first = p.idx[p.ptr[:-1][np.diff(p.ptr) > 0]]  # what the stand-in lanes would read
+    u[rng.choice(first, 8)] = np.inf
+    u[rng.choice(first, 8)] = -np.inf
+    u[rng.integers(0, p.L, 2)] = np.nan
+    got = f64(s.gather_dots(torch.from_numpy(u).cuda()))
+    seg = np.repeat(np.arange(p.C), np.diff(p.ptr))
+    with np.errstate(invalid="ignore"):
+        ref = np.bincount(seg, p.val.astype(np.float64) * u[p.idx], p.C)
+    bad = ~np.isfinite(ref)
+    print(f"{kind}: {np.isinf(ref).sum()} infinite, {np.isnan(ref).sum()} NaN of {p.C}", flush=True)
+    assert np.isinf(ref).any() and np.array_equal(got[bad], ref[bad], equal_nan=True)
+    cond = np.bincount(seg, np.abs(p.val.astype(np.float64) * np.where(np.isfinite(u), u, 0.0)[p.idx]), p.C)
+    assert np.all(np.abs(got[~bad] - ref[~bad]) <= 600 * 2.0 ** -24 * cond[~bad])
+    s.close()
+
+
 @pytest.mark.parametrize("per", [3, 17, 49, 161, 300])
 def test_gather_dots_over_segment_lengths(per):
     # the group widths 4 to 64, segments from empty to beyond one block of each
