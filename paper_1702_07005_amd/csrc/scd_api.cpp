@@ -908,7 +908,7 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "lockstep hits: %s", hipGetErrorString(e));
     LockArgs t{};
     t.K = (uint32_t)kLockMaxMembers;
-    const uint32_t cap = (uint32_t)std::min<size_t>(65535, (h->max_lds - 64) / sizeof(double));
+    const uint32_t cap = (uint32_t)std::min<size_t>(65535, (h->max_lds - 64) / sizeof(double) - 1);
     uint32_t bound[kLockMaxMembers + 1];
     if (!lock_ranges(hh, h->nnz, t.K, cap, bound, t.cell0)) return SCD_OK;
     std::vector<int32_t> ids;

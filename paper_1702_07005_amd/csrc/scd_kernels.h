@@ -340,7 +340,7 @@ struct LockArgs {
     uint32_t spin_limit;   // bounded waits: polls before a wave gives up and sets *err
     int* err;
 };
-inline size_t lock_lds_bytes(uint32_t max_cells) { return sizeof(double) * (size_t)max_cells; }  // beside 8 static
+inline size_t lock_lds_bytes(uint32_t max_cells) { return sizeof(double) * ((size_t)max_cells + 1); }  // beside 8 static
 hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s);
 hipError_t launch_lock_cells(const int32_t* idx, int64_t nnz, const uint16_t* cell_of, uint16_t* out, hipStream_t s);
 

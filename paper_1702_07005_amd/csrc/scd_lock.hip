@@ -74,14 +74,15 @@ __device__ __forceinline__ LockMeta lock_meta(const LockArgs& t, uint64_t j, uin
     return c;
 }
 
-// The first 64 * kLockSlices entries of the part; lanes past its end hold cell 0 with value 0.
-__device__ __forceinline__ void lock_load(const LockArgs& t, const LockMeta& c, uint32_t lane, uint32_t (&ci)[kLockSlices],
-                                          float (&cv)[kLockSlices]) {
+// The first 64 * kLockSlices entries of the part; lanes past its end hold `none`, a cell of value 0 behind the
+// member's own (any of those may hold an infinity, which would make the sums of other coordinates NaN).
+__device__ __forceinline__ void lock_load(const LockArgs& t, const LockMeta& c, uint32_t lane, uint32_t none,
+                                          uint32_t (&ci)[kLockSlices], float (&cv)[kLockSlices]) {
     const uint32_t len = c.o1 - c.o0;
 #pragma unroll
     for (int r = 0; r < kLockSlices; ++r) {
         const uint32_t i = lane + 64u * (uint32_t)r;
-        ci[r] = 0u;
+        ci[r] = none;
         cv[r] = 0.0f;
         if (i < len) {
             ci[r] = t.idx[c.base + c.o0 + i];
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
     const uint32_t cell0 = t.cell0[k], n_cells = t.cell0[k + 1] - cell0;
     U* const u = static_cast<U*>(a.u);
     for (uint32_t i = threadIdx.x; i < n_cells; i += blockDim.x) cells[i] = (double)u[t.ids[cell0 + i]];
+    if (threadIdx.x == 0) cells[n_cells] = 0.0;
     if (threadIdx.x < 2) gave_up[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
     LockMeta cur = lock_meta(t, wave, k), nxt = lock_meta(t, (uint64_t)wave + W, k);
     uint32_t ci[kLockSlices];
     float cv[kLockSlices];
-    lock_load(t, cur, lane, ci, cv);
+    lock_load(t, cur, lane, n_cells, ci, cv);
     uint64_t* const base_tag = t.slots + kLockSlotWords;
     const uint32_t tag0 = (uint32_t)__builtin_amdgcn_readfirstlane(
         (int)__hip_atomic_load(base_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
         __builtin_amdgcn_sched_barrier(0);
         uint32_t ni[kLockSlices];
         float nv[kLockSlices];
-        lock_load(t, nxt, lane, ni, nv);
+        lock_load(t, nxt, lane, n_cells, ni, nv);
         const LockMeta nn = lock_meta(t, (uint64_t)j + 2ull * W, k);
         __builtin_amdgcn_sched_barrier(0);
         uint32_t pv = 0;

@@ -213,6 +213,7 @@ __global__ __launch_bounds__(256) void k_probe_gather(ProbeArgs a) {
             float v[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
+                // Stands in with an entry of the same segment: T is finite (its entries are sums of entries of unit vectors).
                 const bool in = b + (int64_t)r * G < s1;
                 const int64_t k = in ? b + (int64_t)r * G : b;
                 ix[r] = a.idx[k];

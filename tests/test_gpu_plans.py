@@ -404,6 +404,35 @@ def test_lockstep_converges_and_resumes():
     s.close()
 
 
+@pytest.mark.parametrize("wide", [0, 1])
+def test_lockstep_of_an_infinite_entry(wide):
+    # A state with one infinite shared-vector entry: the coordinate that has it diverges, the others reach
+    # the minimiser as without it (condition about 5: 40 epochs reach fp32 rounding).  It is the first cell of
+    # a member, and every part leaves lanes without an entry.
+    rng = np.random.default_rng(14)
+    n, per, L = 251, 400, 4_501
+    idx = np.stack([np.sort(rng.choice(np.arange(500, L), per, replace=False)) for _ in range(n)]).astype(np.int32)
+    idx[0] = np.arange(per)  # apart from all others
+    p = synth.Problem("apart", "ridge_dual", "csr", n, L, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
+                      (rng.standard_normal(n * per) / 20).astype(np.float32), rng.standard_normal(n).astype(np.float32), 1e-3, 0)
+    out = []
+    for first in (0.0, np.inf):
+        s = scd.solver_for(p)
+        s.set_option("shared_fp64", wide)
+        assert _lockstep(s)
+        shared = torch.zeros(L, device="cuda")
+        shared[0] = first
+        s.set_state(torch.zeros(n, device="cuda"), shared, 0)
+        s.epochs(0, 40)
+        m, u, _ = s.get_state()
+        out.append((f64(m), f64(u)))
+        s.close()
+    (m0, u0), (m1, u1) = out
+    assert np.all(np.isfinite(m0)) and not np.isfinite(m1[0]) and not np.any(np.isfinite(u1[:per]))
+    assert np.max(np.abs(m1[1:] - m0[1:])) <= 1e-4 * np.max(np.abs(m0))
+    assert np.max(np.abs(u1[per:] - u0[per:])) <= 1e-4 * np.max(np.abs(u0))
+
+
 def test_lockstep_selection():
     p = LOCKSTEP["text"]()
     s = scd.solver_for(p)
