@@ -172,8 +172,6 @@ struct scd_solver {
     uint32_t* ring = nullptr;     // [kHotRing][staged_rec_words(cap, Smax)]
     uint32_t* ring_flags = nullptr;  // [kHotFlagWords]
     uint64_t* ring_results = nullptr;  // [kHotResultWords]
-    uint32_t* ring_prog = nullptr;   // [4]
-    uint32_t ring_tag = 1;        // tag of the next staged launch (never 0)
     int64_t hot_wait_limit = 0;   // option (test hook): sleeps per wait before giving up, 0 = kHotSpinLimit
     int* err_host = nullptr;      // pinned copies of hot_err: one per gap slot + one for reduce_state
     // Team kernel (long segments, few coordinates in flight): tables built on first need for K.
@@ -726,19 +724,14 @@ int build_hot_tables(scd_solver* h, double min_cover, hipStream_t s) {
             const size_t ring_bytes = sizeof(uint32_t) * (size_t)kHotRing * staged_rec_words(cap, Smax);
             if (hipMalloc(&h->ring, ring_bytes) != hipSuccess ||
                 hipMalloc(&h->ring_flags, sizeof(uint32_t) * kHotFlagWords) != hipSuccess ||
-                hipMalloc(&h->ring_results, sizeof(uint64_t) * kHotResultWords) != hipSuccess ||
-                hipMalloc(&h->ring_prog, 4 * sizeof(uint32_t)) != hipSuccess) {
+                hipMalloc(&h->ring_results, sizeof(uint64_t) * kHotResultWords) != hipSuccess) {
                 (void)hipGetLastError();
                 (void)hipFree(h->ring);
                 (void)hipFree(h->ring_flags);
                 (void)hipFree(h->ring_results);
-                (void)hipFree(h->ring_prog);
                 h->ring = nullptr;
                 h->ring_flags = nullptr;
                 h->ring_results = nullptr;
-                h->ring_prog = nullptr;
-            } else {
-                hip(hipMemsetAsync(h->ring_prog, 0, 4 * sizeof(uint32_t), s), "zero ring_prog");
             }
         }
     }
@@ -1176,7 +1169,6 @@ void release(scd_solver* h) {
     (void)hipFree(h->ring);
     (void)hipFree(h->ring_flags);
     (void)hipFree(h->ring_results);
-    (void)hipFree(h->ring_prog);
     (void)hipFree(h->entry_key);
     (void)hipFree(h->hot_ids);
     (void)hipFree(h->hot_err);
@@ -1542,10 +1534,7 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
                     ha.ring = h->ring;
                     ha.flags = h->ring_flags;
                     ha.results = h->ring_results;
-                    ha.prog = h->ring_prog;
-                    ha.tag = h->ring_tag;
                     ha.stagers = kHotStagers;
-                    h->ring_tag = h->ring_tag == 0xFFFFFFFFu ? 1u : h->ring_tag + 1u;
                     HIP_TRY(launch_epoch_staged(h->form, h->wide != 0, ha, hg.lds, s));
                 } else {
                     HIP_TRY(launch_epoch_hot(h->form, h->wide != 0, ha, hg.lds, s));

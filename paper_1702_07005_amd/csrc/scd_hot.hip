@@ -619,8 +619,9 @@ __device__ void staged_stager(const HotArgs& h, const HotSched& sc, uint32_t* ld
         if (threadIdx.x == 0) {
             uint32_t ok = 0;
             for (uint32_t spins = 0; spins < h.spin_limit; ++spins) {
-                if (__hip_atomic_load(h.prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == h.tag) {
-                    ok = __hip_atomic_load(h.prog + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == hot_xcc_id();
+                if (__hip_atomic_load(h.flags + kHotStartWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1u) {
+                    ok = __hip_atomic_load(h.flags + kHotStartWord + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                         hot_xcc_id();
                     break;
                 }
                 __builtin_amdgcn_s_sleep(2);
@@ -940,10 +941,10 @@ __global__ __launch_bounds__(64 * kHotWaves) void k_epoch_staged(HotArgs h) {
     U* const uu = static_cast<U*>(a.u);
     const int tid = threadIdx.x, wave = (int)wave_uniform((uint32_t)tid >> 6), lane = tid & 63;
     if (tid == 0) {
-        // Workgroup 0's XCD and this launch, for the stagers.
-        __hip_atomic_store(h.prog + 1, hot_xcc_id(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // Workgroup 0's XCD, then that it has started, for the stagers.
+        __hip_atomic_store(h.flags + kHotStartWord + 1, hot_xcc_id(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_s_waitcnt(0x0F70);
-        __hip_atomic_store(h.prog, h.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(h.flags + kHotStartWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     for (uint32_t i = tid; i < h.n_hot + kHotZeroCells; i += blockDim.x) hot[i] = i < h.n_hot ? (HotCell)uu[h.hot_ids[i]] : HotCell(0);
     if (tid < 2 * kHotMaxProducers + 2) ready[tid] = 0u;
@@ -1038,7 +1039,7 @@ hipError_t staged_prepare(int form, bool wide, uint32_t Smax, size_t lds_bytes) 
 
 hipError_t launch_epoch_staged(int form, bool wide, const HotArgs& h, size_t lds_bytes, hipStream_t s) {
     const void* f = staged_kernel(form, wide, h.Smax);
-    if (!f || !h.ring || !h.flags || !h.results || !h.prog || h.stagers < 1 || h.cap > 64) return hipErrorInvalidValue;
+    if (!f || !h.ring || !h.flags || !h.results || h.stagers < 1 || h.cap > 64) return hipErrorInvalidValue;
     // A stager keeps one batch image per wave in the dynamic LDS every workgroup of the launch receives.
     if (staged_lds_bytes(h.hot_bytes, h.cap, h.Smax) > lds_bytes) return hipErrorInvalidValue;
     hipError_t e = launch_fill_zero(reinterpret_cast<uint64_t*>(h.flags), kHotFlagWords / 2, s);

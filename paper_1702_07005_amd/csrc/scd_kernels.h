@@ -167,7 +167,11 @@ __host__ __device__ constexpr uint32_t staged_rec_words(uint32_t cap, uint32_t S
     return hot_buf_words(cap, Smax);
 }
 // Words of the ring's flags: tag[R] (batch + 1 staged), slot_free[R] (batch + 1 loaded), res_free[R]
-// (batch + 1 whose results its stager has read), the claim counter, padded; zeroed before every launch.
+// (batch + 1 whose results its stager has read), the claim counter, and in a 128-byte line of their own the
+// start words: 1 once workgroup 0 has started, and its XCD; padded.  A kernel zeroes them before every launch,
+// also where a captured graph replays it: a start word left by the launch before would let stagers take that
+// launch's XCD for this one's.
+constexpr uint32_t kHotStartWord = 3 * kHotRing + 32;
 constexpr uint32_t kHotFlagWords = 3 * kHotRing + 64;
 // 64-bit words of the result ring: per record, 2 words (model value, coefficient; each with the batch
 // + 1 in its high half) per coordinate of the batch; zeroed before every launch.
@@ -194,8 +198,6 @@ struct HotArgs {
     uint32_t* ring;            // [kHotRing][staged_rec_words(cap, Smax)]
     uint32_t* flags;           // [kHotFlagWords], zero at launch
     uint64_t* results;         // [kHotResultWords], zero at launch
-    uint32_t* prog;            // [4]: launch tag and XCD of workgroup 0, for the stagers
-    uint32_t tag;              // this launch's tag (nonzero, new for every staged launch of the handle)
     uint32_t stagers;          // stager workgroups
     const uint32_t* adapt_in;  // adaptive window (null: W): coordinates in flight for this launch,
                                // written by the previous one
@@ -274,7 +276,7 @@ size_t hot_lds_bytes(uint32_t hot_bytes, uint32_t B, uint32_t Smax);
 size_t staged_lds_bytes(uint32_t hot_bytes, uint32_t cap, uint32_t Smax);
 hipError_t hot_prepare(int form, bool wide, uint32_t Smax, size_t lds_bytes);
 hipError_t launch_epoch_hot(int form, bool wide, const HotArgs& h, size_t lds_bytes, hipStream_t s);
-// The staged variant (h.ring, h.flags, h.prog set): zeroes the flags, then launches 1 + kHotXcds *
+// The staged variant (h.ring, h.flags, h.results set): zeroes the flags, then launches 1 + kHotXcds *
 // h.stagers workgroups.
 hipError_t launch_epoch_staged(int form, bool wide, const HotArgs& h, size_t lds_bytes, hipStream_t s);
 hipError_t staged_prepare(int form, bool wide, uint32_t Smax, size_t lds_bytes);

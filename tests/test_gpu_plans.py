@@ -187,6 +187,39 @@ def test_staged_from_16_mb_of_entries():
         s.close()
 
 
+def test_staged_epochs_replayed_from_a_graph():
+    # A captured call of two epochs repeats their visiting orders at every replay; the oracle runs the same
+    # orders.  Eager epochs and synchronisations between the replays, each checked as an eager epoch is.
+    p = synth.make("click_svm", n_rows=60_001, n_cols=70_001)
+    s = scd.solver_for(p)
+    assert s.info()["kernel"] == "hot_staged"
+    P0, _ = s.objective()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        s.epochs(0, 2)
+    model, shared = np.zeros(p.C), np.zeros(p.L)
+    for replay in range(4):
+        graph.replay()
+        orc.epochs(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, 0, 0, 2, model, shared)
+        if replay == 1:
+            torch.cuda.synchronize()
+            s.set_state(*s.get_state()[:2], epoch=9)
+            s.epochs(0, 1)
+            orc.epochs(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, 0, 9, 1, model, shared)
+        torch.cuda.synchronize()
+        Gr = orc.objectives(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, model, shared)[2]
+        gm, gs, _ = s.get_state()
+        gm, gs = f64(gm), f64(gs)
+        fresh = orc.fresh_shared(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, gm)
+        assert np.max(np.abs(gs - fresh)) <= 1e-4 * np.max(np.abs(fresh)), replay
+        G = s.duality_gap()
+        print(f"  replay {replay}: gap {G:.3e} oracle {Gr:.3e}", flush=True)
+        assert G <= 2.0 * Gr + 1e-6 * abs(P0), replay
+    s.close()
+
+
 @pytest.mark.parametrize("wide", [0, 1])
 def test_wide_automatic_window_cut_for_the_hot_set(wide):
     # The ridge dual on click rows couples weakly enough for a window between 17 and 64 at this

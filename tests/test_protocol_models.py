@@ -8,6 +8,9 @@ interleavings of their waves (host only; no GPU).
   does.  Checked: no interleaving deadlocks (for 1 to 192 stager waves, one to four consumers, rings
   of 2 to 64 records), every record a loader takes is its batch's, every result a stager reads is its
   batch's, and every batch is written out exactly once.
+* The start of a staged launch: stagers learn workgroup 0's XCD from two words.  Checked: those of that
+  XCD take part and no others, in launch after launch (or replay after replay of a captured one) whose
+  workgroup 0 lands on other XCDs.
 * The split epoch: workgroups claim chunks of units in order and process them in order; a SCATTER
   unit waits for the GATHER slots of its coordinate.  Checked: no deadlock for any number of
   workgroups and chunk sizes, and every part of a coordinate takes the same step (the sum of all its
@@ -220,6 +223,41 @@ def test_staged_model_detects_waiting_for_a_tag_while_holding_results():
             return super().loader(q)
 
     assert any(TagFirst(200, 64, 1, 2, seed).run() != list(range(200)) for seed in range(5))
+
+
+# ------------------------------------------------------------------------------- start of a staged launch
+
+def staged_start(words, xcd, zeroed, seed):
+    """XCDs whose stagers take part.  `words`: [1 once workgroup 0 has started, its XCD], from the
+    launch before unless `zeroed`."""
+    rng = random.Random(seed)
+    if zeroed:
+        words[:] = [0, 0]
+    stores = [(1, xcd), (0, 1)]  # workgroup 0's, in order
+    waiting, took = list(range(8)), set()
+    while stores or waiting:
+        if stores and rng.random() < 0.2:
+            i, v = stores.pop(0)
+            words[i] = v
+        elif waiting:
+            x = rng.choice(waiting)
+            if words[0] == 1:
+                waiting.remove(x)
+                if words[1] == x:
+                    took.add(x)
+    return took
+
+
+def test_staged_start_takes_the_stagers_of_workgroup_0s_xcd():
+    rng, words = random.Random(1), [0, 0]
+    for seed in range(300):
+        xcd = rng.randrange(8)
+        assert staged_start(words, xcd, True, seed) == {xcd}
+
+
+def test_staged_start_model_detects_words_kept_from_the_launch_before():
+    words = [0, 0]
+    assert any(staged_start(words, seed % 8, False, seed) != {seed % 8} for seed in range(20))
 
 
 # ------------------------------------------------------------------------------------------- split
