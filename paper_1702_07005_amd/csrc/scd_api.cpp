@@ -181,8 +181,7 @@ struct scd_solver {
     float* team_val = nullptr;    // [nnz]
     uint32_t* team_off = nullptr;  // [C * (K + 1)]
     uint32_t* team_bound = nullptr;  // [K + 1]
-    uint64_t* team_slots = nullptr;  // [cus * 2 * kTeamMax] partial-sum slots (tag 0 at allocation)
-    uint32_t team_tag = 1;        // tag of the next team step
+    uint64_t* team_slots = nullptr;  // [cus * 2 * kTeamMax] partial-sum slots (zeroed by each launch)
     // Lockstep kernel (few coordinates in flight, a shared vector that fits the LDS of a few CUs).
     int64_t lockstep = 1;         // option
     int lock_state = 0;           // 0 tables not tried, 1 built, -1 they do not fit
@@ -781,7 +780,6 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
     if (!h->team_slots) {
         const size_t sb = sizeof(uint64_t) * 2 * kTeamMax * (size_t)h->cus;
         HIP_TRY(hipMalloc(&h->team_slots, sb));
-        HIP_TRY(hipMemsetAsync(h->team_slots, 0, sb, s));
     }
     unsigned* hits = h->hits;
     // Without memory for the tables the other kernels run instead: an allocation that fails here
@@ -1485,12 +1483,9 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
             ta.off = h->team_off;
             ta.slots = h->team_slots;
             ta.K = (uint32_t)lp.team;
-            ta.tag0 = h->team_tag;
             ta.spin_limit = h->hot_wait_limit > 0 ? (uint32_t)h->hot_wait_limit : kHotSpinLimit;
             ta.err = h->hot_err;
             HIP_TRY(launch_epoch_team(h->form, h->wide != 0, lp.fresh != 0, ta, lp.blocks, h->cus, s));
-            // Steps of the busiest team, plus one: the next launch's tags are all new.
-            h->team_tag += (uint32_t)((h->C + n_groups - 1) / n_groups + 1);
         } else if (lp.kind == PLAN_SPLIT) {
             SplitArgs sa{};
             sa.e = a;

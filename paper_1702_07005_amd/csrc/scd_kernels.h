@@ -309,9 +309,8 @@ constexpr int kTeamSlices = 4;  // register slices per lane (256 x 4 entries of 
 struct TeamArgs {
     EpochArgs e;
     const uint32_t* off;   // [C * (K + 1)]
-    uint64_t* slots;       // [n_groups * 2 * kTeamMax]
+    uint64_t* slots;       // [n_groups * 2 * kTeamMax], zeroed by the launch
     uint32_t K;
-    uint32_t tag0;         // tag of the first step of this launch (tags grow by one per step)
     uint32_t spin_limit;   // bounded waits: after this many sleeps a member gives up and sets *err
     int* err;
 };

@@ -22,9 +22,9 @@
 // it reads has landed.  A team thus holds one coordinate between gather and scatter, as a
 // draining group of the pipelined kernel does, and n_groups teams keep the window.
 //
-// Slots: team t, step tag g, member k at slots[(t * 2 + g % 2) * kTeamMax + k].  Tags grow by one
-// per step (and across launches, from the host's counter), so a slot that has not been rewritten
-// for this step carries an older tag.  A member overwrites the slot of step g at step g + 2, after
+// Slots: team t, step tag g, member k at slots[(t * 2 + g % 2) * kTeamMax + k].  They are zeroed before
+// every launch by a kernel, which a captured graph replays too, and tags grow by one per step from 1,
+// so a slot that has not been rewritten for this step carries an older tag.  A member overwrites the slot of step g at step g + 2, after
 // it has seen every member's partial of step g + 1, which each member publishes only after it has
 // read all partials of step g: no member still waits on the value being overwritten.  Each slot is
 // one location written and read with 64-bit device-scope atomics, so no ordering between
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void k_epoch_team(TeamArgs t) {
     const SharedBuf<U> ub =
         shared_buf<U>(a.u, a.u_bytes, reinterpret_cast<U*>(a.sink) + (size_t)blockIdx.x * 256 + threadIdx.x, a.u_shift);
     const uint32_t P = a.n_groups;
-    uint32_t j = team, tag = t.tag0;
+    uint32_t j = team, tag = 1u;
     TeamMeta cA = team_meta(t, perm_at(j, a.perm), k);
     int ciA[R], ciB[R];
     float cvA[R], cvB[R];
@@ -330,6 +330,8 @@ hipError_t launch_team_form(bool wide, bool fresh, const TeamArgs& t, int blocks
 }  // namespace
 
 hipError_t launch_epoch_team(int form, bool wide, bool fresh, const TeamArgs& t, int blocks, int cus, hipStream_t s) {
+    const hipError_t e = launch_fill_zero(t.slots, t.e.n_groups * 2u * (uint32_t)kTeamMax, s);
+    if (e != hipSuccess) return e;
     switch (form) {
         case FORM_RIDGE_PRIMAL: return launch_team_form<FORM_RIDGE_PRIMAL>(wide, fresh, t, blocks, cus, s);
         case FORM_SVM_DUAL: return launch_team_form<FORM_SVM_DUAL>(wide, fresh, t, blocks, cus, s);

@@ -187,12 +187,24 @@ def test_staged_from_16_mb_of_entries():
         s.close()
 
 
-def test_staged_epochs_replayed_from_a_graph():
+REPLAYED = {  # problem, options, epoch kernel
+    "pipelined": (lambda: synth.make("sparse_ridge", n_rows=20_000, n_cols=10_000, density=1e-3, lam=1e-3), {"window": 300}, "pipelined"),
+    "team": (lambda: synth.make("dense_ridge"), {"window": 4, "team": 4}, "team"),
+    "hot": (lambda: synth.make("click_svm", n_rows=20_001, n_cols=30_001), {}, "hot_lds"),
+    "staged": (lambda: synth.make("click_svm", n_rows=60_001, n_cols=70_001), {}, "hot_staged"),
+}
+
+
+@pytest.mark.parametrize("case", sorted(REPLAYED))
+def test_epochs_replayed_from_a_graph(case):
     # A captured call of two epochs repeats their visiting orders at every replay; the oracle runs the same
     # orders.  Eager epochs and synchronisations between the replays, each checked as an eager epoch is.
-    p = synth.make("click_svm", n_rows=60_001, n_cols=70_001)
+    make, options, kernel = REPLAYED[case]
+    p = make()
     s = scd.solver_for(p)
-    assert s.info()["kernel"] == "hot_staged"
+    for key, value in options.items():
+        s.set_option(key, value)
+    assert s.info()["kernel"] == kernel
     P0, _ = s.objective()
     side = torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -215,7 +227,7 @@ def test_staged_epochs_replayed_from_a_graph():
         fresh = orc.fresh_shared(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, gm)
         assert np.max(np.abs(gs - fresh)) <= 1e-4 * np.max(np.abs(fresh)), replay
         G = s.duality_gap()
-        print(f"  replay {replay}: gap {G:.3e} oracle {Gr:.3e}", flush=True)
+        print(f"  {case} replay {replay}: gap {G:.3e} oracle {Gr:.3e}", flush=True)
         assert G <= 2.0 * Gr + 1e-6 * abs(P0), replay
     s.close()
 
