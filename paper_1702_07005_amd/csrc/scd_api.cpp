@@ -194,9 +194,8 @@ struct scd_solver {
     uint32_t split_built = 0;     // part length of the tables (0 = none)
     uint32_t split_n = 0;         // units per epoch at that part length
     SplitUnit* split_units = nullptr;  // [split_n] records, rewritten by each epoch's pre-pass
-    uint64_t* split_partials = nullptr;  // [split_n] tagged partial sums (tag 0 at allocation)
+    uint64_t* split_partials = nullptr;  // [split_n] partial sums (cleared by each launch)
     uint32_t* split_tiles = nullptr;  // [ceil(C / kSplitPrepTile)] pre-pass scratch
-    uint32_t split_tag = 1;       // tag of the next split launch (never 0)
 };
 
 namespace {
@@ -989,7 +988,7 @@ void free_split_tables(scd_solver* h) {
 }
 
 // Unit tables of the split kernel for part length `part`: the number of units per epoch (the same
-// for every permutation), the records the pre-pass rewrites each epoch, the tagged partial sums and
+// for every permutation), the records the pre-pass rewrites each epoch, the partial sums and
 // the pre-pass's tile counts.  Built once per part length (synchronises).
 int build_split_tables(scd_solver* h, uint32_t part, hipStream_t s) {
     if (h->split_built == part) return SCD_OK;
@@ -1007,15 +1006,12 @@ int build_split_tables(scd_solver* h, uint32_t part, hipStream_t s) {
     e = hipMalloc(&h->split_units, sizeof(SplitUnit) * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&h->split_partials, sizeof(uint64_t) * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&h->split_tiles, sizeof(uint32_t) * std::max<size_t>(tiles, 1));
-    if (e == hipSuccess) e = hipMemsetAsync(h->split_partials, 0, sizeof(uint64_t) * (size_t)n, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         free_split_tables(h);
         return fail(SCD_ERR_HIP, "split tables (%llu units): %s", n, hipGetErrorString(e));
     }
     h->split_built = part;
     h->split_n = (uint32_t)n;
-    h->split_tag = 1;
     return SCD_OK;
 }
 
@@ -1492,12 +1488,10 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
             sa.units = h->split_units;
             sa.partials = h->split_partials;
             sa.n_units = h->split_n;
-            sa.tag = h->split_tag;
             sa.spin_limit = h->hot_wait_limit > 0 ? (uint32_t)h->hot_wait_limit : kHotSpinLimit;
             sa.err = h->hot_err;
             HIP_TRY(launch_epoch_split(h->form, h->wide != 0, lp.fresh != 0, sa, lp.part, h->split_tiles, h->split_units,
                                        lp.blocks, s));
-            h->split_tag = h->split_tag == 0xFFFFFFFFu ? 1u : h->split_tag + 1u;
         } else if (lp.kind == PLAN_HOT || lp.kind == PLAN_HOT_STAGED) {
             HotArgs ha{};
             ha.e = a;

@@ -375,9 +375,8 @@ __host__ __device__ inline uint32_t split_units_of(int64_t len, uint32_t part) {
 struct SplitArgs {
     EpochArgs e;           // e.perm: the epoch's permutation; e.queue, e.chunk as for the queued kernel
     const SplitUnit* units;
-    uint64_t* partials;    // [n_units]: GATHER unit u writes (fp32 bits | tag << 32) at partials[u]
+    uint64_t* partials;    // [n_units]: cleared by the pre-pass; GATHER unit u writes (fp32 bits | 1 << 32) at partials[u]
     uint32_t n_units;
-    uint32_t tag;          // this launch's tag (never 0; the host counts launches)
     uint32_t spin_limit;   // bounded waits: after this many sleeps a SCATTER unit gives up and sets *err
     int* err;
 };

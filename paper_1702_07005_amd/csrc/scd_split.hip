@@ -11,8 +11,8 @@
 //   FULL    (len <= part)  gather, reduce, step (eq. update_primal, the SVM dual step, or eq.
 //                          update_dual), model store, scatter: one unit of the queued kernel;
 //   GATHER  part i of k    gather part i, reduce, publish the partial inner product in a 64-bit slot
-//                          (fp32 bits | launch tag << 32) at partials[unit index];
-//   SCATTER part i of k    wait until the k GATHER slots of the coordinate carry this launch's tag,
+//                          (fp32 bits | 1 << 32) at partials[unit index], which the pre-pass cleared;
+//   SCATTER part i of k    wait until the k GATHER slots of the coordinate are filled,
 //                          sum them in a fixed order (the same in every part, so every part takes the
 //                          bitwise-same step), store the model (part 0) and scatter part i.
 //
@@ -111,12 +111,13 @@ __global__ __launch_bounds__(1024) void k_split_scan(uint32_t* __restrict__ tile
     }
 }
 
-// Writes the unit records of each tile, at the tile's offset.  Thread t takes positions t, t + 256,
+// Writes the unit records of each tile, at the tile's offset, and clears the slots of its GATHER units (a replay of
+// a captured launch clears them too).  Thread t takes positions t, t + 256,
 // ... of the tile, so that consecutive lanes write consecutive records (most positions are one
 // unit); the offsets follow position order: slice i (positions i * 256 + t) after slices < i.
 __global__ __launch_bounds__(256) void k_split_write(EpochArgs a, uint32_t part,
                                                      const uint32_t* __restrict__ tile_base,
-                                                     SplitUnit* __restrict__ units) {
+                                                     SplitUnit* __restrict__ units, uint64_t* __restrict__ partials) {
     __shared__ uint32_t wsum[4];
     const PermKeys& p = a.perm;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(256) void k_split_write(EpochArgs a, uint32_t part,
                 r.len = (uint32_t)(rest < (int64_t)part ? rest : (int64_t)part);
                 r.info = ((uint32_t)SPLIT_GATHER << 30) | (k << 15) | q;
                 units[at + q] = r;
+                partials[at + q] = 0ull;
                 r.info = ((uint32_t)SPLIT_SCATTER << 30) | (k << 15) | q;
                 units[at + k + q] = r;
             }
@@ -264,7 +266,7 @@ __device__ __forceinline__ uint32_t split_step(const SplitArgs& sa, const Shared
                         const uint64_t v =
                             __hip_atomic_load(const_cast<uint64_t*>(slot + q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         pv[t] = (uint32_t)v;
-                        have = have && (uint32_t)(v >> 32) == sa.tag;
+                        have = have && (uint32_t)(v >> 32) == 1u;
                     }
                 }
                 if (__all(have)) break;
@@ -316,7 +318,7 @@ __device__ __forceinline__ uint32_t split_step(const SplitArgs& sa, const Shared
                     if (wb + r * 256 < len) split_atomic(ub, (uint32_t)ci[r], (int64_t)(lane + r * 256) < len, coef * cv[r]);
             }
         } else if (lane == 0) {
-            const uint64_t v = ((uint64_t)sa.tag << 32) | (uint64_t)__builtin_bit_cast(uint32_t, g);
+            const uint64_t v = (1ull << 32) | (uint64_t)__builtin_bit_cast(uint32_t, g);
             __hip_atomic_store(sa.partials + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -438,7 +440,7 @@ hipError_t launch_epoch_split(int form, bool wide, bool fresh, const SplitArgs& 
     const uint32_t tiles = (uint32_t)(((uint64_t)C + kSplitPrepTile - 1) / kSplitPrepTile);
     hipLaunchKernelGGL(k_split_count, dim3(tiles), dim3(256), 0, s, sa.e.ptr, sa.e.perm, part, tile_units);
     hipLaunchKernelGGL(k_split_scan, dim3(1), dim3(1024), 0, s, tile_units, tiles);
-    hipLaunchKernelGGL(k_split_write, dim3(tiles), dim3(256), 0, s, sa.e, part, tile_units, units);
+    hipLaunchKernelGGL(k_split_write, dim3(tiles), dim3(256), 0, s, sa.e, part, tile_units, units, sa.partials);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     switch (form) {
         case FORM_RIDGE_PRIMAL: return launch_split_form<FORM_RIDGE_PRIMAL>(wide, fresh, sa, blocks, s);

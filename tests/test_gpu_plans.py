@@ -190,6 +190,8 @@ def test_staged_from_16_mb_of_entries():
 REPLAYED = {  # problem, options, epoch kernel
     "pipelined": (lambda: synth.make("sparse_ridge", n_rows=20_000, n_cols=10_000, density=1e-3, lam=1e-3), {"window": 300}, "pipelined"),
     "team": (lambda: synth.make("dense_ridge"), {"window": 4, "team": 4}, "team"),
+    "split": (lambda: synth.make("text_ridge_csc", n_rows=3_500, n_cols=166_000, row_nnz=370), {"split_part": 128}, "split"),
+    "queued": (lambda: synth.make("text_ridge_csc", n_rows=3_500, n_cols=166_000, row_nnz=370), {"split": 0}, "queued"),
     "hot": (lambda: synth.make("click_svm", n_rows=20_001, n_cols=30_001), {}, "hot_lds"),
     "staged": (lambda: synth.make("click_svm", n_rows=60_001, n_cols=70_001), {}, "hot_staged"),
 }
