@@ -261,7 +261,7 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 64 is cut to 16 for this where the epoch would be staged (below) and the hot set
  *                 covers at least half of the stored entries.  The hot set is chosen
  *                 (a pass over the matrix, synchronising) when this first applies: at create, or
- *                 when "window" or "hot" is set.
+ *                 when "window", "hot", "staged", "adapt" or "group" is set.
  *   "team"        1 (default) = with a binding window, segments of at least 1,024 entries on
  *                 average and none longer than 4 times that, a shared vector of at least 4 MB and
  *                 "group" 0, process each in-flight

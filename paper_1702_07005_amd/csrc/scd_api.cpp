@@ -1628,6 +1628,8 @@ int scd_set_option(scd_handle_t h, const char* key, int64_t value) {
     if (!strcmp(key, "staged")) {
         if (value < 0 || value > 2) return fail(SCD_ERR_INVALID, "staged must be 0, 1 or 2");
         h->staged = value;
+        if (int r = set_device(h)) return r;
+        if (int r = hot_if_needed(h, nullptr)) return r;  // it may be what cuts an automatic window (hot_geometry)
     } else if (!strcmp(key, "adapt")) {
         if (value != 0 && value != 1) return fail(SCD_ERR_INVALID, "adapt must be 0 or 1");
         h->adapt = value;

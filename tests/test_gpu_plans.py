@@ -255,6 +255,12 @@ def test_wide_automatic_window_cut_for_the_hot_set(wide):
     small = synth.as_ridge_dual(synth.make("click_svm", n_rows=40_000, n_cols=60_000, lam=6 / 40_000))
     s = scd.solver_for(small)
     assert s.info()["auto_window"] > 16 and s.info()["kernel"] == "pipelined"
+    # the plan follows from the options, not from the order they are set in
+    s.set_option("staged", 2)
+    assert s.info()["kernel"] == "hot_staged" and s.info()["window"] == 16
+    follow_oracle(small, s, 2)
+    s.set_option("staged", 1)
+    assert s.info()["kernel"] == "pipelined"
     s.close()
 
 
