@@ -1754,7 +1754,7 @@ int scd_get_option(scd_handle_t h, const char* key, int64_t* value) {
                 HIP_TRY(hipDeviceSynchronize());
                 HIP_TRY(hipMemcpy(&v, h->hot_adapt, sizeof v, hipMemcpyDeviceToHost));
             }
-            *value = v ? (int64_t)v : window;
+            *value = v ? (int64_t)v : (int64_t)hg.W;  // hg.W: an automatic window above 16 is cut
         } else {
             scd_info_t info;
             scd_get_info(h, &info);

@@ -245,7 +245,9 @@ def test_wide_automatic_window_cut_for_the_hot_set(wide):
     auto = s.info()["auto_window"]
     print(f"auto window {auto} {s.info()['kernel']} hot {s.info()['hot_entries']}", flush=True)
     assert 16 < auto <= 64 and s.info()["kernel"] == "hot_staged" and s.info()["window"] == 16
+    assert s.get_option("next_window") == 16
     follow_oracle(p, s, 4)
+    assert s.get_option("next_window") == 16
     for key, value in (("window", auto), ("staged", 0), ("hot", 0), ("group", 8), ("pipeline", 0)):
         s.set_option(key, value)
         assert (s.info()["kernel"] == "hot_staged") == (key == "pipeline"), key
