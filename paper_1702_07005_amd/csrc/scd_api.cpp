@@ -162,6 +162,7 @@ struct scd_solver {
     int32_t* hot_ids = nullptr;   // [n_hot]
     uint32_t n_hot = 0;
     double hot_cover = 0.0;       // fraction of stored entries that point at a hot entry
+    int hot_narrow = 0;           // its cover is too small for a cut window (found without building it)
     int* hot_err = nullptr;       // device flag set by a timed-out wait in the hot-set kernel
     int64_t adapt = 1;            // option: automatic window of the hot-set kernel follows the moving fraction
     uint32_t* hot_adapt = nullptr;  // [2]: the hot-set kernel's window for the next epoch (device)
@@ -696,6 +697,7 @@ int build_hot_tables(scd_solver* h, double min_cover, hipStream_t s) {
     (void)hipFree(scratch);
     if (rc == SCD_OK && (double)sum < min_cover * (double)h->nnz) {
         h->hot_built = 0;  // a narrower window may still want it
+        h->hot_narrow = 1;
         cnt = 0;
     }
     if (rc == SCD_OK && cnt > 0 && (rc = assign_slots(h, hits, T, cnt, &slot_of, &h->hot_ids, s)) == SCD_OK) {
@@ -748,9 +750,16 @@ int build_hot_tables(scd_solver* h, double min_cover, hipStream_t s) {
 // Builds the hot set when the current options would use the hot-set kernel.
 int hot_if_needed(scd_solver* h, hipStream_t s) {
     const int64_t window = h->window ? h->window : h->auto_window;
+    const bool cut = window > kHotMaxWindow;
     HotGeom g;
-    if (!h->hot || h->group != 0 || h->hot_built || !hot_geometry(h, window, &g)) return SCD_OK;
-    return build_hot_tables(h, window > kHotMaxWindow ? kHotWidenCover : 0.0, s);
+    if (!h->hot || h->group != 0 || h->hot_built || (cut && h->hot_narrow) || !hot_geometry(h, window, &g)) return SCD_OK;
+    const int r = build_hot_tables(h, cut ? kHotWidenCover : 0.0, s);
+    if (!cut || r != SCD_ERR_OOM) return r;
+    // The pipelined kernel runs such a window too: no memory for the tables is no error.
+    (void)hipGetLastError();
+    g_err.clear();
+    h->hot_built = 0;
+    return SCD_OK;
 }
 
 void free_team_tables(scd_solver* h) {
@@ -774,7 +783,7 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     const size_t nnz1 = (size_t)std::max<int64_t>(h->nnz, 1);
-    const size_t need = nnz1 * 8 + (size_t)h->C * (K + 1) * 4 + sizeof(unsigned) * (size_t)h->L;
+    const size_t need = nnz1 * 8 + (size_t)h->C * (K + 1) * 4 + (h->hits ? 0 : sizeof(unsigned) * (size_t)h->L);
     if (need + (size_t(1) << 30) > free_b) return SCD_OK;
     if (!h->team_slots) {
         const size_t sb = sizeof(uint64_t) * 2 * kTeamMax * (size_t)h->cus;
@@ -1357,7 +1366,15 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
             h->wide = 1;
             (void)hipFree(h->u);
             h->u = nullptr;
-            hip(hipMalloc(&h->u, sizeof(double) * (size_t)h->L), "hipMalloc(shared, fp64)");
+            const size_t wide_bytes = sizeof(double) * (size_t)h->L;
+            if (h->hits && hipMalloc(&h->u, wide_bytes) != hipSuccess) {
+                // The counts are only kept to spare counting again.
+                (void)hipGetLastError();
+                (void)hipFree(h->hits);
+                h->hits = nullptr;
+                h->u = nullptr;
+            }
+            if (rc == SCD_OK && !h->u) hip(hipMalloc(&h->u, wide_bytes), "hipMalloc(shared, fp64)");
         }
     }
     if (rc == SCD_OK) {
@@ -1383,9 +1400,9 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         if (rc == SCD_OK) step(hot_if_needed(h, s));
         if (rc == SCD_OK) step(team_if_needed(h, s));
         if (rc == SCD_OK) step(lock_if_needed(h, s));
-        if (rc == SCD_OK) step(split_if_needed(h, s));
         (void)hipFree(h->hits);
         h->hits = nullptr;
+        if (rc == SCD_OK) step(split_if_needed(h, s));
         hip(hipMemsetAsync(h->model, 0, sizeof(float) * (size_t)h->C, s), "zero model");
         hip(hipMemsetAsync(h->u, 0, (h->wide ? sizeof(double) : sizeof(float)) * (size_t)h->L, s), "zero shared");
         hip(hipStreamSynchronize(s), "synchronize");

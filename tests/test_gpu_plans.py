@@ -173,6 +173,40 @@ def test_coupling_estimate_without_memory_for_the_rows():
         assert abs(c - coupling) <= 2e-5 * coupling and abs(h - coherence) <= 2e-5 * max(abs(coherence), coupling)
 
 
+@pytest.mark.parametrize("case", ["fp64", "cut"])
+def test_create_with_little_memory(case):
+    # What scd_create holds while it runs is given up where memory is short: the counts when the shared
+    # vector is allocated again in fp64 ("fp64": an index that all rows have), and the hot set that would cut
+    # an automatic window of 17 to 64 ("cut"; the pipelined kernel runs it).
+    if case == "fp64":
+        rng = np.random.default_rng(6)
+        n, L, per = 30_000, 260_000_000, 80
+        idx = np.sort(rng.integers(1, 3_000, (n, per)) * (L // 3_000) + np.arange(per), axis=1).astype(np.int32)
+        idx[:, 0] = 0
+        p = synth.Problem("wide", "ridge_dual", "csr", n, L, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
+                          (rng.standard_normal(n * per) / np.sqrt(per)).astype(np.float32),
+                          rng.standard_normal(n).astype(np.float32), 1e-2, 0)
+        leave = 8 * L + (256 << 20)  # the vector in fp64, not the counts (4 bytes an index) beside it
+    else:
+        n, L = 60_000, 500_000_000
+        p = synth.as_ridge_dual(synth.make("click_svm", n_rows=n, n_cols=L, lam=6 / n))
+        leave = 8 * L + (400 << 20)  # the vector and the counts, not the hot set's table of 2 bytes an index
+    d = scd.upload(p)
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - leave, dtype=torch.uint8, device="cuda")
+    s = scd.Solver(p.n_rows, p.n_cols, *d, p.lam, p.form)
+    i = s.info()
+    print(f"{case}: {i['kernel']} auto window {i['auto_window']} fp64 {i['shared_fp64']} hot {i['hot_entries']}", flush=True)
+    assert i["shared_fp64"] == (case == "fp64") and i["hot_entries"] == 0 and i["kernel"] == "pipelined"
+    assert case == "fp64" or 16 < i["auto_window"] <= 64
+    P0, _ = s.objective()
+    s.epochs(0, 2)
+    assert 0.0 <= s.duality_gap() < abs(P0)
+    s.close()
+    del hold
+    torch.cuda.empty_cache()
+
+
 # ------------------------------------------------------------- hot-set plans
 
 def test_staged_from_16_mb_of_entries():
