@@ -4,12 +4,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -591,7 +593,7 @@ HitScratch hit_scratch(void* buf) {
 // histogram pass narrows T's interval kHitBins times, so two or three passes over hits find it.
 int hits_threshold(const scd_solver* h, const unsigned* hits, unsigned cap, const HitScratch& w, unsigned* T, hipStream_t s) {
     unsigned* bins = w.bins;
-    std::vector<unsigned> n(kHitBins);
+    std::array<unsigned, kHitBins> n;
     uint64_t lo = 1, hi = (uint64_t)h->max_hits + 1;  // T in [lo, hi]; `above` entries have at least hi hits
     uint64_t above = 0;
     while (lo < hi) {
@@ -638,23 +640,24 @@ int assign_slots(const scd_solver* h, const unsigned* hits, unsigned T, unsigned
                  int32_t** hot_ids, hipStream_t s) {
     const size_t nblk = (size_t)((h->L + kHotAssignBlock - 1) / kHotAssignBlock);
     unsigned* blocks = nullptr;
-    std::vector<unsigned> base(nblk);
     *slot_of = nullptr;
     *hot_ids = nullptr;
+    const std::unique_ptr<unsigned[]> base(new (std::nothrow) unsigned[nblk]);
+    if (!base) return fail(SCD_ERR_OOM, "host allocation failed");
     hipError_t e = hipMalloc(&blocks, sizeof(unsigned) * nblk);
     if (e == hipSuccess) e = hipMalloc(slot_of, sizeof(uint16_t) * (size_t)h->L);
     if (e == hipSuccess) e = hipMalloc(hot_ids, sizeof(int32_t) * (size_t)count);
     if (e == hipSuccess) e = launch_hot_block_count(hits, h->L, T, blocks, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(base.data(), blocks, sizeof(unsigned) * nblk, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(base.get(), blocks, sizeof(unsigned) * nblk, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess) {
         unsigned run = 0;
-        for (auto& b : base) {
-            const unsigned c = b;
-            b = run;
+        for (size_t b = 0; b < nblk; ++b) {
+            const unsigned c = base[b];
+            base[b] = run;
             run += c;
         }
-        e = hipMemcpyAsync(blocks, base.data(), sizeof(unsigned) * nblk, hipMemcpyHostToDevice, s);
+        e = hipMemcpyAsync(blocks, base.get(), sizeof(unsigned) * nblk, hipMemcpyHostToDevice, s);
     }
     if (e == hipSuccess) e = launch_hot_assign(hits, h->L, T, blocks, *slot_of, *hot_ids, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -807,19 +810,25 @@ int build_team_tables(scd_solver* h, int K, hipStream_t s) {
     auto hip = [&](hipError_t e, const char* what) {
         if (rc == SCD_OK && e != hipSuccess) rc = fail(SCD_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
     };
-    std::vector<unsigned> hh;
+    // As with the device's memory: without the host's for the counts the other kernels run instead.
+    const std::unique_ptr<unsigned[]> hh(new (std::nothrow) unsigned[(size_t)h->L]);
+    if (!hh) {
+        if (hits != h->hits) (void)hipFree(hits);
+        free_team_tables(h);
+        return SCD_OK;
+    }
     if (rc == SCD_OK) {
         if (hits != h->hits) {
             hip(hipMemsetAsync(hits, 0, sizeof(unsigned) * (size_t)h->L, s), "zero team hits");
             hip(launch_count_hits(h->idx, h->nnz, hits, s), "count hits");
         }
-        hh.resize((size_t)h->L);
-        hip(hipMemcpyAsync(hh.data(), hits, sizeof(unsigned) * (size_t)h->L, hipMemcpyDeviceToHost, s), "copy hits");
+        hip(hipMemcpyAsync(hh.get(), hits, sizeof(unsigned) * (size_t)h->L, hipMemcpyDeviceToHost, s), "copy hits");
         hip(hipStreamSynchronize(s), "synchronize");
     }
     if (rc == SCD_OK) {
         // bound[q] = the first index whose preceding entries number at least q * nnz / K.
-        std::vector<uint32_t> bound((size_t)K + 1, (uint32_t)h->L);
+        std::array<uint32_t, kTeamMax + 1> bound;
+        bound.fill((uint32_t)h->L);
         bound[0] = 0;
         const double total = (double)h->nnz;
         double cum = 0.0;
