@@ -557,6 +557,25 @@ int plan_epoch(const scd_solver* h, LaunchPlan* lp, uint32_t* n_groups) {
     return SCD_OK;
 }
 
+// Device scratch for set-up: while scd_create runs, the spread copy's buffer where it is large enough (an
+// allocation of a few MB and its release take 0.1-0.3 ms), else an allocation.
+struct SetupScratch {
+    char* p = nullptr;
+    bool own = false;
+    hipError_t get(const scd_solver* h, size_t bytes) {
+        // h->hits is held during scd_create only, when no epoch can be using the spread copy.
+        if (h->hits && h->us && ((size_t)h->L << kSpreadShift) >= bytes) {
+            p = static_cast<char*>(h->us);
+            return hipSuccess;
+        }
+        own = true;
+        return hipMalloc(&p, bytes);
+    }
+    ~SetupScratch() {
+        if (own) (void)hipFree(p);
+    }
+};
+
 // Stored entries per shared-vector index: those that scd_create counted, or (after it) counted again
 // into a buffer that the caller frees.
 int need_hits(scd_solver* h, unsigned** hits, bool* owned, hipStream_t s) {
@@ -866,39 +885,6 @@ void free_lock_tables(scd_solver* h) {
     h->lock_args = LockArgs{};
 }
 
-// Members' index ranges from the hits: the used indices cut into K runs of about equal entry count, or,
-// where a run would exceed `cap` cells, of equal cell count.  bound[0..K], cell0[0..K]; false if they
-// do not fit.
-bool lock_ranges(const std::vector<unsigned>& hits, int64_t nnz, uint32_t K, uint32_t cap, uint32_t* bound,
-                 uint32_t* cell0) {
-    const uint32_t L = (uint32_t)hits.size();
-    uint64_t used = 0;
-    for (const unsigned v : hits) used += v != 0;
-    if (used == 0 || used > (uint64_t)K * cap) return false;
-    for (int by_cells = 0; by_cells < 2; ++by_cells) {
-        const uint64_t total = by_cells ? used : (uint64_t)nnz;
-        uint64_t cum = 0;
-        uint32_t cell = 0, q = 1;
-        bound[0] = cell0[0] = 0;
-        for (uint32_t i = 0; i < L; ++i) {
-            while (q < K && cum * K >= (uint64_t)q * total) {
-                bound[q] = i;
-                cell0[q++] = cell;
-            }
-            cum += by_cells ? hits[i] != 0 : hits[i];
-            cell += hits[i] != 0;
-        }
-        for (; q <= K; ++q) {
-            bound[q] = L;
-            cell0[q] = cell;
-        }
-        uint32_t most = 0;
-        for (uint32_t k = 0; k < K; ++k) most = std::max(most, cell0[k + 1] - cell0[k]);
-        if (most <= cap) return true;
-    }
-    return false;
-}
-
 // Tables of the lockstep kernel: the used shared-vector indices as cells, and a copy of the segments with
 // each segment's entries grouped by member and their indices replaced by cells (6 bytes per stored entry).
 // Built once, on first need (synchronises); without the memory, or where the used entries do not fit the
@@ -909,75 +895,66 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     unsigned* hits = nullptr;
     bool own_hits = false;
     if (int r = need_hits(h, &hits, &own_hits, s)) return r == SCD_ERR_OOM ? SCD_OK : r;
-    std::vector<unsigned> hh((size_t)h->L);
-    hipError_t e = hipMemcpyAsync(hh.data(), hits, sizeof(unsigned) * (size_t)h->L, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (own_hits) (void)hipFree(hits);
-    if (e != hipSuccess) return fail(SCD_ERR_HIP, "lockstep hits: %s", hipGetErrorString(e));
     LockArgs t{};
     t.K = (uint32_t)kLockMaxMembers;
     const uint32_t cap = (uint32_t)std::min<size_t>(65535, (h->max_lds - 64) / sizeof(double) - 1);
-    uint32_t bound[kLockMaxMembers + 1];
-    if (!lock_ranges(hh, h->nnz, t.K, cap, bound, t.cell0)) return SCD_OK;
-    std::vector<int32_t> ids;
-    std::vector<uint16_t> cell_of((size_t)h->L, 0);
-    ids.reserve(t.cell0[t.K]);
-    for (uint32_t k = 0; k < t.K; ++k) {
-        t.max_cells = std::max(t.max_cells, t.cell0[k + 1] - t.cell0[k]);
-        for (uint32_t i = bound[k]; i < bound[k + 1]; ++i)
-            if (hh[i]) {
-                cell_of[i] = (uint16_t)(ids.size() - t.cell0[k]);
-                ids.push_back((int32_t)i);
-            }
-    }
-    const size_t nnz = (size_t)h->nnz;
-    std::vector<uint64_t> slots(kLockSlotWords + 1, 0);
-    slots[kLockSlotWords] = 1;  // the first launch's first tag
-    // One allocation for the tables (t.slots, at its start, owns it) and one for the scratch.
+    const size_t nnz = (size_t)h->nnz, max_ids = (size_t)std::min<int64_t>(h->L, (int64_t)t.K * cap);
     auto place = [](size_t& at, size_t bytes) {
         const size_t here = at;
         at += (bytes + 255) / 256 * 256;
         return here;
     };
-    size_t size = 0, scratch_size = 0;
-    const size_t o_slots = place(size, sizeof(uint64_t) * slots.size()), o_ids = place(size, sizeof(int32_t) * ids.size()),
+    // Which index has which cell, from the hits; the entries grouped by range.
+    LockRanges ranges{};
+    size_t scratch_size = 0;
+    const size_t o_blocks = place(scratch_size, sizeof(LockBlock) * lock_blocks(h->L)),
+                 o_ranges = place(scratch_size, sizeof ranges), o_cell = place(scratch_size, sizeof(uint16_t) * (size_t)h->L),
+                 o_cell_ids = place(scratch_size, sizeof(int32_t) * max_ids),
+                 o_grouped = place(scratch_size, sizeof(int32_t) * nnz);
+    SetupScratch scratch;
+    char* base = nullptr;
+    hipError_t e = scratch.get(h, scratch_size);
+    char* const cells = scratch.p;
+    if (e == hipSuccess)
+        e = launch_lock_ranges(hits, h->L, h->nnz, t.K, cap, reinterpret_cast<LockBlock*>(cells + o_blocks),
+                               reinterpret_cast<LockRanges*>(cells + o_ranges), reinterpret_cast<uint16_t*>(cells + o_cell),
+                               reinterpret_cast<int32_t*>(cells + o_cell_ids), s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&ranges, cells + o_ranges, sizeof ranges, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (own_hits) (void)hipFree(hits);
+    const bool fits = e == hipSuccess && ranges.cell0[t.K] <= t.K * cap;
+    for (uint32_t k = 0; k < t.K; ++k) {
+        t.cell0[k + 1] = ranges.cell0[k + 1];
+        t.max_cells = std::max(t.max_cells, t.cell0[k + 1] - t.cell0[k]);
+    }
+    // One allocation for the tables: t.slots, at its start, owns it.
+    size_t size = 0;
+    const size_t o_slots = place(size, sizeof(uint64_t) * (kLockSlotWords + 1)), o_ids = place(size, sizeof(int32_t) * t.cell0[t.K]),
                  o_off = place(size, sizeof(uint32_t) * (size_t)h->C * (t.K + 1)), o_val = place(size, sizeof(float) * nnz),
                  o_idx = place(size, sizeof(uint16_t) * nnz);
-    const size_t o_grouped = place(scratch_size, sizeof(int32_t) * nnz),
-                 o_cell = place(scratch_size, sizeof(uint16_t) * (size_t)h->L), o_bound = place(scratch_size, sizeof bound);
-    char *base = nullptr, *scratch = nullptr;
-    e = hipMalloc(&base, size);
-    if (e == hipSuccess) e = hipMalloc(&scratch, scratch_size);
-    if (e == hipSuccess) {
+    if (fits) e = hipMalloc(&base, size);
+    if (fits && e == hipSuccess) {
         t.slots = reinterpret_cast<uint64_t*>(base + o_slots);
-        int32_t* const d_ids = reinterpret_cast<int32_t*>(base + o_ids);
-        uint32_t* const d_off = reinterpret_cast<uint32_t*>(base + o_off);
-        float* const d_val = reinterpret_cast<float*>(base + o_val);
-        uint16_t* const d_idx = reinterpret_cast<uint16_t*>(base + o_idx);
-        int32_t* const grouped = reinterpret_cast<int32_t*>(scratch + o_grouped);
-        uint16_t* const d_cell = reinterpret_cast<uint16_t*>(scratch + o_cell);
-        uint32_t* const d_bound = reinterpret_cast<uint32_t*>(scratch + o_bound);
-        t.ids = d_ids;
-        t.off = d_off;
-        t.val = d_val;
-        t.idx = d_idx;
-        auto up = [&](void* to, const void* from, size_t bytes) {
-            if (e == hipSuccess) e = hipMemcpyAsync(to, from, bytes, hipMemcpyHostToDevice, s);
-        };
-        up(t.slots, slots.data(), sizeof(uint64_t) * slots.size());
-        up(d_bound, bound, sizeof bound);
-        up(d_ids, ids.data(), sizeof(int32_t) * ids.size());
-        up(d_cell, cell_of.data(), sizeof(uint16_t) * (size_t)h->L);
+        int32_t* const grouped = reinterpret_cast<int32_t*>(cells + o_grouped);
+        uint32_t* const off = reinterpret_cast<uint32_t*>(base + o_off);
+        float* const val = reinterpret_cast<float*>(base + o_val);
+        uint16_t* const idx = reinterpret_cast<uint16_t*>(base + o_idx);
+        t.ids = reinterpret_cast<int32_t*>(base + o_ids);
+        t.off = off;
+        t.val = val;
+        t.idx = idx;
+        const uint32_t* const bound = reinterpret_cast<LockRanges*>(cells + o_ranges)->bound;
+        e = launch_reset_waits(nullptr, t.slots, s);
         if (e == hipSuccess)
-            e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, d_bound, (int)t.K, grouped, d_val, d_off, s);
-        if (e == hipSuccess) e = launch_lock_cells(grouped, h->nnz, d_cell, d_idx, s);
+            e = hipMemcpyAsync(base + o_ids, cells + o_cell_ids, sizeof(int32_t) * t.cell0[t.K], hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess) e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, bound, (int)t.K, grouped, val, off, s);
+        if (e == hipSuccess) e = launch_lock_cells(grouped, h->nnz, reinterpret_cast<uint16_t*>(cells + o_cell), idx, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
-    (void)hipFree(scratch);
-    if (e != hipSuccess) {
+    if (!fits || e != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);
-        return e == hipErrorOutOfMemory ? SCD_OK : fail(SCD_ERR_HIP, "lockstep tables: %s", hipGetErrorString(e));
+        return e == hipSuccess || e == hipErrorOutOfMemory ? SCD_OK : fail(SCD_ERR_HIP, "lockstep tables: %s", hipGetErrorString(e));
     }
     h->lock_args = t;
     static std::atomic<uint32_t> made{0};
@@ -1094,11 +1071,12 @@ int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* di
             }
         }
     }
+    SetupScratch rows_scratch;
     float* rows = nullptr;
-    if (hipMalloc(&rows, sizeof(float) * kProbeRow * (size_t)h->L) != hipSuccess) {
+    if (rows_scratch.get(h, sizeof(float) * kProbeRow * (size_t)h->L) == hipSuccess)
+        rows = reinterpret_cast<float*>(rows_scratch.p);
+    else
         (void)hipGetLastError();
-        rows = nullptr;
-    }
     int rc = SCD_OK;
     auto hip = [&](hipError_t e, const char* what) {
         if (rc == SCD_OK && e != hipSuccess)
@@ -1139,7 +1117,6 @@ int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* di
     }
     hip(hipMemcpyAsync(&bits, dev_bits, sizeof bits, hipMemcpyDeviceToHost, s), "copy kappa");
     hip(hipStreamSynchronize(s), "synchronize");
-    (void)hipFree(rows);
     (void)hipFree(slot_of);
     (void)hipFree(hot_ids);
     if (rc != SCD_OK) return rc;

@@ -341,6 +341,21 @@ struct LockArgs {
     uint32_t spin_limit;   // bounded waits: polls before a wave gives up and sets *err
     int* err;
 };
+// Index ranges and cells of the members, from the hits.
+struct LockRanges {
+    uint32_t bound[kLockMaxMembers + 1];  // member k holds indices [bound[k], bound[k + 1])
+    uint32_t cell0[kLockMaxMembers + 1];  // as in LockArgs; cell0[K] above K cap: they do not fit, and no cells are given
+    uint32_t cut_bound[2][kLockMaxMembers + 1], cut_cell[2][kLockMaxMembers + 1];  // working values
+};
+struct LockBlock {   // of kHotAssignBlock indices: their sums, then the sums before them
+    uint64_t entries;
+    uint32_t used, pad;
+};
+inline int64_t lock_blocks(int64_t L) { return (L + kHotAssignBlock - 1) / kHotAssignBlock; }
+// Cuts the used indices into K runs of about equal entry count, or, where a run would exceed `cap` cells, of equal
+// cell count: *r, cell_of[L] (within the range) and ids[cell0[K]].  L is at most 1,024 kHotAssignBlock.
+hipError_t launch_lock_ranges(const unsigned* hits, int64_t L, int64_t nnz, uint32_t K, uint32_t cap, LockBlock* blocks,
+                              LockRanges* r, uint16_t* cell_of, int32_t* ids, hipStream_t s);
 inline size_t lock_lds_bytes(uint32_t max_cells) { return sizeof(double) * ((size_t)max_cells + 1); }  // beside 8 static
 hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s);
 hipError_t launch_lock_cells(const int32_t* idx, int64_t nnz, const uint16_t* cell_of, uint16_t* out, hipStream_t s);
@@ -446,7 +461,7 @@ hipError_t launch_sum_partials(const double* partials, int nparts, int width, do
 hipError_t launch_objective(int form, const ObjArgs& o, int G, int blocks, int cus, double* partials, double* sums,
                             hipStream_t s);
 hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s);
-// *err = 0 and, with slots, the lockstep exchange as it is at first (LockArgs::slots).
+// With err, *err = 0; with slots, the lockstep exchange as it is at first (LockArgs::slots).
 hipError_t launch_reset_waits(int* err, uint64_t* slots, hipStream_t s);
 // Sets the calling thread's message returned by scd_last_error.
 void set_last_error(const char* msg);

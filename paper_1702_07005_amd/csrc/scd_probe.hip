@@ -297,9 +297,12 @@ static hipError_t probe_scatter_typed(const ProbeArgs& a, int cus, hipStream_t s
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    const int64_t want = ((int64_t)a.C * G + 1023) / 1024;
-    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)cus * (a.n_hot ? 1 : 2)));
-    hipLaunchKernelGGL((k_probe_scatter<G, NP>), dim3(blocks), dim3(1024), lds, s, a);
+    // Sixteen waves share a workgroup's slots; without slots small workgroups spread few segments over more
+    // CUs (600 columns of 4,000: 38 CUs and 150).
+    const int threads = a.n_hot ? 1024 : 256, per_cu = a.n_hot ? 1 : 8;
+    const int64_t want = ((int64_t)a.C * G + threads - 1) / threads;
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)cus * per_cu));
+    hipLaunchKernelGGL((k_probe_scatter<G, NP>), dim3(blocks), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 

@@ -467,7 +467,7 @@ hipError_t launch_fill_zero(uint64_t* p, uint32_t n_words, hipStream_t s) {
 }
 
 __global__ __launch_bounds__(256) void k_reset_waits(int* __restrict__ err, uint64_t* __restrict__ slots) {
-    if (threadIdx.x == 0) *err = 0;
+    if (err && threadIdx.x == 0) *err = 0;
     if (slots)
         for (int i = threadIdx.x; i <= kLockSlotWords; i += 256) slots[i] = i == kLockSlotWords ? 1ull : 0ull;
 }

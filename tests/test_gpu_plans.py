@@ -562,6 +562,38 @@ def test_lockstep_selection():
         s.close()
 
 
+@pytest.mark.parametrize("n,L,common,seed", [(64, 1_025, 60, 1), (96, 60_007, 200, 2), (270, 111_000, 300, 3), (250, 300_001, 0, 4)])
+def test_lockstep_ranges_and_cells(n, L, common, seed):
+    # The members' index ranges come from the hits: cut where the entries are about equal, or, where
+    # that exceeds a member's LDS (seed 3: 23,625 entries a member, most of an index of their own), where the cells are.  A cell given twice or to the wrong member breaks the invariant at its indices.
+    rng = np.random.default_rng(seed)
+    per = 700 if seed == 3 else 450
+    own = (L - common) // n if seed == 3 else 0
+    idx = []
+    for r in range(n):
+        a = np.arange(common)
+        m = per - common
+        if own:  # every other index belongs to one row only
+            b = common + r * own + rng.choice(own, min(own, m), replace=False)
+        else:
+            b = common + rng.choice(L - common - 3, m, replace=False)  # the last indices unused
+        idx.append(np.sort(np.concatenate([a, b])))
+    lens = np.array([len(i) for i in idx])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    val = (rng.standard_normal(int(ptr[-1])) / np.sqrt(per)).astype(np.float32)
+    p = synth.Problem("ranges", "ridge_dual", "csr", n, L, ptr, np.concatenate(idx).astype(np.int32), val,
+                      rng.standard_normal(n).astype(np.float32), 1 / n, 0)
+    s = scd.solver_for(p)
+    i = s.info()
+    print(f"{n} x {L}: auto window {i['auto_window']} window {i['window']} used {len(np.unique(p.idx))}", flush=True)
+    assert _lockstep(s)
+    follow_oracle(p, s, 4)
+    # every index some entry points at takes part, and no other changes
+    gs = f64(s.get_state()[1])
+    assert np.all(gs[np.setdiff1d(np.arange(L), p.idx)] == 0.0) and np.mean(gs[np.unique(p.idx)] != 0.0) > 0.999
+    s.close()
+
+
 def test_lockstep_limits_on_the_entries_in_flight():
     # 24,576 entries in flight while the copy takes at most 2.5 MB (6 bytes an entry), else 12,288
     for rows, cols in ((2_000, 208), (2_000, 209), (2_500, 375), (6_000, 100)):
