@@ -396,6 +396,26 @@ bool lock_wanted(const scd_solver* h) {
     return in_flight <= (h->nnz * 6 <= kLockMaxL2Bytes ? kLockMaxInFlightL2 : kLockMaxInFlight);
 }
 
+// A round lasts as long as its slowest wave, and what a part has beyond the slices in registers is streamed by one
+// wave of one member while all others wait (about 0.35 us for each 64 entries).  With four slices while the
+// longest part of a round, on average over the epoch's random rounds, has at most half a slice more; with eight
+// while it has at most half a slice more than that, or than a mean segment cut evenly has (dense columns beyond 4,096
+// entries: all parts alike).  Else the kernel does not pay.  1,000 rows, pipelined / lockstep with four / with
+// eight slices, ms an epoch: 300 of 330 entries in one range 0.319 / 0.322 / 0.240, 350 of 400 0.397 / 0.315 / 0.265,
+// 480 of 500 0.397 / 0.559 / 0.340, 570 of 700 0.397 / 0.667 / 0.457; a tenth of the rows 4,000 long, evenly
+// spread, among 330 0.310 / 0.339 / 0.269; 250 of 300 in one range, or 700 evenly spread 0.397 / 0.238 / 0.253 and
+// 0.302 / 0.193 / 0.210.
+constexpr double kLockMaxExcess = 0.5;
+double lock_mean_excess(const uint32_t (&bins)[kLockExcessBins], double C, double W) {
+    double at_least = 0.0, mean = 0.0;
+    for (int b = kLockExcessBins - 1; b >= 0; --b) {
+        at_least += bins[b];
+        // Each bin counts at its upper end, 2^(b + 1) - 1: 2^b more than the bin below.
+        mean += std::ldexp(1.0, b) * (1.0 - std::pow(1.0 - at_least / C, W));
+    }
+    return mean;
+}
+
 uint32_t split_part_len(const scd_solver* h) { return h->split_part ? (uint32_t)h->split_part : kSplitMaxPart; }
 
 // The split kernel's limits: at most kSplitMaxParts parts per segment, fewer than 2^32 units per epoch
@@ -888,7 +908,7 @@ void free_lock_tables(scd_solver* h) {
 // Tables of the lockstep kernel: the used shared-vector indices as cells, and a copy of the segments with
 // each segment's entries grouped by member and their indices replaced by cells (6 bytes per stored entry).
 // Built once, on first need (synchronises); without the memory, or where the used entries do not fit the
-// members' LDS, the pipelined kernel runs instead.
+// members' LDS or the segments fall too unevenly over the ranges, the pipelined kernel runs instead.
 int build_lock_tables(scd_solver* h, hipStream_t s) {
     h->lock_state = -1;
     if (h->nnz == 0 || h->max_seg >= (int64_t(1) << 32)) return SCD_OK;
@@ -906,10 +926,12 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     };
     // Which index has which cell, from the hits; the entries grouped by range.
     LockRanges ranges{};
+    LockExcess excess{};
     size_t scratch_size = 0;
     const size_t o_blocks = place(scratch_size, sizeof(LockBlock) * lock_blocks(h->L)),
                  o_ranges = place(scratch_size, sizeof ranges), o_cell = place(scratch_size, sizeof(uint16_t) * (size_t)h->L),
                  o_cell_ids = place(scratch_size, sizeof(int32_t) * max_ids),
+                 o_excess = place(scratch_size, sizeof(LockExcess)),
                  o_grouped = place(scratch_size, sizeof(int32_t) * nnz);
     SetupScratch scratch;
     char* base = nullptr;
@@ -948,10 +970,21 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
         if (e == hipSuccess)
             e = hipMemcpyAsync(base + o_ids, cells + o_cell_ids, sizeof(int32_t) * t.cell0[t.K], hipMemcpyDeviceToDevice, s);
         if (e == hipSuccess) e = launch_team_partition(h->ptr, h->idx, h->val, (uint32_t)h->C, bound, (int)t.K, grouped, val, off, s);
+        LockExcess* const d_excess = reinterpret_cast<LockExcess*>(cells + o_excess);
+        const double even = std::ceil((double)h->nnz / (double)h->C / t.K / 64.0);
+        const uint32_t slices[2] = {(uint32_t)kLockSlices, std::max<uint32_t>(kLockSlicesLong, (uint32_t)even)};
+        if (e == hipSuccess) e = launch_lock_excess(off, (uint32_t)h->C, t.K, slices, d_excess, s);
         if (e == hipSuccess) e = launch_lock_cells(grouped, h->nnz, reinterpret_cast<uint16_t*>(cells + o_cell), idx, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&excess, d_excess, sizeof excess, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
-    if (!fits || e != hipSuccess) {
+    bool pays = false;
+    for (int v = 1; v >= 0; --v)
+        if (lock_mean_excess(excess.n[v], (double)h->C, (double)h->auto_window) <= kLockMaxExcess) {
+            pays = true;
+            t.slices = (uint32_t)(v ? kLockSlicesLong : kLockSlices);
+        }
+    if (!fits || !pays || e != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);
         return e == hipSuccess || e == hipErrorOutOfMemory ? SCD_OK : fail(SCD_ERR_HIP, "lockstep tables: %s", hipGetErrorString(e));

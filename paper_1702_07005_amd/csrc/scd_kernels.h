@@ -325,6 +325,8 @@ hipError_t launch_team_partition(const int64_t* ptr, const int32_t* idx, const f
 // Lockstep epoch: rounds of W coordinates, one per wave, over K workgroups of one XCD that hold the shared
 // vector in LDS, each its index range (see scd_lock.hip).
 constexpr int kLockMaxWindow = 16;   // waves per workgroup at most
+// Entries per lane held in registers: parts of up to 256 entries, or of up to 512 (LockArgs::slices).
+constexpr int kLockSlices = 4, kLockSlicesLong = 8;
 constexpr int kLockMaxMembers = 8;
 constexpr int kLockSlotWords = 2 * kLockMaxWindow * kLockMaxMembers;
 struct LockArgs {
@@ -338,6 +340,7 @@ struct LockArgs {
     uint64_t* slots;       // [kLockSlotWords + 1]: zero at first; the last word is the next launch's first tag,
                            // 1 at first
     uint32_t K, W, xcd;
+    uint32_t slices;       // kLockSlices or kLockSlicesLong
     uint32_t spin_limit;   // bounded waits: polls before a wave gives up and sets *err
     int* err;
 };
@@ -356,6 +359,14 @@ inline int64_t lock_blocks(int64_t L) { return (L + kHotAssignBlock - 1) / kHotA
 // cell count: *r, cell_of[L] (within the range) and ids[cell0[K]].  L is at most 1,024 kHotAssignBlock.
 hipError_t launch_lock_ranges(const unsigned* hits, int64_t L, int64_t nnz, uint32_t K, uint32_t cap, LockBlock* blocks,
                               LockRanges* r, uint16_t* cell_of, int32_t* ids, hipStream_t s);
+// excess->n[v][b] = coordinates whose largest part takes 2^b to 2^(b + 1) - 1 more slices of 64 entries than
+// base[v] (zeroed here).
+constexpr int kLockExcessBins = 32;
+struct LockExcess {
+    uint32_t n[2][kLockExcessBins];
+};
+hipError_t launch_lock_excess(const uint32_t* off, uint32_t C, uint32_t K, const uint32_t (&base)[2], LockExcess* excess,
+                              hipStream_t s);
 inline size_t lock_lds_bytes(uint32_t max_cells) { return sizeof(double) * ((size_t)max_cells + 1); }  // beside 8 static
 hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s);
 hipError_t launch_lock_cells(const int32_t* idx, int64_t nnz, const uint16_t* cell_of, uint16_t* out, hipStream_t s);

@@ -42,13 +42,18 @@
 // (7 and 9 in flight) 55 and 46 us; 500 x 60 dense (2 and 3) 49 and 31 us; text rows of 370 entries on 166,000
 // columns (6 and 8) 1.22 and 0.68 ms; of 809 on 127,000 (4 and 6) 2.16 and 0.69 ms.  A round takes 1.5-2 us: the
 // exchange, the loads that its wait covers, and the LDS reads and adds of up to four slices a wave.
+//
+// S slices of 64 entries of a part stay in registers; what is beyond is streamed twice, loads and LDS in turn.
+// Four take parts of 256 entries, eight of 512, at 10% more time where the parts are short (2,000 x 200 dense 42.5
+// and 47.4 us an epoch, text rows of 370 0.583 and 0.647 ms) and less where they are long (4,000 x 100 dense, parts of
+// 500, 53.0 and 45.1 us; 1,000 rows of 450 with 370 in one range 0.564 and 0.466 ms); scd_create chooses by the parts.
+#include <algorithm>
+
 #include "scd_device.h"
 #include "scd_kernels.h"
 
 namespace scd {
 namespace {
-
-constexpr int kLockSlices = 4;  // entries per lane held in registers: parts of up to 256 entries
 
 struct LockMeta {
     int64_t base;
@@ -74,13 +79,14 @@ __device__ __forceinline__ LockMeta lock_meta(const LockArgs& t, uint64_t j, uin
     return c;
 }
 
-// The first 64 * kLockSlices entries of the part; lanes past its end hold `none`, a cell of value 0 behind the
+// The first 64 S entries of the part; lanes past its end hold `none`, a cell of value 0 behind the
 // member's own (any of those may hold an infinity, which would make the sums of other coordinates NaN).
+template <int S>
 __device__ __forceinline__ void lock_load(const LockArgs& t, const LockMeta& c, uint32_t lane, uint32_t none,
-                                          uint32_t (&ci)[kLockSlices], float (&cv)[kLockSlices]) {
+                                          uint32_t (&ci)[S], float (&cv)[S]) {
     const uint32_t len = c.o1 - c.o0;
 #pragma unroll
-    for (int r = 0; r < kLockSlices; ++r) {
+    for (int r = 0; r < S; ++r) {
         const uint32_t i = lane + 64u * (uint32_t)r;
         ci[r] = none;
         cv[r] = 0.0f;
@@ -91,7 +97,7 @@ __device__ __forceinline__ void lock_load(const LockArgs& t, const LockMeta& c, 
     }
 }
 
-template <int FORM, typename U>
+template <int FORM, typename U, int S>
 __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) {
     extern __shared__ __align__(16) unsigned char lock_lds[];
     __shared__ int gave_up[2];
@@ -115,8 +121,8 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
     // hold it up, and the waves that poll for it hold up each other: 0.68 -> 2.1 ms an epoch on the text
     // rows, 46 -> 137 us on the dense columns.
     LockMeta cur = lock_meta(t, wave, k), nxt = lock_meta(t, (uint64_t)wave + W, k);
-    uint32_t ci[kLockSlices];
-    float cv[kLockSlices];
+    uint32_t ci[S];
+    float cv[S];
     lock_load(t, cur, lane, n_cells, ci, cv);
     uint64_t* const base_tag = t.slots + kLockSlotWords;
     const uint32_t tag0 = (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -131,9 +137,9 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
         const int64_t at = cur.base + cur.o0;
         float acc = 0.0f;
 #pragma unroll
-        for (int q = 0; q < kLockSlices; ++q)
+        for (int q = 0; q < S; ++q)
             if (64u * (uint32_t)q < len) acc = fmaf(cv[q], (float)cells[ci[q]], acc);
-        for (uint32_t i = 64u * kLockSlices + lane; i < len; i += 64u) acc = fmaf(t.val[at + i], (float)cells[t.idx[at + i]], acc);
+        for (uint32_t i = 64u * S + lane; i < len; i += 64u) acc = fmaf(t.val[at + i], (float)cells[t.idx[at + i]], acc);
         if (left) break;
         // (Past the last position, in the last round, a wave goes through the motions on its stand-in.)
         const float p = group_sum<64>(acc);
@@ -142,8 +148,8 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
             __hip_atomic_store(slot + k, ((uint64_t)tag << 32) | (uint64_t)__float_as_uint(p), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_sched_barrier(0);
-        uint32_t ni[kLockSlices];
-        float nv[kLockSlices];
+        uint32_t ni[S];
+        float nv[S];
         lock_load(t, nxt, lane, n_cells, ni, nv);
         const LockMeta nn = lock_meta(t, (uint64_t)j + 2ull * W, k);
         __builtin_amdgcn_sched_barrier(0);
@@ -171,14 +177,14 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
         const float m_new = coord_step<FORM>(g, cur.sn, cur.m_old, cur.ylab, a.k, &coef);
         if (j < n && coef != 0.0f) {
 #pragma unroll
-            for (int q = 0; q < kLockSlices; ++q)
+            for (int q = 0; q < S; ++q)
                 if (64u * (uint32_t)q < len && lane + 64u * (uint32_t)q < len) atomicAdd(cells + ci[q], (double)(coef * cv[q]));
-            for (uint32_t i = 64u * kLockSlices + lane; i < len; i += 64u)
+            for (uint32_t i = 64u * S + lane; i < len; i += 64u)
                 atomicAdd(cells + t.idx[at + i], (double)(coef * t.val[at + i]));
         }
         if (lane == 0 && j < n && j % t.K == k) a.model[cur.m] = m_new;
 #pragma unroll
-        for (int q = 0; q < kLockSlices; ++q) {
+        for (int q = 0; q < S; ++q) {
             ci[q] = ni[q];
             cv[q] = nv[q];
         }
@@ -195,13 +201,13 @@ __global__ __launch_bounds__(64 * kLockMaxWindow) void k_epoch_lock(LockArgs t) 
     for (uint32_t i = threadIdx.x; i < n_cells; i += blockDim.x) u[t.ids[cell0 + i]] = (U)cells[i];
 }
 
-template <int FORM, typename U>
+template <int FORM, typename U, int S>
 hipError_t launch_lock_typed(const LockArgs& t, hipStream_t s) {
     const size_t lds = lock_lds_bytes(t.max_cells);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_epoch_lock<FORM, U>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_epoch_lock<FORM, U, S>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_epoch_lock<FORM, U>), dim3(t.K * kTeamXcds), dim3(64 * t.W), lds, s, t);
+    hipLaunchKernelGGL((k_epoch_lock<FORM, U, S>), dim3(t.K * kTeamXcds), dim3(64 * t.W), lds, s, t);
     return hipGetLastError();
 }
 
@@ -329,6 +335,24 @@ __global__ __launch_bounds__(kRangeThreads) void k_lock_assign(const unsigned* _
     }
 }
 
+__global__ __launch_bounds__(256) void k_lock_excess(const uint32_t* __restrict__ off, uint32_t C, uint32_t K, uint32_t base0,
+                                                     uint32_t base1, LockExcess* __restrict__ excess) {
+    __shared__ uint32_t h[2 * kLockExcessBins];
+    uint32_t* const out = excess->n[0];
+    if (threadIdx.x < 2 * kLockExcessBins) h[threadIdx.x] = 0u;
+    __syncthreads();
+    for (uint64_t c = blockIdx.x * 256u + threadIdx.x; c < C; c += (uint64_t)gridDim.x * 256u) {
+        const uint32_t* o = off + c * (K + 1);
+        uint32_t most = 0;
+        for (uint32_t k = 0; k < K; ++k) most = max(most, o[k + 1] - o[k]);
+        const uint32_t slices = most / 64u + (most % 64u != 0u);
+        if (slices > base0) atomicAdd(h + (31 - __clz((int)(slices - base0))), 1u);
+        if (slices > base1) atomicAdd(h + kLockExcessBins + (31 - __clz((int)(slices - base1))), 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kLockExcessBins && h[threadIdx.x]) atomicAdd(out + threadIdx.x, h[threadIdx.x]);
+}
+
 // Cell of every stored entry of the grouped copy: cell_of[index] within its range.
 __global__ __launch_bounds__(256) void k_lock_cells(const int32_t* __restrict__ idx, int64_t nnz,
                                                     const uint16_t* __restrict__ cell_of, uint16_t* __restrict__ out) {
@@ -338,16 +362,21 @@ __global__ __launch_bounds__(256) void k_lock_cells(const int32_t* __restrict__ 
 
 }  // namespace
 
+template <int FORM>
+static hipError_t launch_lock_form(bool wide, const LockArgs& t, hipStream_t s) {
+    if (t.slices == (uint32_t)kLockSlicesLong)
+        return wide ? launch_lock_typed<FORM, double, kLockSlicesLong>(t, s) : launch_lock_typed<FORM, float, kLockSlicesLong>(t, s);
+    return wide ? launch_lock_typed<FORM, double, kLockSlices>(t, s) : launch_lock_typed<FORM, float, kLockSlices>(t, s);
+}
+
 hipError_t launch_epoch_lock(int form, bool wide, const LockArgs& t, hipStream_t s) {
-    if (t.K < 1 || t.K > (uint32_t)kLockMaxMembers || t.W < 1 || t.W > (uint32_t)kLockMaxWindow || t.xcd >= kTeamXcds)
+    if (t.K < 1 || t.K > (uint32_t)kLockMaxMembers || t.W < 1 || t.W > (uint32_t)kLockMaxWindow || t.xcd >= kTeamXcds ||
+        (t.slices != (uint32_t)kLockSlices && t.slices != (uint32_t)kLockSlicesLong))
         return hipErrorInvalidValue;
     switch (form) {
-        case FORM_RIDGE_PRIMAL:
-            return wide ? launch_lock_typed<FORM_RIDGE_PRIMAL, double>(t, s) : launch_lock_typed<FORM_RIDGE_PRIMAL, float>(t, s);
-        case FORM_SVM_DUAL:
-            return wide ? launch_lock_typed<FORM_SVM_DUAL, double>(t, s) : launch_lock_typed<FORM_SVM_DUAL, float>(t, s);
-        case FORM_RIDGE_DUAL:
-            return wide ? launch_lock_typed<FORM_RIDGE_DUAL, double>(t, s) : launch_lock_typed<FORM_RIDGE_DUAL, float>(t, s);
+        case FORM_RIDGE_PRIMAL: return launch_lock_form<FORM_RIDGE_PRIMAL>(wide, t, s);
+        case FORM_SVM_DUAL: return launch_lock_form<FORM_SVM_DUAL>(wide, t, s);
+        case FORM_RIDGE_DUAL: return launch_lock_form<FORM_RIDGE_DUAL>(wide, t, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -361,6 +390,14 @@ hipError_t launch_lock_ranges(const unsigned* hits, int64_t L, int64_t nnz, uint
     hipLaunchKernelGGL(k_lock_block_scan, dim3(1), dim3(1024), 0, s, blocks, (uint32_t)nb, K, (uint32_t)L, r);
     hipLaunchKernelGGL(k_lock_cuts, grid, threads, 0, s, hits, L, (uint64_t)nnz, K, blocks, r);
     hipLaunchKernelGGL(k_lock_assign, grid, threads, 0, s, hits, L, K, cap, blocks, r, cell_of, ids);
+    return hipGetLastError();
+}
+
+hipError_t launch_lock_excess(const uint32_t* off, uint32_t C, uint32_t K, const uint32_t (&base)[2], LockExcess* excess,
+                              hipStream_t s) {
+    static_assert(sizeof(LockExcess) == 8 * kLockExcessBins, "whole 64-bit words");
+    if (const hipError_t e = launch_fill_zero(reinterpret_cast<uint64_t*>(excess), kLockExcessBins, s); e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lock_excess, dim3(std::min(grid_for(C), 256u)), dim3(256), 0, s, off, C, K, base[0], base[1], excess);
     return hipGetLastError();
 }
 

@@ -574,7 +574,7 @@ def test_lockstep_ranges_and_cells(n, L, common, seed):
         a = np.arange(common)
         m = per - common
         if own:  # every other index belongs to one row only
-            b = common + r * own + rng.choice(own, min(own, m), replace=False)
+            b = common + r + n * rng.choice(own, m, replace=False)
         else:
             b = common + rng.choice(L - common - 3, m, replace=False)  # the last indices unused
         idx.append(np.sort(np.concatenate([a, b])))
@@ -591,6 +591,32 @@ def test_lockstep_ranges_and_cells(n, L, common, seed):
     # every index some entry points at takes part, and no other changes
     gs = f64(s.get_state()[1])
     assert np.all(gs[np.setdiff1d(np.arange(L), p.idx)] == 0.0) and np.mean(gs[np.unique(p.idx)] != 0.0) > 0.999
+    s.close()
+
+
+@pytest.mark.parametrize("case,lockstep", [("even", True), ("half_range", True), ("one_range", False), ("few_long", True),
+                                           ("many_long", True), ("long", False)])
+def test_lockstep_of_uneven_parts(case, lockstep):
+    # Parts of up to 256 and of up to 512 entries stay in registers.  Beyond, the longest part of a round holds
+    # up the others: rows that lie in one of the eight index ranges, and long rows among short ones, keep the
+    # pipelined kernel; a few do not matter.  (250 weakly coupled rows: a window of 250 / 16.)
+    rng = np.random.default_rng(21)
+    n, L = 250, 60_000
+    tenth = rng.random(n) < 0.1
+    per, span = {"even": (700, L), "half_range": (500, 520), "one_range": (700, 800), "few_long": (330, L),
+                 "many_long": (np.where(tenth, 3_000, 330), L), "long": (np.where(tenth, 6_000, 330), L)}[case]
+    lens = np.broadcast_to(per, n).copy()
+    if case == "few_long":
+        lens[100] = 1_500
+    idx = np.concatenate([np.sort(rng.integers(0, L - span + 1) + rng.choice(span, m, replace=False)) for m in lens])
+    val = (rng.standard_normal(len(idx)) / np.sqrt(np.repeat(lens, lens))).astype(np.float32)
+    p = synth.Problem("uneven", "ridge_dual", "csr", n, L, np.concatenate([[0], np.cumsum(lens)]).astype(np.int64),
+                      idx.astype(np.int32), val, rng.standard_normal(n).astype(np.float32), 1 / n, 0)
+    s = scd.solver_for(p)
+    i = s.info()
+    print(f"{case}: auto window {i['auto_window']} window {i['window']} entries {p.nnz}", flush=True)
+    assert i["auto_window"] == 15 and i["kernel"] == "pipelined" and _lockstep(s) == lockstep
+    follow_oracle(p, s, 4)
     s.close()
 
 
