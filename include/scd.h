@@ -217,7 +217,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 automatic window of 2 to 16, "group", "fresh_reads" 0, "team" 1, and a shared vector
  *                 whose used entries (those some stored entry points at; at most 1 M entries in all) fit
  *                 the LDS of eight workgroups as fp64 (about 160,000), and auto_window segments of at most
- *                 12,288 entries together on average (24,576 up to 416,666 stored entries), and segments that
+ *                 12,288 entries together on average (24,576 up to 416,666 stored entries), (auto_window - 1) x coherence
+ *                 (below) at most 0.1, and segments that
  *                 spread over eight ranges of about equal entry count (a segment with more than 512 entries, and more
  *                 than an eighth of the mean length, in one of them holds up its round: at most half a step of 64
  *                 entries on average), run the epoch in

@@ -383,6 +383,14 @@ int team_members(const scd_solver* h, int64_t* teams) {
 // times faster, all of 14); dense 2,000 x 200, 18,000 to 22,000 in flight, 2.4 MB: 0.055 and 0.046; 2,000 x 300,
 // 22,000 in flight, 3.6 MB: 0.079 and 0.083; 2,500 x 375, 35,000 in flight, 5.6 MB: 0.072 and 0.092;
 // 4,000 x 600, 64,000 in flight: 0.106 and 0.171.
+//
+// A round's coordinates all step from the state before the round.  Where they pull the same way (a positive mean
+// off-diagonal entry of G, as positive values give), that overshoots more than the draining groups do, which take
+// 4/5 of the window, rounded down, and do not run in step.  Worst ratio to the sequential gap over 6 epochs and 4
+// seeds, lockstep and pipelined, by (W - 1) x coherence: up to 0.1 at most 1.72 and 1.62; 0.118 (W = 2, which leaves
+// the pipelined kernel one group) 2.23 and 1.00; 0.17 2.11 and 1.46; 0.27 2.45 and 1.64; 0.32 3.86 and 2.00; 0.53 7.95 and
+// 3.89.  Beyond 0.1 the pipelined kernel keeps the epoch.
+constexpr double kLockMaxCoherent = 0.1;
 constexpr int64_t kLockMaxShared = int64_t(1) << 20;
 constexpr double kLockMaxInFlight = 12288.0;
 constexpr double kLockMaxInFlightL2 = 24576.0;  // with a copy of at most kLockMaxL2Bytes
@@ -390,7 +398,8 @@ constexpr int64_t kLockMaxL2Bytes = 2500000;
 bool lock_wanted(const scd_solver* h) {
     if (!h->lockstep || h->window != 0 || h->group != 0 || h->fresh || !h->pipeline || h->team != 1 || h->auto_window < 2 ||
         h->auto_window > kLockMaxWindow || h->auto_window >= h->C || h->L > kLockMaxShared ||
-        auto_group(h) != kBlockThreads || h->cus < (int)kTeamXcds * kLockMaxMembers)
+        auto_group(h) != kBlockThreads || h->cus < (int)kTeamXcds * kLockMaxMembers ||
+        (double)(h->auto_window - 1) * h->coherence > kLockMaxCoherent)
         return false;
     const double in_flight = (double)h->auto_window * ((double)h->nnz / (double)h->C);
     return in_flight <= (h->nnz * 6 <= kLockMaxL2Bytes ? kLockMaxInFlightL2 : kLockMaxInFlight);

@@ -17,8 +17,9 @@
 //   4. a workgroup barrier, after which every wave of the member gathers the next round.
 //
 // A coordinate misses the updates of the W - 1 others of its round at most, and of those only the ones
-// before it in the visiting order are ones the sequential algorithm would have seen: on average half as many
-// as the draining kernels' coordinates miss at the same window, so W is the automatic window itself.
+// before it in the visiting order are ones the sequential algorithm would have seen, so W is the automatic window
+// itself.  (The steps of a round are taken from one state: not for coordinates that mostly pull the same way, see
+// the plan's rule.)
 //
 // Slots: (tag mod 2, wave, member).  A wave overwrites its slot of round g at round g + 2, after it has seen
 // every member's partial of round g + 1, which each publishes only after it has read all of round g.  Each
