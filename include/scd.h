@@ -236,7 +236,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 entries.  It does so when the window does not bind (every coordinate may be in
  *                 flight), and with a binding window when the coordinates in flight hold at least
  *                 4,096 entries (65,536 with a workgroup per coordinate), a segment has at most one entry per 32 of the shared vector on
- *                 average, and there are at least two stored entries per shared-vector entry;
+ *                 average, there are at least two stored entries per shared-vector entry, and a segment's entries
+ *                 lie apart (on average 0.47 or more of the packed vector's 64-byte lines per entry, 0.7 in fp64);
  *                 0 = it runs on the packed vector.
  *   "queue_chunk" consecutive permutation positions each workgroup of the queued kernel claims
  *                 at a time: 0 (default) = 1 per 64 coordinates in flight (at least 1), else
@@ -311,9 +312,9 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 The state calls exchange fp32 copies either way.
  * Errors: SCD_ERR_UNSUPPORTED for an unknown key, SCD_ERR_INVALID for a bad value. */
 int scd_set_option(scd_handle_t h, const char *key, int64_t value);
-/* Reads an option's value, or the read-only key "next_window": the coordinates the next epoch will
+/* Reads an option's value, or a read-only key: "next_window", the coordinates the next epoch will
  * keep in flight at most (with an adaptive window, the value the last epoch left in device memory;
- * this read synchronises the device). */
+ * this read synchronises the device); "next_spread", 1 if the next scd_epochs runs on the spread copy. */
 int scd_get_option(scd_handle_t h, const char *key, int64_t *value);
 
 int scd_get_info(scd_handle_t h, scd_info_t *info);

@@ -152,6 +152,7 @@ struct scd_solver {
     int64_t fresh = 0;
     int64_t pipeline = 1;
     int64_t queue_chunk = 0;  // option: positions per queue claim, 0 = by window
+    double lines = 1.0, lines_wide = 1.0;  // 64-byte lines per entry of a segment, fp32 and fp64 (spread_possible)
     int64_t spread = 1;       // option: run an unbound pipelined plan on the spread copy
     void* us = nullptr;       // spread copy of the shared vector (entry i at byte i << kSpreadShift),
                               // allocated at create when it takes at most kSpreadMaxBytes
@@ -284,15 +285,25 @@ int64_t pipe_groups(const scd_solver* h, int64_t window, int64_t groups) {
 // each are bound by latency until more are in flight: text rows of 370 entries on 166,000 columns, 6 in
 // flight 1.22 and 1.23 ms, 100 in flight 0.256 and 0.248, of 809 entries at about 6 1.09 and 1.13, of 2,038
 // at about 10 7.35 and 7.51; columns of 1,000 entries on 100,000 rows, 100 in flight 5.6 and 3.0.  Not where a
-// segment holds neighbouring entries (2,000 x 200 dense: 47 and 107 us at 8 in flight): it would touch
-// one 64-byte segment per entry instead of one per 16.  Nor where the copies in and out (64 bytes per
+// segment holds neighbouring entries (2,000 x 200 dense: 47 and 107 us at 8 in flight): packed, they share
+// 64-byte lines, which the spread copy has one of per entry.  The share of lines to entries decides (counted on a
+// sample of the segments, whatever order they are stored in); columns of 96 entries on 100,000 rows in runs of
+// neighbours, packed and spread at 632 in flight, fp32: runs of 1 0.52 and 0.25 ms, 2 (half as many lines) 0.28 and
+// 0.24, 3 0.20 and 0.25, 8 0.10 and 0.25, 96 0.072 and 0.241; fp64, whose packed gathers and atomics wait less:
+// 1 0.42 and 0.27, 2 0.23 and 0.26, 3 0.18 and 0.27.  Nor where the copies in and out (64 bytes per
 // entry, 4.4 us each way at 100,000) could take longer than the gathers they save.
 constexpr double kSpreadMinInFlight = 4096.0;  // entries of the coordinates in flight,
 constexpr double kSpreadMinInFlightBlock = 65536.0;  // with a workgroup per coordinate
+constexpr double kSpreadMinLines = 0.47, kSpreadMinLinesWide = 0.7;  // lines per entry, fp32 and fp64
+// What does not depend on the options: the lines are counted where this holds.
+bool spread_possible(const scd_solver* h) {
+    return h->us && h->C > 0 && (double)h->nnz / (double)h->C * 32.0 <= (double)h->L && h->nnz >= 2 * h->L;
+}
 bool spread_pays(const scd_solver* h, int64_t window, int64_t groups, int G) {
     if (window >= h->C) return true;
     const double mean = (double)h->nnz / (double)h->C;
-    return (double)groups * mean >= (G == kBlockThreads ? kSpreadMinInFlightBlock : kSpreadMinInFlight) && mean * 32.0 <= (double)h->L && h->nnz >= 2 * h->L;
+    return spread_possible(h) && (double)groups * mean >= (G == kBlockThreads ? kSpreadMinInFlightBlock : kSpreadMinInFlight) &&
+           (h->wide ? h->lines_wide >= kSpreadMinLinesWide : h->lines >= kSpreadMinLines);
 }
 
 // Lanes per coordinate of a pipelined plan whose window binds: wider groups than the segment length
@@ -1410,10 +1421,20 @@ int scd_create(const scd_matrix_t* A, const float* y, double lambda, int32_t for
         hip(launch_norms(h->ptr, h->idx, h->val, formulation == SCD_RIDGE_PRIMAL ? h->y : nullptr, (uint32_t)h->C,
                          G, obj_blocks(h, G), h->norms, h->cy, h->cyd, s),
             "norms");
+        // How local the segments are; the probe below synchronises.
+        uint32_t* const line_counts = reinterpret_cast<uint32_t*>(h->host_sums + 4);
+        if (rc == SCD_OK && spread_possible(h)) {
+            hip(launch_lines(h->ptr, h->idx, (uint32_t)h->C, reinterpret_cast<uint32_t*>(h->sums + 4), s), "lines");
+            hip(hipMemcpyAsync(line_counts, h->sums + 4, kLineWords * sizeof(uint64_t), hipMemcpyDeviceToHost, s), "copy lines");
+        }
         // Coupling of the coordinates: sets the default window.
         double coh2 = 0.0, diag1 = 0.0, cn = 0.0;
         float kmax = 0.0f;
         if (rc == SCD_OK) step(probe_coupling(h, G, s, &coh2, &diag1, &cn, &kmax));
+        if (rc == SCD_OK && spread_possible(h) && line_counts[0]) {
+            h->lines = (double)line_counts[1] / line_counts[0];
+            h->lines_wide = (double)line_counts[2] / line_counts[0];
+        }
         if (rc == SCD_OK) {
             const double pairs = cn * (cn - 1.0);
             h->coherence = pairs > 0.0 ? (coh2 - diag1) / pairs : 0.0;
@@ -1785,6 +1806,12 @@ int scd_get_option(scd_handle_t h, const char* key, int64_t* value) {
     else if (!strcmp(key, "shared_fp64")) *value = h->wide;
     else if (!strcmp(key, "adapt")) *value = h->adapt;
     else if (!strcmp(key, "staged")) *value = h->staged;
+    else if (!strcmp(key, "next_spread")) {
+        LaunchPlan lp;
+        uint32_t n_groups = 1;
+        plan_epoch(h, &lp, &n_groups);
+        *value = h->us && h->spread && lp.kind == PLAN_PIPE && lp.spread ? 1 : 0;
+    }
     else if (!strcmp(key, "next_window")) {
         // Coordinates in flight the next epoch will use (read-only; synchronises the device).
         LaunchPlan lp;

@@ -437,6 +437,11 @@ hipError_t launch_norms(const int64_t* ptr, const int32_t* idx, const float* val
                         int blocks, float* out, float* cy, double* cyd, hipStream_t s);
 hipError_t launch_validate(const int64_t* ptr, uint32_t S, const int32_t* idx, const float* val, int64_t nnz,
                            int64_t bound, const float* y, int64_t ny, int pm1, int* flags, hipStream_t s);
+// How local the segments are: of up to kLineSegments segments, spread evenly, and kLineEntries entries of each, out[0]
+// counts the entries, out[1] and out[2] the 64-byte lines of an fp32 and of an fp64 shared vector that each segment's
+// entries lie in.  out holds kLineWords 64-bit words, zeroed here.
+constexpr uint32_t kLineSegments = 256, kLineEntries = 2048, kLineWords = 2;
+hipError_t launch_lines(const int64_t* ptr, const int32_t* idx, uint32_t C, uint32_t* out, hipStream_t s);
 // Coupling probe: kProbeRow probes in one pass, or one (np).  At most kProbeSlots of the most used
 // shared-vector entries, of at least kProbeMinHits, are summed in LDS (kProbeRow + 1 sums each).
 constexpr int kProbeRow = 8;

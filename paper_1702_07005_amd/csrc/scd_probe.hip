@@ -107,6 +107,44 @@ hipError_t launch_hits_histogram(const unsigned* hits, int64_t L, unsigned lo, u
     return hipGetLastError();
 }
 
+// Distinct keys that the workgroup's threads insert (open addressing in LDS; at most kLineEntries of them in twice as
+// many places).  True for the one insertion of each key.
+__device__ __forceinline__ bool line_insert(uint32_t* table, uint32_t key) {
+    constexpr uint32_t places = 2 * kLineEntries;
+    uint32_t at = (key * 0x9E3779B1u) % places;
+    for (;;) {
+        const uint32_t was = atomicCAS(table + at, 0xFFFFFFFFu, key);
+        if (was == 0xFFFFFFFFu) return true;
+        if (was == key) return false;
+        at = (at + 1u) % places;
+    }
+}
+
+// One workgroup per segment of the sample.  Exact for the entries it takes, in whatever order they are stored.
+__global__ __launch_bounds__(256) void k_lines(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, uint32_t C,
+                                               uint32_t* __restrict__ out) {
+    __shared__ uint32_t table[2 * kLineEntries];
+    const uint32_t c = (uint32_t)((uint64_t)blockIdx.x * C / gridDim.x);
+    const int64_t s0 = ptr[c], len = ptr[c + 1] - s0;
+    const uint32_t n = len < (int64_t)kLineEntries ? (uint32_t)len : kLineEntries;
+    if (threadIdx.x == 0 && n) atomicAdd(out, n);
+    for (int shift = 4; shift >= 3; --shift) {  // 16 fp32 or 8 fp64 entries a line
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < 2 * kLineEntries; i += 256) table[i] = 0xFFFFFFFFu;
+        __syncthreads();
+        uint32_t lines = 0;
+        for (uint32_t i = threadIdx.x; i < n; i += 256) lines += line_insert(table, (uint32_t)idx[s0 + i] >> shift) ? 1u : 0u;
+        for (int o = 32; o > 0; o >>= 1) lines += __shfl_xor(lines, o, 64);
+        if ((threadIdx.x & 63) == 0 && lines) atomicAdd(out + (5 - shift), lines);
+    }
+}
+
+hipError_t launch_lines(const int64_t* ptr, const int32_t* idx, uint32_t C, uint32_t* out, hipStream_t s) {
+    if (const hipError_t e = launch_fill_zero(reinterpret_cast<uint64_t*>(out), kLineWords, s); e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lines, dim3(std::min(C, kLineSegments)), dim3(256), 0, s, ptr, idx, C, out);
+    return hipGetLastError();
+}
+
 // ----------------------------------------------------------------------------------------
 // Coupling probe.  With a~_c = sigma_c a_c / sqrt(|a_c|^2 + mu) (sigma_c = the label for the SVM, 1
 // otherwise; mu = lambda N for the ridge steps, 0 for the SVM step), G = A~^T A~ holds the

@@ -69,6 +69,33 @@ def test_wide_groups_and_spread_copy(form, window, lanes, wide):
     assert np.max(np.abs(out[0] - out[1])) <= 1e-5 * np.max(np.abs(out[0]))
 
 
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("run,spread", [(1, 1), (2, None), (4, 0), (96, 0)])
+def test_spread_copy_only_where_entries_lie_apart(run, spread, wide):
+    # Columns whose entries are runs of neighbours, stored in a random order: packed, a run shares 64-byte lines.
+    rng = np.random.default_rng(run)
+    n, L, per = 5_000, 60_000, 96
+    start = np.stack([rng.choice(L // run, per // run, replace=False) for _ in range(n)]) * run
+    idx = (start[:, :, None] + np.arange(run)).reshape(n, per)
+    idx = rng.permuted(idx, axis=1).astype(np.int32)
+    val = (rng.standard_normal(n * per) / np.sqrt(per)).astype(np.float32)
+    p = synth.Problem("runs", "ridge_primal", "csc", L, n, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1), val,
+                      rng.standard_normal(L).astype(np.float32), 1e-2, 0)
+    s = scd.solver_for(p)
+    s.set_option("shared_fp64", wide)
+    s.set_option("window", 400)
+    i = s.info()
+    lines = np.mean([len(np.unique(r >> (3 if wide else 4))) for r in idx[:500]]) / per
+    print(f"run {run} wide {wide}: {i['kernel']} lines per entry {lines:.3f} spread {s.get_option('next_spread')}", flush=True)
+    assert i["kernel"] == "pipelined" and i["window"] == 400
+    assert s.get_option("next_spread") == (lines >= (0.7 if wide else 0.47)) and spread in (None, s.get_option("next_spread"))
+    follow_oracle(p, s, 2)
+    s.set_option("window", 0)
+    s.set_option("spread", 0)
+    assert s.get_option("next_spread") == 0
+    s.close()
+
+
 def test_wide_groups_with_segments_of_every_length():
     # segments from empty to beyond a wave's register slices (64 x 4 entries)
     rng = np.random.default_rng(4)
