@@ -225,7 +225,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
  *                 lockstep rounds of
  *                 auto_window coordinates: the eight workgroups each hold an index range of the shared
  *                 vector, every coordinate of a round is a wave of each, and the waves exchange partial
- *                 inner products.  scd_info_t still names kernel 4, with window = auto_window.  It needs a
+ *                 inner products.  scd_info_t still names kernel 4, with window = auto_window (scd_get_option
+ *                 tells it apart: "next_lockstep").  It needs a
  *                 copy of A grouped by range (6 bytes per stored entry and 36 per coordinate, made when
  *                 this first applies: at create or on an option; synchronising; without the memory it is
  *                 not used).  0 = never.
@@ -314,7 +315,8 @@ int scd_set_state(scd_handle_t h, const float *model_dev, const float *shared_de
 int scd_set_option(scd_handle_t h, const char *key, int64_t value);
 /* Reads an option's value, or a read-only key: "next_window", the coordinates the next epoch will
  * keep in flight at most (with an adaptive window, the value the last epoch left in device memory;
- * this read synchronises the device); "next_spread", 1 if the next scd_epochs runs on the spread copy. */
+ * this read synchronises the device); "next_spread", 1 if the next scd_epochs runs on the spread copy;
+ * "next_lockstep", 1 if it runs in lockstep rounds (option "lockstep"), for which scd_info_t names kernel 4. */
 int scd_get_option(scd_handle_t h, const char *key, int64_t *value);
 
 int scd_get_info(scd_handle_t h, scd_info_t *info);

@@ -1806,6 +1806,12 @@ int scd_get_option(scd_handle_t h, const char* key, int64_t* value) {
     else if (!strcmp(key, "shared_fp64")) *value = h->wide;
     else if (!strcmp(key, "adapt")) *value = h->adapt;
     else if (!strcmp(key, "staged")) *value = h->staged;
+    else if (!strcmp(key, "next_lockstep")) {
+        LaunchPlan lp;
+        uint32_t n_groups = 1;
+        plan_epoch(h, &lp, &n_groups);
+        *value = lp.lock;
+    }
     else if (!strcmp(key, "next_spread")) {
         LaunchPlan lp;
         uint32_t n_groups = 1;

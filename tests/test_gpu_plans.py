@@ -459,9 +459,11 @@ def _rows(lens, L, form, lam, seed, repeat=False, positive=False):
 
 
 def _lockstep(s):
-    """The lockstep kernel runs the epochs: a workgroup per coordinate, the whole automatic window."""
+    """The lockstep kernel runs the epochs, with the whole automatic window."""
     i = s.info()
-    return i["kernel"] == "pipelined" and i["group_lanes"] == 256 and i["window"] == i["auto_window"] <= 16
+    lock = s.get_option("next_lockstep") == 1
+    assert not lock or (i["kernel"] == "pipelined" and i["group_lanes"] == 256 and i["window"] == i["auto_window"] <= 16)
+    return lock
 
 
 LOCKSTEP = {
@@ -490,7 +492,7 @@ def test_lockstep_follows_the_oracle(case, wide):
     empty = np.diff(p.ptr) == 0
     assert np.all(model[empty] == (1.0 if p.form == "svm_dual" else 0.0))
     s.set_option("lockstep", 0)
-    assert not _lockstep(s) or info["auto_window"] * 4 // 5 == info["auto_window"]
+    assert not _lockstep(s)
     s.close()
 
 
@@ -564,12 +566,10 @@ def test_lockstep_selection():
     p = LOCKSTEP["text"]()
     s = scd.solver_for(p)
     assert _lockstep(s) and s.get_option("lockstep") == 1
-    auto = s.info()["auto_window"]
     for key, value in (("lockstep", 0), ("group", 256), ("pipeline", 0), ("fresh_reads", 1), ("team", 0), ("window", 1)):
         before = s.get_option(key)
         s.set_option(key, value)
-        i = s.info()
-        assert (i["kernel"], i["group_lanes"], i["window"]) != ("pipelined", 256, auto), key
+        assert not _lockstep(s), key
         s.epochs(0, 1)
         s.set_option(key, before)
         assert _lockstep(s), key
@@ -580,23 +580,23 @@ def test_lockstep_selection():
     fresh = orc.fresh_shared(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, f64(gm))
     assert np.max(np.abs(f64(gs) - fresh)) <= 1e-4 * np.max(np.abs(fresh))
     s.close()
-    # more used entries than eight workgroups' LDS holds: 400 rows of 450 entries, each index once
-    n, per = 400, 450
-    idx = np.arange(n * per, dtype=np.int32).reshape(n, per)
-    idx[:, :200] = np.arange(200)  # shared, so that the window binds
-    q = synth.Problem("wide", "ridge_dual", "csr", n, n * per, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
-                      np.ones(n * per, dtype=np.float32), np.ones(n, dtype=np.float32), 1e-3, 0)
-    many = synth.Problem("wider", "ridge_dual", "csr", 2 * n, 2 * n * per, np.arange(2 * n + 1, dtype=np.int64) * per,
-                         np.concatenate([idx.reshape(-1), np.where(idx < 200, idx, idx + n * per).reshape(-1)]).astype(np.int32),
-                         np.ones(2 * n * per, dtype=np.float32), np.ones(2 * n, dtype=np.float32), 1e-3, 0)
-    for prob, used in ((q, 200 + 400 * 250), (many, 200 + 800 * 250)):
-        s = scd.solver_for(prob)
+    # used entries that eight workgroups' LDS holds (8 x 20,471), and more: 256 rows of 200 common indices and
+    # their own
+    rng = np.random.default_rng(5)
+    n = 256
+    for own, fits in ((638, True), (640, False)):
+        used = 200 + n * own
+        idx = np.concatenate([np.broadcast_to(np.arange(200), (n, 200)),
+                              200 + np.arange(n)[:, None] + n * np.arange(own)[None, :]], axis=1).astype(np.int32)
+        per = 200 + own
+        q = synth.Problem("wide", "ridge_dual", "csr", n, used, np.arange(n + 1, dtype=np.int64) * per, idx.reshape(-1),
+                          (rng.standard_normal(n * per) / np.sqrt(per)).astype(np.float32),
+                          rng.standard_normal(n).astype(np.float32), 1 / n, 0)
+        s = scd.solver_for(q)
         i = s.info()
-        assert len(np.unique(prob.idx)) == used
         print(f"{used} used entries: kernel {i['kernel']} window {i['window']} auto {i['auto_window']}", flush=True)
-        if i["auto_window"] >= 5:  # below, four fifths of the window is the window less one at most
-            assert _lockstep(s) == (used < 163_000)
-        s.epochs(0, 2)
+        assert 2 <= i["auto_window"] <= 16 and _lockstep(s) == fits == (used <= 8 * 20_471)
+        follow_oracle(q, s, 2)
         s.close()
 
 
@@ -667,7 +667,8 @@ def test_lockstep_limits_on_the_entries_in_flight():
         in_flight = i["auto_window"] * rows
         want = 2 <= i["auto_window"] <= 16 and in_flight <= (24_576 if p.nnz * 6 <= 2_500_000 else 12_288)
         print(f"{rows} x {cols}: auto {i['auto_window']} in flight {in_flight} window {i['window']}", flush=True)
-        assert i["kernel"] == "pipelined" and i["window"] == (i["auto_window"] if want else i["auto_window"] * 4 // 5)
+        assert i["kernel"] == "pipelined" and _lockstep(s) == want
+        assert i["window"] == (i["auto_window"] if want else i["auto_window"] * 4 // 5)
         follow_oracle(p, s, 3)
         s.close()
 
