@@ -49,11 +49,19 @@ def algorithmic_bytes(prob) -> int:
     return 16 * prob.nnz + 24 * prob.C
 
 
+def kernel_sources() -> list:
+    """Every file the library is compiled from: its sources and their headers."""
+    import glob
+
+    from paper_1702_07005_amd import build
+
+    return [*build.SOURCES, *sorted(glob.glob(os.path.join(build.CSRC, "*.h")))]
+
+
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("scd_device.h", "scd_epoch.hip", "scd_hot.hip", "scd_team.hip", "scd_lock.hip", "scd_split.hip", "scd_setup.hip",
-              "scd_kernels.h", "scd_api.cpp"):
-        with open(os.path.join(ROOT, "paper_1702_07005_amd", "csrc", f), "rb") as fh:
+    for path in kernel_sources():
+        with open(path, "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 

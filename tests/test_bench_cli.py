@@ -25,6 +25,18 @@ def test_kernel_source_hash_is_stable_and_tracks_sources(tmp_path, monkeypatch):
 
     h = bench.kernel_source_hash()
     assert h == bench.kernel_source_hash() and len(h) == 16
+    # every source and header of the library enters it
+    from paper_1702_07005_amd import build
+
+    names = {os.path.basename(f) for f in bench.kernel_sources()}
+    assert names == {f for f in os.listdir(build.CSRC) if f.endswith((".hip", ".cpp", ".h"))} - {"ceiling.hip"}
+    for f in bench.kernel_sources():
+        copy = tmp_path / os.path.basename(f)
+        copy.write_bytes(open(f, "rb").read() + b"\n")
+        with monkeypatch.context() as m:
+            m.setattr(bench, "kernel_sources", lambda f=f, copy=copy, all=bench.kernel_sources(): [
+                str(copy) if g == f else g for g in all])
+            assert bench.kernel_source_hash() != h, f
     # a counter summary is used only when it was taken on the current sources
     (tmp_path / "profiles").mkdir()
     path = tmp_path / "profiles" / "epoch_w_traffic.json"
