@@ -1554,6 +1554,7 @@ int scd_epochs(scd_handle_t h, uint64_t seed, int32_t n_epochs, void* stream) {
             sa.units = h->split_units;
             sa.partials = h->split_partials;
             sa.n_units = h->split_n;
+            sa.tag = 1;
             sa.spin_limit = h->hot_wait_limit > 0 ? (uint32_t)h->hot_wait_limit : kHotSpinLimit;
             sa.err = h->hot_err;
             HIP_TRY(launch_epoch_split(h->form, h->wide != 0, lp.fresh != 0, sa, lp.part, h->split_tiles, h->split_units,

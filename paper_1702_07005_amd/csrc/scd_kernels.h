@@ -401,8 +401,10 @@ __host__ __device__ inline uint32_t split_units_of(int64_t len, uint32_t part) {
 struct SplitArgs {
     EpochArgs e;           // e.perm: the epoch's permutation; e.queue, e.chunk as for the queued kernel
     const SplitUnit* units;
-    uint64_t* partials;    // [n_units]: cleared by the pre-pass; GATHER unit u writes (fp32 bits | 1 << 32) at partials[u]
+    uint64_t* partials;    // [n_units]: cleared by the pre-pass; GATHER unit u writes (fp32 bits | tag << 32) at partials[u]
     uint32_t n_units;
+    uint32_t tag;          // not 0.  An argument and not a constant: with a constant the compiler spills 614 vector
+                           // registers of k_epoch_split (text-ridge columns, 1.3 B entries: 70 and 117 ms an epoch)
     uint32_t spin_limit;   // bounded waits: after this many sleeps a SCATTER unit gives up and sets *err
     int* err;
 };

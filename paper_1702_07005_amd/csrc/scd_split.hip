@@ -11,7 +11,7 @@
 //   FULL    (len <= part)  gather, reduce, step (eq. update_primal, the SVM dual step, or eq.
 //                          update_dual), model store, scatter: one unit of the queued kernel;
 //   GATHER  part i of k    gather part i, reduce, publish the partial inner product in a 64-bit slot
-//                          (fp32 bits | 1 << 32) at partials[unit index], which the pre-pass cleared;
+//                          (fp32 bits | tag << 32) at partials[unit index], which the pre-pass cleared;
 //   SCATTER part i of k    wait until the k GATHER slots of the coordinate are filled,
 //                          sum them in a fixed order (the same in every part, so every part takes the
 //                          bitwise-same step), store the model (part 0) and scatter part i.
@@ -266,7 +266,7 @@ __device__ __forceinline__ uint32_t split_step(const SplitArgs& sa, const Shared
                         const uint64_t v =
                             __hip_atomic_load(const_cast<uint64_t*>(slot + q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         pv[t] = (uint32_t)v;
-                        have = have && (uint32_t)(v >> 32) == 1u;
+                        have = have && (uint32_t)(v >> 32) == sa.tag;
                     }
                 }
                 if (__all(have)) break;
@@ -318,7 +318,7 @@ __device__ __forceinline__ uint32_t split_step(const SplitArgs& sa, const Shared
                     if (wb + r * 256 < len) split_atomic(ub, (uint32_t)ci[r], (int64_t)(lane + r * 256) < len, coef * cv[r]);
             }
         } else if (lane == 0) {
-            const uint64_t v = (1ull << 32) | (uint64_t)__builtin_bit_cast(uint32_t, g);
+            const uint64_t v = ((uint64_t)sa.tag << 32) | (uint64_t)__builtin_bit_cast(uint32_t, g);
             __hip_atomic_store(sa.partials + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
