@@ -37,7 +37,12 @@
 //
 // Placement: workgroup b runs on XCD b mod 8; the members are those of one XCD (correct on any, slower
 // across).  K is at most 8, so that the four kernels a process runs at once by default all fit one XCD's 32
-// CUs, one member each, and none waits for members that cannot start; handles use the XCDs in turn.
+// CUs, one member each, and none waits for members that cannot start; handles use the XCDs in turn.  Beside the
+// other kernels with waits between workgroups: a team epoch has at most 32 workgroups per XCD, of which a CU takes four
+// (and keeps none from a member with less than all its LDS), so it is resident whole beside any members and ends
+// without them; a staged epoch claims its batches, so any one of its stagers lets it end.  Members that could not start
+// do so then, well within the wait limit.  (More than four kernels at once, GPU_MAX_HW_QUEUES above its default, may
+// hold five lockstep epochs of one XCD, 40 CUs: their waits end with an error.)
 //
 // Measured, pipelined at its share of the automatic window W and this kernel at W, per epoch: 2,000 x 200 dense
 // (7 and 9 in flight) 55 and 46 us; 500 x 60 dense (2 and 3) 49 and 31 us; text rows of 370 entries on 166,000

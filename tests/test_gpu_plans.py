@@ -691,6 +691,30 @@ def test_lockstep_handles_side_by_side():
         s.close()
 
 
+def test_kernels_with_waits_between_workgroups_side_by_side():
+    # Epochs of lockstep, team (256 workgroups) and staged solvers queued on streams of their own: whatever
+    # workgroups are resident first, every epoch ends and no wait times out.
+    team = synth.make("dense_ridge", n_rows=4_000, n_cols=300)
+    problems = [LOCKSTEP["text"](), team, synth.make("click_svm", n_rows=60_001, n_cols=70_001), LOCKSTEP["dual"]()]
+    solvers = [scd.solver_for(p) for p in problems]
+    solvers[1].set_option("window", 16)
+    solvers[1].set_option("team", 16)
+    assert [s.info()["kernel"] for s in solvers] == ["pipelined", "team", "hot_staged", "pipelined"]
+    assert _lockstep(solvers[0]) and _lockstep(solvers[3])
+    streams = [torch.cuda.Stream() for _ in solvers]
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for s, st in zip(solvers, streams):
+            s.epochs(0, 5, stream=st)
+    torch.cuda.synchronize()
+    for p, s in zip(problems, solvers):
+        gm, gs, e = s.get_state()
+        assert e == 30 and s.duality_gap() >= 0.0  # raises where a wait timed out
+        fresh = orc.fresh_shared(p.form, p.n_rows, p.n_cols, p.ptr, p.idx, p.val, p.y, p.lam, f64(gm))
+        assert np.max(np.abs(f64(gs) - fresh)) <= 1e-4 * np.max(np.abs(fresh)), p.form
+        s.close()
+
+
 def test_lockstep_replayed_from_a_graph():
     # A captured call of two epochs repeats their visiting orders at every replay.  Replays between eager
     # epochs and state reads follow a solver that runs the same orders eagerly: the steps are the same, and
