@@ -215,10 +215,9 @@ def main():
     stream = torch.cuda.current_stream()
     solver = scd.solver_for(prob, device=dev)
     info = solver.info()
-    # The library runs an unbound pipelined plan on its spread copy of a shared vector of at most
-    # 4 M entries, copied out and back inside each scd_epochs call.
-    spread = (info["kernel"] == "pipelined" and info["window"] >= prob.C and prob.L <= (1 << 22)
-              and solver.get_option("spread") == 1)
+    # A pipelined plan may run on the spread copy of the shared vector, copied out and back inside each
+    # scd_epochs call.
+    spread = solver.get_option("next_spread") == 1
     zeros_m = torch.zeros(prob.C, dtype=torch.float32, device=dev)
     zeros_s = torch.zeros(prob.L, dtype=torch.float32, device=dev)
 

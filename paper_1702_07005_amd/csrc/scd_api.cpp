@@ -98,9 +98,11 @@ constexpr double kTeamMaxSkew = 4.0;  // longest segment at most this many times
 constexpr int64_t kTeamMinSharedBytes = int64_t(4) << 20;
 // Staged hot-set epochs, automatic choice: matrices whose entries take more than this (8 bytes each), and
 // a GPU with CUs for the stagers.  Click rows, settled, single workgroup against staged, ms an epoch:
-// 50,000 rows (15.6 MB) 1.39 and 0.59, 100,000 3.27 and 1.15, 500,000 15.9 and 5.7, 1 M 36 and 11.3.  The
-// smallest matrices, of which a program may run many at once on its streams, keep to the one workgroup:
-// a staged epoch wants 17 of one XCD's CUs.
+// 20,000 rows (6.2 MB) 0.72 and 0.28, 60,000 1.69 and 0.78, 100,000 3.36 and 1.27, 400,000 13.8 and 4.97, 1 M 36 and
+// 11.3; so the crossing lies below all of them, and the line is not where it could be.  Several solvers on streams of
+// their own hold their rates: four of 20,000 rows run 5,400 and 12,900 epochs a second in all (one 1,380 and
+// 3,590), four of 100,000 1,170 and 3,060 (one 298 and 786), four of 400,000 261 and 796 (one 73 and 201).  Batches
+// are claimed from a counter, so a launch progresses with any one of its 16 stager workgroups resident.
 constexpr int64_t kStagedMinBytes = int64_t(16) << 20;
 // An automatic window above what the hot-set kernel holds is cut to that for a staged epoch, up to this
 // window and where the hot set covers at least this share of the entries: the pipelined kernel's atomics
@@ -153,7 +155,7 @@ struct scd_solver {
     int64_t pipeline = 1;
     int64_t queue_chunk = 0;  // option: positions per queue claim, 0 = by window
     double lines = 1.0, lines_wide = 1.0;  // 64-byte lines per entry of a segment, fp32 and fp64 (spread_possible)
-    int64_t spread = 1;       // option: run an unbound pipelined plan on the spread copy
+    int64_t spread = 1;       // option: run a pipelined plan on the spread copy where that pays
     void* us = nullptr;       // spread copy of the shared vector (entry i at byte i << kSpreadShift),
                               // allocated at create when it takes at most kSpreadMaxBytes
     double* sink = nullptr;  // pipelined kernel, fp64 shared vector: slots inactive lanes add 0 to
@@ -389,11 +391,12 @@ int team_members(const scd_solver* h, int64_t* teams) {
 // entries may fit.  Options that ask for another schedule turn it off.
 //
 // Its eight CUs take all the entries of a round, so it pays while those are few, or while the grouped copy
-// stays in one XCD's 4 MB of L2.  Pipelined against lockstep, entries in flight (W x mean length), ms an epoch:
-// text rows of 300 to 900, 1,800 to 10,800 in flight, 8 to 27 MB of copy: 0.57-2.64 and 0.37-1.75 (1.4 to 2.3
-// times faster, all of 14); dense 2,000 x 200, 18,000 to 22,000 in flight, 2.4 MB: 0.055 and 0.046; 2,000 x 300,
-// 22,000 in flight, 3.6 MB: 0.079 and 0.083; 2,500 x 375, 35,000 in flight, 5.6 MB: 0.072 and 0.092;
-// 4,000 x 600, 64,000 in flight: 0.106 and 0.171.
+// stays in one XCD's 4 MB of L2.  Pipelined over lockstep time by entries in flight (W x mean length) and copy:
+// up to 12,288, text rows 1.4 to 2.4 (copies of 8 to 333 MB), dense 1.1 to 1.5; up to 24,576 with at most 2.5 MB,
+// dense 1.03 to 1.27.  Beyond the lines, with them lifted: up to 24,576 and 2.6 to 42 MB, 0.95 (dense 2,000 x 300) to 2.1
+// (text rows of 1,600), 11 of 12 at least 1.06; 30,000 to 48,000 0.76 (dense 2,500 x 300), 1.00, 1.04, 1.04, 1.9 (5,000 x 150),
+// 2.1 (6,000 x 100).  So the crossing lies between 20,000 and 48,000 in flight and depends on the length more than on
+// the copy; the lines are on its safe side.
 //
 // A round's coordinates all step from the state before the round.  Where they pull the same way (a positive mean
 // off-diagonal entry of G, as positive values give), that overshoots more than the draining groups do, which take

@@ -5,9 +5,10 @@
 // atomic adds run at 20-25 G/s however they are spread, and far slower where many hit one address
 // (click-log data: the commonest values of a field are in a fifth of all rows).  So the adds of the
 // most used entries are summed in LDS, a copy per workgroup, and only the sums go to memory; the
-// others go there directly.  scd_create, before and after: 5 M click rows (195 M entries) 295 and 37 ms,
-// 50 M rows 2.5 and 0.38 s, 350,000 text rows (1.3 B entries, a third of which have slots) 0.97 and
-// 0.50 s, 5 M entries spread evenly (no slots) 3.4 and 2.9 ms.
+// others go there directly, a row of eight probes' sums as one request.  scd_create with an atomic per add, with
+// slots, and with rows as one request too: 5 M click rows (195 M entries) 295, 37 and 18 ms, 50 M rows 2.5, 0.38 and
+// 0.17 s, 350,000 text rows (1.3 B entries, a third of which have slots) 0.97, 0.50 and 0.20 s, 5 M entries spread evenly
+// (no slots) 3.3, 2.9 and 1.05 ms.
 #include <algorithm>
 
 #include "scd_device.h"
