@@ -937,7 +937,12 @@ int build_lock_tables(scd_solver* h, hipStream_t s) {
     if (h->nnz == 0 || h->max_seg >= (int64_t(1) << 32)) return SCD_OK;
     unsigned* hits = nullptr;
     bool own_hits = false;
-    if (int r = need_hits(h, &hits, &own_hits, s)) return r == SCD_ERR_OOM ? SCD_OK : r;
+    if (int r = need_hits(h, &hits, &own_hits, s)) {
+        if (r != SCD_ERR_OOM) return r;
+        (void)hipGetLastError();
+        g_err.clear();
+        return SCD_OK;
+    }
     LockArgs t{};
     t.K = (uint32_t)kLockMaxMembers;
     const uint32_t cap = (uint32_t)std::min<size_t>(65535, (h->max_lds - 64) / sizeof(double) - 1);
@@ -1094,7 +1099,7 @@ int obj_blocks(const scd_solver* h, int G) { return objective_blocks(h->C, G); }
 // where memory for a row of kProbeRow values per shared-vector entry is free; otherwise each has its
 // own, with h->u as the probe vector.  Synchronises; h->u and h->model are scratch here.
 int probe_coupling(scd_solver* h, int G, hipStream_t s, double* coh2, double* diag1, double* cn, float* kmax) {
-    static_assert(kProbes % kProbeRow == 0, "whole passes");
+    static_assert(kProbes == kProbeRow, "one pass");
     ProbeArgs a{};
     a.ptr = h->ptr;
     a.idx = h->idx;

@@ -2,7 +2,7 @@
 // the threshold that selects the most used entries, and the coupling probe.
 //
 // All of them scatter: one add per stored entry (hits) or nine (the probe's vectors).  Device-scope
-// atomic adds run at 20-25 G/s however they are spread, and far slower where many hit one address
+// atomic adds run at 20-25 G requests/s of up to 64 bytes, and far slower where many hit one address
 // (click-log data: the commonest values of a field are in a fifth of all rows).  So the adds of the
 // most used entries are summed in LDS, a copy per workgroup, and only the sums go to memory; the
 // others go there directly, a row of eight probes' sums as one request.  scd_create with an atomic per add, with
